@@ -68,7 +68,7 @@ def kernel_name(shape_name, R):
         rows, cpl = STRIP_GEOMETRY[shape_name]
         return f"strip_kernel<{R}, false, {rows}, {cpl}>"
     tw, th = TILE_GEOMETRY[shape_name]
-    return f"step_kernel<{R}, {tw}, {th}>"
+    return f"step_kernel<{R}, {tw}, {th}, false, false, false>"
 
 
 KERNEL_SOURCES = ("paper_2006_10406_amd/csrc/eed4_strip.h",

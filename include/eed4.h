@@ -69,7 +69,7 @@ extern "C" {
 /* Launch each inner step directly instead of replaying a captured hipGraph
  * of the cycle (same results; for comparison). */
 #define EED4_NO_GRAPH        0x4
-/* Use the workgroup-tile step kernel (64 x 32 outputs per 256-thread
+/* Use the workgroup-tile step kernel (60 x 32 outputs per 256-thread
  * workgroup, stages separated by barriers) instead of the default wave-strip
  * kernel.  Both compute the same step with bitwise the same results. */
 #define EED4_TILE_KERNEL     0x8
@@ -78,7 +78,8 @@ extern "C" {
  * (the autotuners of eed4_inpaint and eed4_inpaint_batched; eed4_fsi_cycle,
  * eed4_fsi_step and eed4_backward use the choice eed4_inpaint made for the
  * same problem size, else a work-size rule):
- * 0: 64x32 workgroup tiles, 1: 64x16 tiles, 2: 32x32 tiles, 3: wave strips of
+ * 0: 64x32 workgroup tiles (64 lanes, of which 60 output columns, by 32 rows),
+ * 1: 64x16 tiles, 2: 32x32 tiles (28 output columns), 3: wave strips of
  * 60 columns x >= 64 rows, 4: strips of >= 136 rows, 5: strips of >= 28 rows,
  * 6: strips of >= 8 rows, 7: strips of 124 columns (two per lane) x >= 64 rows,
  * 8: 124-column strips of >= 28 rows, 9: 32x16 tiles, 10: 16x16 tiles.
@@ -101,11 +102,13 @@ extern "C" {
  *   EED4_MU3_ARITHMETIC    (mu_1 + mu_2)/2 = (1 + g)/2
  *   EED4_MU3_MAX           max(mu_1, mu_2) = 1.
  * Every eigenvalue stays in [0, 1], so the step bound tau <= 1/16 holds for
- * all of them.  A non-default variant runs the 60-column strip kernel of
- * shape 5 (EED4_FORCE_SHAPE may name only that shape; EED4_TILE_KERNEL is
- * EED4_EINVAL) in every entry point: eed4_inpaint, eed4_fsi_cycle,
- * eed4_fsi_step, the batched calls (no shape tuning) and, with the matching
- * reverse step, eed4_backward. */
+ * all of them.  A non-default variant is reported as shape 5 (EED4_FORCE_SHAPE
+ * may name only that shape; EED4_TILE_KERNEL is EED4_EINVAL) in every entry
+ * point and is not tuned: eed4_inpaint, eed4_fsi_cycle, eed4_fsi_step and the
+ * recompute of eed4_backward run the 60-column strips of shape 5 on large
+ * problems or when it is forced, and workgroup tiles of 60 columns with bitwise
+ * the same results on smaller ones; the batched calls and the reverse step run
+ * the strips. */
 #define EED4_CHARBONNIER       0
 #define EED4_PERONA_MALIK      1
 #define EED4_PERONA_MALIK_EXP  2

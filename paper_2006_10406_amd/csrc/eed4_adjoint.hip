@@ -1163,7 +1163,7 @@ extern "C" int eed4_backward(const float *ckpt, const uint8_t *mask, const float
     t.H = H;
     t.W = W;
     t.R = R;
-    const int fshape = step_shape(p, B, H, W);      // forward recompute
+    const int fshape = run_shape(p, B, H, W);      // forward recompute
     hipError_t e;
 #define EED4_TRY(x, what)                                    \
     do {                                                     \

@@ -341,6 +341,16 @@ int step_shape(const eed4_params *p, int B, int H, int W)
     return default_step_shape(R, B, H, W);
 }
 
+// The kernel shape that runs: step_shape's, but a tensor variant, whose public
+// shape id is fixed, takes the shape of its size rule unless that id is forced.
+int run_shape(const eed4_params *p, int B, int H, int W)
+{
+    const int shape = step_shape(p, B, H, W);
+    return model_of_flags(p->flags) != 0 && !((p->flags >> 8) & 0xff)
+               ? variant_shape(eed4_radius(p->sigma), B, H, W)
+               : shape;
+}
+
 int default_step_shape(int R, int B, int H, int W)
 {
     const long long waves = (long long)tiles_per_image(kShapeStrip, R, H, W) * B;
@@ -652,7 +662,7 @@ int eed4_inpaint(float *u, const uint8_t *mask, const float *known, int B, int H
 
     CycleJob j;
     j.S = u; j.X = (float *)(base + L.X); j.Y = (float *)(base + L.Y);
-    j.mask = mask; j.B = B; j.H = H; j.W = W; j.R = R; j.shape = step_shape(p, B, H, W); j.n = p->cycle_len;
+    j.mask = mask; j.B = B; j.H = H; j.W = W; j.R = R; j.shape = run_shape(p, B, H, W); j.n = p->cycle_len;
     j.sigma = p->sigma; j.tau = p->tau; j.lambda = p->lambda; j.model = model_of_flags(p->flags);
     j.partials = (double *)(base + L.partials); j.sums = (double *)(base + L.sums);
     double *hist_dev = (double *)(base + L.hist);
@@ -701,7 +711,7 @@ int eed4_fsi_cycle(float *u, const uint8_t *mask, const float *known, int B, int
     hipStream_t s = (hipStream_t)stream;
     CycleJob j;
     j.S = u; j.X = (float *)(base + L.X); j.Y = (float *)(base + L.Y);
-    j.mask = mask; j.B = B; j.H = H; j.W = W; j.R = eed4_radius(p->sigma); j.shape = step_shape(p, B, H, W);
+    j.mask = mask; j.B = B; j.H = H; j.W = W; j.R = eed4_radius(p->sigma); j.shape = run_shape(p, B, H, W);
     j.n = p->cycle_len; j.sigma = p->sigma; j.tau = p->tau; j.lambda = p->lambda;
     j.model = model_of_flags(p->flags);
     j.partials = (double *)(base + L.partials); j.sums = d_sums;
@@ -736,8 +746,8 @@ int eed4_fsi_step(const float *ucur, const float *uprev, float *uout, const uint
     if (o0 < c0 + bytes && c0 < o0 + bytes) return EED4_EINVAL;
     const int R = eed4_radius(p->sigma);
     StepArgs a = make_args(p->sigma, R, p->tau, p->lambda, k, model_of_flags(p->flags));
-    hipError_t e = launch_step(R, step_shape(p, B, H, W), ucur, uprev, uout, nullptr, mask, B, H, W, a, nullptr,
-                               (hipStream_t)stream);
+    hipError_t e = launch_step(R, run_shape(p, B, H, W), ucur, uprev, uout, nullptr, mask, B, H, W, a,
+                               nullptr, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(e, "fsi step launch");
     return EED4_OK;
 }

@@ -29,23 +29,24 @@ __global__ __launch_bounds__(256) void hold_kernel(float *u, const uint8_t *__re
         if (m[j]) u[i0 + j] = known[i0 + j];
 }
 
-template <int R, int TW, int TH>
-__global__ __launch_bounds__(tile_threads(TW, TH)) void step_kernel(
+// Fused step over workgroup tiles.  RES adds the cycle residual, GEN selects the
+// tensor variant at run time, VST also writes K_sigma * u^k (into vout).
+template <int R, int TW, int TH, bool RES, bool GEN, bool VST>
+__global__ __launch_bounds__(256) void step_kernel(
     const float *ucur, const float *uprev, float *uout, const float *ref,
     const uint8_t *__restrict__ mask, int H, int W, int nbx, int tiles_per_img, StepArgs a,
-    double *partials)
+    double *partials, float *vout)
 {
-    constexpr int NTH = tile_threads(TW, TH);
-    __shared__ __attribute__((aligned(16))) float smem[TileGeo<R, TW, TH, NTH>::SMEM];
+    __shared__ __attribute__((aligned(16))) float smem[TileGeo<R, TW, TH>::SMEM];
     const int tile = xcd_tile(blockIdx.x, gridDim.x);
     const int b = tile / tiles_per_img;
     const int t = tile - b * tiles_per_img;
     const int ty = t / nbx, tx = t - ty * nbx;
     const size_t off = (size_t)b * H * W;
-    step_tile<R, TW, TH, NTH>(smem, ucur + off, uprev + off, uout + off,
-                              ref ? ref + off : nullptr, mask + off, H, W, ty, tx, a.w, a.tau,
-                              a.alpha, 0.25f * a.inv_lam2,
-                              partials ? partials + 2 * (size_t)tile : nullptr);
+    step_tile<R, TW, TH, kThreads, GEN, VST>(
+        smem, ucur + off, uprev + off, uout + off, RES ? ref + off : nullptr, mask + off, H, W, ty,
+        tx, a.w, a.tau, a.alpha, 0.25f * a.inv_lam2, RES ? partials + 2 * (size_t)tile : nullptr,
+        a.model, VST ? vout + off : nullptr);
 }
 
 // Fused step over wave strips.  GEN selects the tensor variant at run time
@@ -242,7 +243,21 @@ int tiles_per_image(int shape, int R, int H, int W)
         return ((W + sw - 1) / sw) * ((H + oh - 1) / oh);
     }
     const TileShape ts = kTileShapes[tile_index(shape)];
-    return ((W + ts.tw - 1) / ts.tw) * ((H + ts.th - 1) / ts.th);
+    const int sw = tile_cols(ts.tw);
+    return ((W + sw - 1) / sw) * ((H + ts.th - 1) / ts.th);
+}
+
+// Kernel shape a tensor variant runs (the public shape id of a variant stays
+// kShapeStripShort): the strips from about 3072 waves on, where they are level
+// with the 60 x 32 tiles (FOEED at 2560^2: 25.5 against 25.8 us; the variants
+// at 2048^2 24.6 against 19.2 us, at 2896^2 30.4 against 32.1 us), and 60 x 16
+// tiles where those of 32 rows would be fewer than four a CU (1024^2: 8.6 us,
+// 28-row strips 20.6 us).
+int variant_shape(int R, int B, int H, int W)
+{
+    const long long waves = (long long)tiles_per_image(kShapeStripShort, R, H, W) * B;
+    if (waves >= 3072) return kShapeStripShort;
+    return (long long)tiles_per_image(0, R, H, W) * B >= 1024 ? 0 : 1;
 }
 
 template <int R, int ROWS, int CPL = 1, bool GEN = false>
@@ -294,32 +309,6 @@ static hipError_t launch_keepv_t(const float *ucur, const float *uprev, float *u
     return hipGetLastError();
 }
 
-// Strip height of the keep-v step for a forward step shape: tensor variants
-// run 28-row strips; FOEED keeps the height of a strip shape (wide shapes map
-// to their height) and runs 8-row strips in place of a tile shape (small
-// images, where tiles win).
-static int keepv_rows(int shape, int model)
-{
-    if (model != 0) return 28;
-    switch (shape) {
-    case kShapeStrip: case kShapeStripTall: case kShapeStripWide: return 64;
-    case kShapeStripShort: case kShapeStripWideShort: return 28;
-    default: return 8;
-    }
-}
-
-template <int R>
-static hipError_t launch_keepv_r(int shape, const float *ucur, const float *uprev, float *uout,
-                                 float *vout, const uint8_t *mask, int B, int H, int W,
-                                 const StepArgs &a, hipStream_t s)
-{
-    const int rows = keepv_rows(shape, a.model);
-    if (a.model != 0) return launch_keepv_t<R, 28, true>(ucur, uprev, uout, vout, mask, B, H, W, a, s);
-    if (rows == 64) return launch_keepv_t<R, 64, false>(ucur, uprev, uout, vout, mask, B, H, W, a, s);
-    if (rows == 28) return launch_keepv_t<R, 28, false>(ucur, uprev, uout, vout, mask, B, H, W, a, s);
-    return launch_keepv_t<R, 8, false>(ucur, uprev, uout, vout, mask, B, H, W, a, s);
-}
-
 template <int R>
 static hipError_t launch_blur_r(const float *u, float *v, int B, int H, int W, const StepArgs &a,
                                 hipStream_t s)
@@ -332,18 +321,36 @@ static hipError_t launch_blur_r(const float *u, float *v, int B, int H, int W, c
     return hipGetLastError();
 }
 
-template <int R, int TW, int TH>
+template <int R, int TW, int TH, bool GEN = false>
 static hipError_t launch_step_t(const float *ucur, const float *uprev, float *uout,
                                 const float *ref, const uint8_t *mask, int B, int H, int W,
                                 const StepArgs &a, double *partials, hipStream_t s)
 {
-    const int nbx = (W + TW - 1) / TW, nby = (H + TH - 1) / TH;
+    const int nbx = (W + tile_cols(TW) - 1) / tile_cols(TW), nby = (H + TH - 1) / TH;
     const int tpi = nbx * nby;
     const long long ntiles = (long long)tpi * B;
     if (ntiles <= 0 || ntiles > 0x7fffffffLL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((step_kernel<R, TW, TH>), dim3((unsigned)ntiles), dim3(tile_threads(TW, TH)),
-                       0, s, ucur,
-                       uprev, uout, ref, mask, H, W, nbx, tpi, a, partials);
+    const dim3 g((unsigned)ntiles), b(256);
+    if (ref)
+        hipLaunchKernelGGL((step_kernel<R, TW, TH, true, GEN, false>), g, b, 0, s, ucur, uprev, uout,
+                           ref, mask, H, W, nbx, tpi, a, partials, nullptr);
+    else
+        hipLaunchKernelGGL((step_kernel<R, TW, TH, false, GEN, false>), g, b, 0, s, ucur, uprev,
+                           uout, nullptr, mask, H, W, nbx, tpi, a, nullptr, nullptr);
+    return hipGetLastError();
+}
+
+template <int R, int TW, int TH, bool GEN>
+static hipError_t launch_keepv_tile(const float *ucur, const float *uprev, float *uout, float *vout,
+                                    const uint8_t *mask, int B, int H, int W, const StepArgs &a,
+                                    hipStream_t s)
+{
+    const int nbx = (W + tile_cols(TW) - 1) / tile_cols(TW), nby = (H + TH - 1) / TH;
+    const long long ntiles = (long long)nbx * nby * B;
+    if (ntiles <= 0 || ntiles > 0x7fffffffLL) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((step_kernel<R, TW, TH, false, GEN, true>), dim3((unsigned)ntiles), dim3(256),
+                       0, s, ucur, uprev, uout, nullptr, mask, H, W, nbx, nbx * nby, a, nullptr,
+                       vout);
     return hipGetLastError();
 }
 
@@ -352,11 +359,14 @@ static hipError_t launch_step_r(int shape, const float *ucur, const float *uprev
                                 const float *ref, const uint8_t *mask, int B, int H, int W,
                                 const StepArgs &a, double *partials, hipStream_t s)
 {
-    // tensor variants: one kernel shape (60-column strips of >= 28 rows)
-    if (a.model != 0)
-        return shape == kShapeStripShort
-                   ? launch_strip_t<R, 28, 1, true>(ucur, uprev, uout, ref, mask, B, H, W, a, partials, s)
-                   : hipErrorInvalidValue;
+    if (a.model != 0) {              // tensor variants: the shapes of variant_shape
+        switch (shape) {
+        case 0: return launch_step_t<R, 64, 32, true>(ucur, uprev, uout, ref, mask, B, H, W, a, partials, s);
+        case 1: return launch_step_t<R, 64, 16, true>(ucur, uprev, uout, ref, mask, B, H, W, a, partials, s);
+        case kShapeStripShort: return launch_strip_t<R, 28, 1, true>(ucur, uprev, uout, ref, mask, B, H, W, a, partials, s);
+        default: return hipErrorInvalidValue;
+        }
+    }
     switch (shape) {
     case 0: return launch_step_t<R, 64, 32>(ucur, uprev, uout, ref, mask, B, H, W, a, partials, s);
     case 1: return launch_step_t<R, 64, 16>(ucur, uprev, uout, ref, mask, B, H, W, a, partials, s);
@@ -370,6 +380,24 @@ static hipError_t launch_step_r(int shape, const float *ucur, const float *uprev
     case kShapeTile32x16: return launch_step_t<R, 32, 16>(ucur, uprev, uout, ref, mask, B, H, W, a, partials, s);
     case kShapeTile16x16: return launch_step_t<R, 16, 16>(ucur, uprev, uout, ref, mask, B, H, W, a, partials, s);
     default: return hipErrorInvalidValue;
+    }
+}
+
+// The keep-v step of a forward step shape: a strip shape keeps its height (wide
+// shapes map to their height), a tile shape runs the tile of its width class.
+template <int R, bool GEN>
+static hipError_t launch_keepv_r(int shape, const float *ucur, const float *uprev, float *uout,
+                                 float *vout, const uint8_t *mask, int B, int H, int W,
+                                 const StepArgs &a, hipStream_t s)
+{
+    switch (shape) {
+    case 0: return launch_keepv_tile<R, 64, 32, GEN>(ucur, uprev, uout, vout, mask, B, H, W, a, s);
+    case kShapeStripShort: case kShapeStripWideShort:
+        return launch_keepv_t<R, 28, GEN>(ucur, uprev, uout, vout, mask, B, H, W, a, s);
+    case kShapeStrip: case kShapeStripTall: case kShapeStripWide:
+        if constexpr (!GEN) return launch_keepv_t<R, 64, false>(ucur, uprev, uout, vout, mask, B, H, W, a, s);
+        return hipErrorInvalidValue;
+    default: return launch_keepv_tile<R, 64, 16, GEN>(ucur, uprev, uout, vout, mask, B, H, W, a, s);
     }
 }
 
@@ -393,7 +421,10 @@ hipError_t launch_step_keepv(int R, int shape, const float *ucur, const float *u
 {
     switch (R) {
 #define EED4_CASE(r) \
-    case r: return launch_keepv_r<r>(shape, ucur, uprev, uout, vout, mask, B, H, W, a, s);
+    case r:                                                                                   \
+        return a.model != 0                                                                   \
+                   ? launch_keepv_r<r, true>(shape, ucur, uprev, uout, vout, mask, B, H, W, a, s) \
+                   : launch_keepv_r<r, false>(shape, ucur, uprev, uout, vout, mask, B, H, W, a, s);
         EED4_CASE(0) EED4_CASE(1) EED4_CASE(2) EED4_CASE(3) EED4_CASE(4)
         EED4_CASE(5) EED4_CASE(6) EED4_CASE(7) EED4_CASE(8)
 #undef EED4_CASE

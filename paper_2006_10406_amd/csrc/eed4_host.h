@@ -57,6 +57,7 @@ size_t align_up(size_t x);
 int check_params(const eed4_params *p, int B, int H, int W);
 int check_ws(void *ws, size_t ws_bytes, size_t need);
 int step_shape(const eed4_params *p, int B, int H, int W);
+int run_shape(const eed4_params *p, int B, int H, int W);
 
 // Without a tuned choice, the single-image path uses workgroup tiles when
 // the default strips would give fewer waves than this (too few to fill the
@@ -78,17 +79,17 @@ inline void tune_order(int first, int (&order)[kNumShapes])
 
 // Candidates of the single-image tuner, `first` (the size rule's default)
 // first; returns their count.  Where the default is a strip (enough work for
-// the strips to fill the chip) the workgroup tiles are left out: they need
-// 2-3x the instructions per pixel and lose by far more than the tuner's
-// margin, and timing them would only load the GPU.  Where the default is a
-// tile the 28- and 8-row strips are the strips that can compete.
+// the strips to fill the chip) only the 64 x 32 tile of the tiles is timed: it
+// is level with the strips at about 9 million pixels and 15 % slower at 4096^2.
+// Where the default is a tile the 28- and 8-row strips are the strips that can
+// compete.
 inline int tune_candidates(int first, int (&order)[kNumShapes])
 {
     int n = 0;
     order[n++] = first;
     for (int sh = 0; sh < kNumShapes; ++sh) {
         if (sh == first) continue;
-        const bool keep = is_strip(first) ? is_strip(sh)
+        const bool keep = is_strip(first) ? is_strip(sh) || sh == 0
                                            : (!is_strip(sh) || sh == kShapeStripShort ||
                                               sh == kShapeStripTiny);
         if (keep) order[n++] = sh;

@@ -53,19 +53,15 @@ constexpr int kDiffPeronaMalik = 1, kDiffPeronaMalikExp = 2, kDiffGemanReynolds 
 constexpr int kMu3Arithmetic = 1, kMu3Max = 2;
 inline int model_of_flags(int flags) { return ((flags >> 16) & 0xf) | (((flags >> 20) & 0x3) << 4); }
 
-// Output tile of the fused step kernels.
+// Workgroup tile of the fused step kernels: tw lanes (tw - 4 output columns)
+// by th output rows.
 struct TileShape {
     int tw, th;
 };
-
-// Threads of a tile workgroup: 512 for the 32 x 32 tile (one output per
-// thread in the last stage, half the serial work per thread in each stage:
-// 10 % faster on a 512^2 image, 6-7 % on 3 x 512^2 and 16 x 256^2, where tiles
-// are chosen), 256 for the others.
-constexpr int tile_threads(int tw, int th) { return tw == 32 && th == 32 ? 512 : kThreads; }
+constexpr int tile_cols(int tw) { return tw - 4; }
 
 // Kernel shapes compiled into the library (index = config id): 0..2 and
-// 9..10 are workgroup tiles (tw x th outputs per workgroup of tile_threads);
+// 9..10 are workgroup tiles (tw - 4 columns x th rows per 256 threads);
 // 3..8 are wave strips (60 or 124 columns x a segment of rows per wave).  The
 // small tiles (9, 10) give images of a few hundred pixels a side more
 // workgroups than the chip has CUs.
@@ -110,6 +106,7 @@ hipError_t launch_blur(int R, const float *u, float *v, int B, int H, int W, con
 hipError_t launch_reduce(const double *partials, int tiles_per_img, int B, double *sums,
                          hipStream_t s);
 int tiles_per_image(int shape, int R, int H, int W);  // residual partials per image
+int variant_shape(int R, int B, int H, int W);        // kernel shape of a tensor variant
 int strip_rows(int R, int shape);                      // output rows per strip segment
 
 }  // namespace eed4

@@ -129,6 +129,42 @@ __device__ __forceinline__ void model_mu(float x, int model, float &mu1, float &
                                  : __builtin_amdgcn_sqrtf(g);
 }
 
+// model_mu for N points at once: one uniform branch per field for all of them,
+// so that the points' arithmetic stays in one block each and can interleave.
+template <int N>
+__device__ __forceinline__ void model_mu_rows(const float (&x)[N], int model, float (&mu1)[N],
+                                              float (&mu3)[N])
+{
+#pragma clang fp contract(off)
+    const int diff = model & 0xf, rule = model >> 4;
+    if (diff == kDiffPeronaMalik) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) mu1[i] = __builtin_amdgcn_rcpf(1.0f + x[i]);
+    } else if (diff == kDiffPeronaMalikExp) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) mu1[i] = __builtin_amdgcn_exp2f(-x[i] * 1.44269504088896341f);
+    } else if (diff == kDiffGemanReynolds) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const float r = __builtin_amdgcn_rcpf(1.0f + x[i]);
+            mu1[i] = r * r;
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < N; ++i) mu1[i] = __builtin_amdgcn_rsqf(1.0f + x[i]);
+    }
+    if (rule == kMu3Arithmetic) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) mu3[i] = 0.5f * (1.0f + mu1[i]);
+    } else if (rule == kMu3Max) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) mu3[i] = 1.0f;
+    } else {
+#pragma unroll
+        for (int i = 0; i < N; ++i) mu3[i] = __builtin_amdgcn_sqrtf(mu1[i]);
+    }
+}
+
 // Raw buffer resource over the `bytes` bytes from `base` (gfx9 descriptor:
 // stride 0, no swizzle).  A load at a byte offset at or beyond `bytes` reads 0
 // and a store there is dropped: lanes without an output pixel use kOffNone.
@@ -147,6 +183,29 @@ constexpr unsigned kOffNone = 0x80000000u;
 __device__ __forceinline__ float buf_f32(__amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff)
 {
     return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, voff, soff, 0));
+}
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ f32x4 buf_f32x4(__amdgpu_buffer_rsrc_t r, unsigned voff)
+{
+    return __builtin_bit_cast(f32x4, (u32x4)__builtin_amdgcn_raw_buffer_load_b128(r, voff, 0, 0));
+}
+
+// The Gaussian taps in vector registers (R + 1 of them: the kernel is
+// symmetric, w[j] = w[2R - j]).  A vector instruction with a scalar-register
+// operand issues every 4.15 cycles, one with vector registers only every 2.4
+// to 2.6 (measured, 2 to 8 waves a SIMD), and the two passes are a third of
+// the step's instructions.
+template <int R>
+__device__ __forceinline__ void vector_weights(const float *w, float (&wv)[2 * R + 1])
+{
+#pragma unroll
+    for (int j = 0; j <= R; ++j) {
+        wv[j] = w[j];
+        asm volatile("" : "+v"(wv[j]));
+        wv[2 * R - j] = wv[j];
+    }
 }
 
 // Image row of consecutive stream rows under the half-sample mirror: the row

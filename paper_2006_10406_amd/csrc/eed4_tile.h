@@ -1,24 +1,37 @@
 // Device code of one fused FOEED/FSI inner step on one output tile.
 //
-// One workgroup of NTH threads (256 unless given) computes a TW x TH tile of u^{k+1} from u^k
-// (read with a halo of R+2 pixels, R = Gaussian radius) and u^{k-1}:
-//   A  load u^k (tile + halo) into LDS; border tiles gather through the
-//      half-sample mirror, which realises the Neumann condition (Sec. 2.1)
-//   B  x pass of the separable Gaussian presmoothing (Sec. 2.2)
-//   C  y pass
-//   D  at every point of the tile grown by one pixel: central-difference
-//      gradient of u_sigma, fourth-order diffusion tensor from it (Sec. 3.1,
-//      eigenvalues g, 1, sqrt g, 0), Hessian of u (Sec. 3.3 stencils, mixed
-//      term with corrected signs) and the contraction T = D : H
-//   E  outer second differences of T (eq. genModel), explicit step,
-//      FSI extrapolation (Sec. 3.3) and Dirichlet hold of the known pixels;
-//      optionally the FP64 cycle residual.
+// One workgroup of NTH threads computes a tile of u^{k+1} from u^k (read with
+// a halo of R+2 pixels, R = Gaussian radius) and u^{k-1}.  TW lanes hold TW
+// consecutive columns, of which the middle TW - 4 are outputs (the contracted
+// Hessian T needs one column more on each side and the gradient another); a
+// group of TW lanes owns OH consecutive rows, and the NTH / TW groups stack to
+// TH rows:
+//   A  u^k of the tile and its halo into LDS, 16 bytes a lane (border tiles
+//      gather through the half-sample mirror, which realises the Neumann
+//      condition, Sec. 2.1); u^{k-1}, mask and cycle start of the group's own
+//      outputs into registers, so that their latency hides behind the stages
+//   B  x pass of the separable Gaussian presmoothing (Sec. 2.2), four outputs
+//      per item from 16-byte LDS reads, each row once per workgroup
+//   C  in registers, every row of the group at once: y pass, central-difference
+//      gradient of u_sigma, fourth-order diffusion tensor from it (Sec. 3.1),
+//      Hessian of u (Sec. 3.3 stencils, mixed term with corrected signs),
+//      T = D : H, outer second differences of T (eq. genModel), explicit step,
+//      FSI extrapolation (Sec. 3.3) and Dirichlet hold; optionally the FP64
+//      cycle residual and the presmoothed image K_sigma * u^k.
 // Every intermediate is evaluated on the mirror-extended image, so the halo
 // values of T carry the parity the boundary needs and P stays symmetric.
+//
+// What bounds it: a tile is a chain of a global load, two barriers and about
+// OH + 4 rows of dependent arithmetic, and below about a million pixels that
+// chain and the launch are the whole time.  Stage C keeps OH + 4 independent
+// rows in flight, which the streaming strips cannot, so two waves a SIMD
+// already fill the vector unit; it reads the x pass from LDS instead of taking
+// it again for the 2R + 4 halo rows of every group.
 #pragma once
 
 #include "eed4_internal.h"
 #include "eed4_pointwise.h"
+#include "eed4_strip.h"
 
 namespace eed4 {
 
@@ -30,34 +43,33 @@ __device__ __forceinline__ int mirror_index(int i, int n)
     return m < n ? m : p - 1 - m;
 }
 
+// Half-sample mirror of -n <= i < 2n (one reflection), clamped to the image
+// for indices beyond that (no needed value comes from those).
+__device__ __forceinline__ int mirror_once(int i, int n)
+{
+    i = i < 0 ? -1 - i : i;
+    i = i >= n ? 2 * n - 1 - i : i;
+    return i < 0 ? 0 : (i >= n ? n - 1 : i);
+}
+
 template <int R, int TW, int TH, int NTH = kThreads>
 struct TileGeo {
-    static_assert(TW % 4 == 0 && NTH % TW == 0, "tile width");
+    static constexpr int OH = TH * TW / NTH;              // output rows per lane group
+    static_assert(64 % TW == 0 && TW >= 16 && OH >= 1 && OH * (NTH / TW) == TH, "tile shape");
     static constexpr int h = R + 2;                       // input halo
-    static constexpr int UH = TH + 2 * h;                 // rows of u in LDS
-    static constexpr int UWr = TW + 2 * h;                // used columns of u
-    static constexpr int UW = (UWr + 3) & ~3;             // padded row stride
-    static constexpr int XW = TW + 4;                     // columns after the x pass
-    static constexpr int VH = TH + 4;                     // rows after the y pass
-    static constexpr int PH = TH + 2, PW = TW + 2;        // tensor points
-    static constexpr int NU = UH * UW, NX = UH * XW, NV = VH * XW, NP = PH * PW;
-    static constexpr int NT = 3 * NP;
-    static constexpr int REGA = (NU + NX > NT) ? NU + NX : NT;  // u + x pass, later T
-    static constexpr int SMEM = REGA + NV;                // floats of LDS
-    static constexpr int NF4 = (4 + 2 * R + 3) / 4;       // float4 loads per x window
-    static constexpr int NQ = XW / 4;                     // x-pass items per row
-    static constexpr int nyr()
-    {
-        int r = 4;
-        while (((VH + r - 1) / r) * XW > NTH && r < VH) ++r;
-        return r;
-    }
-    static constexpr int NYR = nyr();                     // rows per y-pass item
-    static constexpr int NRUN = (VH + NYR - 1) / NYR;
-    static constexpr int NPT = (NP + NTH - 1) / NTH;
-    static constexpr int RPP = NTH / TW;                  // output rows per pass
-    static_assert(TH % RPP == 0, "tile height");
-    static_assert(UW * UH >= 0, "");
+    static constexpr int SW = TW - 4;                     // output columns
+    static constexpr int SC = (h + 3) & ~3;               // staged columns left of the outputs
+    static constexpr int OFF = SC - h;                    // first tap of lane 0's column
+    static constexpr int UH = TH + 2 * h;                 // staged rows
+    static constexpr int UWn = SC + TW + (R > 2 ? R - 2 : 0);  // staged columns needed
+    static constexpr int UQ = (UWn + 3) / 4;              // 16-byte loads per staged row
+    static constexpr int NF4 = (OFF + 4 + 2 * R + 3) / 4; // 16-byte LDS reads per x-pass item
+    static constexpr int NQ = TW / 4;                     // x-pass items per row
+    static constexpr int UW = 4 * (UQ > NF4 + NQ - 1 ? UQ : NF4 + NQ - 1);   // row stride of u
+    static constexpr int NA = UH * UQ, NB = UH * NQ;      // items of stages A and B
+    static constexpr int NU = UH * UW, NX = UH * TW;
+    static constexpr int SMEM = NU + NX;                  // floats of LDS
+    static constexpr int NV = OH + 4, NT = OH + 2;        // rows of v and of T per group
 };
 
 // Accumulates sum (un - ref)^2 and sum un^2 of the tile in FP64 and writes
@@ -89,175 +101,201 @@ __device__ __forceinline__ void block_sum2(double d2, double n2, double *scratch
 
 // One tile.  ucur/uprev/uout/ref/mask point at the image (H x W).  ref, when
 // not null, is the cycle-start state for the residual (it may equal uout: each
-// pixel is read before it is written by the same thread).
-template <int R, int TW, int TH, int NTH = kThreads>
+// pixel is read before it is written by the same thread).  GEN: tensor variant
+// `model` chosen at run time; VST: also K_sigma * u^k into vout.
+template <int R, int TW, int TH, int NTH = kThreads, bool GEN = false, bool VST = false>
 __device__ __forceinline__ void step_tile(float *smem, const float *ucur, const float *uprev,
                                           float *uout, const float *ref,
                                           const uint8_t *__restrict__ mask, int H, int W, int ty,
                                           int tx, const float (&w)[2 * kRMax + 1], float tau,
-                                          float alpha, float il2q, double *partial)
+                                          float alpha, float il2q, double *partial, int model = 0,
+                                          float *vout = nullptr)
 {
     using G = TileGeo<R, TW, TH, NTH>;
-    float *sU = smem;
-    float *sX = smem + G::NU;
-    float *sV = smem + G::REGA;
-    float *sT = smem;  // [3][PH][PW], written after sU and sX are dead
-    const int tid = threadIdx.x;
-    const int gx0 = tx * TW, gy0 = ty * TH;
+    constexpr int OH = G::OH, NV = G::NV, NT = G::NT;
+    float *sU = smem, *sX = smem + G::NU;
+    const int tid = threadIdx.x, lane = tid % TW;
+    int grp = tid / TW;
+    if constexpr (TW == 64) grp = __builtin_amdgcn_readfirstlane(grp);
+    const int X0 = tx * G::SW, Y0 = ty * TH, Yg = Y0 + grp * OH;
     if constexpr (kLdsSentinel) sentinel_fill_block(smem, G::SMEM);
 
-    // The pointwise operands of this thread's outputs (stage E: rows rr,
-    // rr + RPP, ... of column c) are loaded first, so that their memory
-    // latency overlaps stages A-D instead of following them.  Tiles with
-    // more than 4 outputs per thread load them in stage E (the registers
-    // would cost more waves than the latency they hide).
-    constexpr int NE = TH / G::RPP;
-    constexpr bool PF = NE <= 4;
-    const int c = tid % TW, rr = tid / TW;
-    float ek[NE], ep[NE], ef[NE];
-    int em[NE];
+    // Every plane through a buffer resource based at the lowest row a needed
+    // value comes from (the library keeps UH * W * 4 below 2^31); lanes without
+    // an output pixel use an offset beyond it, so they read 0 and store nothing.
+    const unsigned W4 = 4u * (unsigned)W;
+    const int y0 = Y0 - G::h, b0 = y0 > 0 ? y0 : 0;
+    const int nb = H - b0 < G::UH ? H - b0 : G::UH;
+    const size_t base = (size_t)b0 * W;
+    const __amdgpu_buffer_rsrc_t rs_u = buffer_rsrc(ucur + base, (unsigned)nb * W4);
+    const __amdgpu_buffer_rsrc_t rs_p = buffer_rsrc(uprev + base, (unsigned)nb * W4);
+    const __amdgpu_buffer_rsrc_t rs_o = buffer_rsrc(uout + base, (unsigned)nb * W4);
+    const __amdgpu_buffer_rsrc_t rs_m = buffer_rsrc(mask + base, (unsigned)nb * (unsigned)W);
+
+    // ---- A: loads ----
+    constexpr int IA = (G::NA + NTH - 1) / NTH;
+    f32x4 st[IA];
+    const int xs = X0 - G::SC;                            // image column of staged column 0
+    if (H >= G::UH && xs >= 0 && xs + 4 * G::UQ <= W) {
 #pragma unroll
-    for (int e = 0; e < NE; ++e) {
-        const int gy = gy0 + rr + e * G::RPP, gx = gx0 + c;
-        ek[e] = ep[e] = ef[e] = 0.0f;
-        em[e] = 0;
-        if (PF && gy < H && gx < W) {
-            const size_t gi = (size_t)gy * W + gx;
-            ek[e] = ucur[gi];
-            ep[e] = uprev[gi];
-            em[e] = mask[gi];
-            if (ref) ef[e] = ref[gi];
+        for (int k = 0; k < IA; ++k) {
+            const int it = tid + k * NTH, r = it / G::UQ, q = it - r * G::UQ;
+            int y = mirror_once(y0 + r, H);
+            y = y < b0 ? b0 : y;
+            const unsigned vo = it < G::NA ? (unsigned)(y - b0) * W4 + 4u * (unsigned)(xs + 4 * q)
+                                           : kOffNone;
+            st[k] = buf_f32x4(rs_u, vo);
+        }
+    } else {
+        const bool tiny = H < G::UH || W < 4 * G::UQ;     // may need repeated reflection
+#pragma unroll
+        for (int k = 0; k < IA; ++k) {
+            const int it = tid + k * NTH, r = it / G::UQ, q = it - r * G::UQ;
+            int y = tiny ? mirror_index(y0 + r, H) : mirror_once(y0 + r, H);
+            y = y < b0 ? b0 : y;
+            const unsigned ro = (unsigned)(y - b0) * W4;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int x = xs + 4 * q + e;
+                const int xm = tiny ? mirror_index(x, W) : mirror_once(x, W);
+                st[k][e] = buf_f32(rs_u, it < G::NA ? ro + 4u * (unsigned)xm : kOffNone, 0);
+            }
         }
     }
-
-    // ---- A: u^k with halo ----
-    {
-        const int x0 = gx0 - G::h, y0 = gy0 - G::h;
-        const bool inside = x0 >= 0 && y0 >= 0 && x0 + G::UWr <= W && y0 + G::UH <= H;
-        if (inside) {
-            for (int i = tid; i < G::UH * G::UWr; i += NTH) {
-                int r = i / G::UWr, c = i - r * G::UWr;
-                sU[r * G::UW + c] = ucur[(size_t)(y0 + r) * W + (x0 + c)];
-            }
+    const int c = X0 - 2 + lane;                          // this lane's column
+    const bool out_col = lane >= 2 && lane < TW - 2 && c < W;
+    const unsigned vo4 = out_col ? 4u * (unsigned)c : kOffNone;
+    const unsigned vo1 = out_col ? (unsigned)c : kOffNone;
+    // byte offsets of the group's rows: scalar where a group is a whole wave
+    auto load_row = [&](__amdgpu_buffer_rsrc_t rs, int j) {
+        const unsigned ro = (unsigned)((Yg + j < H ? Yg + j : H - 1) - b0) * W4;
+        return TW == 64 ? buf_f32(rs, vo4, ro) : buf_f32(rs, vo4 + ro, 0);
+    };
+    auto store_row = [&](__amdgpu_buffer_rsrc_t rs, int j, float x) {
+        const unsigned ro = (unsigned)(Yg + j - b0) * W4;
+        if constexpr (TW == 64) {
+            if (Yg + j < H)
+                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(x), rs, vo4, ro, 0);
         } else {
-            for (int i = tid; i < G::UH * G::UWr; i += NTH) {
-                int r = i / G::UWr, c = i - r * G::UWr;
-                int yy = mirror_index(y0 + r, H), xx = mirror_index(x0 + c, W);
-                sU[r * G::UW + c] = ucur[(size_t)yy * W + xx];
-            }
+            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(x), rs,
+                                                  Yg + j < H ? vo4 + ro : kOffNone, 0, 0);
         }
-    }
-    __syncthreads();
-
-    // ---- B: x pass, 4 outputs per item ----
-    for (int i = tid; i < G::UH * G::NQ; i += NTH) {
-        int r = i / G::NQ, q = i - r * G::NQ;
-        const float4 *src = reinterpret_cast<const float4 *>(sU + r * G::UW + 4 * q);
-        float win[4 * G::NF4];
+    };
+    float ep[OH], ef[OH];
+    unsigned em[OH];
 #pragma unroll
-        for (int f = 0; f < G::NF4; ++f) {
-            float4 v = src[f];
-            win[4 * f] = v.x;
-            win[4 * f + 1] = v.y;
-            win[4 * f + 2] = v.z;
-            win[4 * f + 3] = v.w;
-        }
-        float o[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            float s = w[0] * win[e];
-#pragma unroll
-            for (int j = 1; j <= 2 * R; ++j) s = fmaf(w[j], win[e + j], s);
-            o[e] = s;
-        }
-        *reinterpret_cast<float4 *>(sX + r * G::XW + 4 * q) = make_float4(o[0], o[1], o[2], o[3]);
-    }
-    __syncthreads();
-
-    // ---- C: y pass, NYR outputs per item ----
-    for (int i = tid; i < G::NRUN * G::XW; i += NTH) {
-        int run = i / G::XW, c = i - run * G::XW;
-        int r0 = run * G::NYR;
-        float win[G::NYR + 2 * R];
-#pragma unroll
-        for (int j = 0; j < G::NYR + 2 * R; ++j)
-            win[j] = (r0 + j < G::UH) ? sX[(r0 + j) * G::XW + c] : 0.0f;
-#pragma unroll
-        for (int e = 0; e < G::NYR; ++e) {
-            if (r0 + e < G::VH) {
-                sV[(r0 + e) * G::XW + c] = ypass_sym<R>(w, [&](int j) { return win[e + R + j]; });
-            }
-        }
-    }
-    __syncthreads();
-
-    // ---- D: gradient, tensor, Hessian, contraction on the tile grown by 1 ----
-    float txx[G::NPT], tyy[G::NPT], txy[G::NPT];
-#pragma unroll
-    for (int k = 0; k < G::NPT; ++k) {
-        int p = tid + k * NTH;
-        txx[k] = tyy[k] = txy[k] = 0.0f;
-        if (p < G::NP) {
-            int pr = p / G::PW, pc = p - pr * G::PW;
-            const float *v = sV + (pr + 1) * G::XW + (pc + 1);
-            const float gxs = v[1] - v[-1];                          // 2 gx
-            const float gys = v[G::XW] - v[-G::XW];                  // 2 gy
-            const float *u = sU + (pr + G::h - 1) * G::UW + (pc + G::h - 1);
-            const float uc = u[0];
-            const float hxx = second_diff(u[-1], uc, u[1]);
-            const float hyy = second_diff(u[-G::UW], uc, u[G::UW]);
-            const float hxy = mixed_diff(xdiff(u[G::UW - 1], u[G::UW + 1]),
-                                         xdiff(u[-G::UW - 1], u[-G::UW + 1]));
-            const float s2 = grad2_sq(gxs, gys);                     // 4 |grad|^2
-            float mu1, mu3;
-            foeed_mu(s2, il2q, mu1, mu3);
-            contract(gxs, gys, s2, mu1, mu3, hxx, hyy, hxy, txx[k], tyy[k], txy[k]);
-        }
-    }
-    __syncthreads();
-    if constexpr (kLdsSentinel) sentinel_fill_block(sT, G::NT);
-#pragma unroll
-    for (int k = 0; k < G::NPT; ++k) {
-        int p = tid + k * NTH;
-        if (p < G::NP) {
-            sT[p] = txx[k];
-            sT[G::NP + p] = tyy[k];
-            sT[2 * G::NP + p] = txy[k];
-        }
-    }
-    __syncthreads();
-
-    // ---- E: outer differences, FSI step, Dirichlet hold, residual ----
-    double d2 = 0.0, n2 = 0.0;
-    constexpr int UE = PF ? NE : 2;
-#pragma unroll UE
-    for (int e = 0; e < NE; ++e) {
-        const int r = rr + e * G::RPP;
-        int gy = gy0 + r, gx = gx0 + c;
-        if (gy < H && gx < W) {
-            int p = (r + 1) * G::PW + (c + 1);
-            const float *Txx = sT + p;
-            const float *Tyy = sT + G::NP + p;
-            const float *Txy = sT + 2 * G::NP + p;
-            const float pu = outer_div(Txx[0], Tyy[0], Txx[-1] + Txx[1], Tyy[-G::PW] + Tyy[G::PW],
-                                       Txy[G::PW + 1] - Txy[G::PW - 1],
-                                       Txy[-G::PW + 1] - Txy[-G::PW - 1]);
-            size_t gi = (size_t)gy * W + gx;
-            const float uk = PF ? ek[e] : ucur[gi];
-            const float up = PF ? ep[e] : uprev[gi];
-            const float un = fsi_update(pu, uk, up, tau, alpha, (PF ? em[e] : mask[gi]) != 0);
-            if (ref) {
-                double dd = (double)un - (double)(PF ? ef[e] : ref[gi]);
-                d2 = fma(dd, dd, d2);
-                n2 = fma((double)un, (double)un, n2);
-            }
-            uout[gi] = un;
-        }
+    for (int j = 0; j < OH; ++j) {
+        const unsigned ro = (unsigned)((Yg + j < H ? Yg + j : H - 1) - b0) * (unsigned)W;
+        ep[j] = load_row(rs_p, j);
+        em[j] = TW == 64 ? __builtin_amdgcn_raw_buffer_load_b8(rs_m, vo1, ro, 0)
+                         : __builtin_amdgcn_raw_buffer_load_b8(rs_m, vo1 + ro, 0, 0);
+        ef[j] = 0.0f;
     }
     if (ref) {
-        __syncthreads();
-        block_sum2<NTH>(d2, n2, reinterpret_cast<double *>(smem), partial);
+        const __amdgpu_buffer_rsrc_t rs_r = buffer_rsrc(ref + base, (unsigned)nb * W4);
+#pragma unroll
+        for (int j = 0; j < OH; ++j) ef[j] = load_row(rs_r, j);
     }
+#pragma unroll
+    for (int k = 0; k < IA; ++k) {
+        const int it = tid + k * NTH, r = it / G::UQ, q = it - r * G::UQ;
+        if (it < G::NA) *reinterpret_cast<f32x4 *>(sU + r * G::UW + 4 * q) = st[k];
+    }
+    float wv[2 * R + 1], vtau = tau, valpha = alpha, vil2q = il2q;
+    vector_weights<R>(w, wv);
+    asm volatile("" : "+v"(vtau), "+v"(valpha), "+v"(vil2q));
+    __syncthreads();
+
+    // ---- B: x pass ----
+#pragma unroll
+    for (int k = 0; k < (G::NB + NTH - 1) / NTH; ++k) {
+        const int it = tid + k * NTH;
+        if (G::NB % NTH == 0 || it < G::NB) {
+            const int r = it / G::NQ, q = it % G::NQ;
+            const f32x4 *src = reinterpret_cast<const f32x4 *>(sU + r * G::UW + 4 * q);
+            float win[4 * G::NF4];
+#pragma unroll
+            for (int f = 0; f < G::NF4; ++f) {
+                const f32x4 t = src[f];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) win[4 * f + e] = t[e];
+            }
+            f32x4 o;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                float acc = wv[0] * win[G::OFF + e];
+#pragma unroll
+                for (int j = 1; j <= 2 * R; ++j) acc = fmaf(wv[j], win[G::OFF + e + j], acc);
+                o[e] = acc;
+            }
+            *reinterpret_cast<f32x4 *>(sX + TW * r + 4 * q) = o;
+        }
+    }
+    __syncthreads();
+
+    // ---- C: the group's rows; row j of xw, u and v is image row Yg - h + j,
+    // Yg - 2 + j and Yg - 2 + j, row t of T is Yg - 1 + t ----
+    double d2 = 0.0, n2 = 0.0;
+    if (TW < 64 || Yg < H) {                              // (wave-uniform where TW == 64)
+        const float *px = sX + TW * (grp * OH) + lane;
+        const float *pu = sU + G::UW * (grp * OH + R) + (G::SC - 2) + lane;
+        float xw[NV + 2 * R];
+#pragma unroll
+        for (int j = 0; j < NV + 2 * R; ++j) xw[j] = px[TW * j];
+        float uc[NV], us[NV], ud[NV], v[NV];
+#pragma unroll
+        for (int j = 0; j < NV; ++j) {
+            const float l = pu[G::UW * j - 1], r = pu[G::UW * j + 1];
+            uc[j] = pu[G::UW * j];
+            us[j] = l + r;
+            ud[j] = xdiff(l, r);
+            v[j] = ypass_sym<R>(wv, [&](int t) { return xw[j + R + t]; });
+        }
+        float gxs[NT], gys[NT], s2[NT], mu1[NT], mu3[NT];
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            gxs[t] = from_next_lane(v[t + 1]) - from_prev_lane(v[t + 1]);            // 2 gx
+            gys[t] = v[t + 2] - v[t];                                                // 2 gy
+            s2[t] = grad2_sq(gxs[t], gys[t]);                                        // 4 |grad|^2
+            if constexpr (!GEN) foeed_mu(s2[t], vil2q, mu1[t], mu3[t]);
+        }
+        if constexpr (GEN) {
+            float x[NT];
+#pragma unroll
+            for (int t = 0; t < NT; ++t) x[t] = s2[t] * vil2q;
+            model_mu_rows(x, model, mu1, mu3);
+        }
+        float txx[NT], tyy[NT], z[NT];
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            const float hxx = second_diff_sum(us[t + 1], uc[t + 1]);
+            const float hyy = second_diff(uc[t], uc[t + 1], uc[t + 2]);
+            const float hxy = mixed_diff(ud[t + 2], ud[t]);
+            float txy;
+            contract(gxs[t], gys[t], s2[t], mu1[t], mu3[t], hxx, hyy, hxy, txx[t], tyy[t], txy);
+            z[t] = from_next_lane(txy) - from_prev_lane(txy);
+        }
+        __amdgpu_buffer_rsrc_t rs_v = rs_o;
+        if constexpr (VST) rs_v = buffer_rsrc(vout + base, (unsigned)nb * W4);
+#pragma unroll
+        for (int j = 0; j < OH; ++j) {
+            const float sxx = from_prev_lane(txx[j + 1]) + from_next_lane(txx[j + 1]);
+            const float pr = outer_div(txx[j + 1], tyy[j + 1], sxx, tyy[j] + tyy[j + 2], z[j + 2],
+                                       z[j]);
+            const float un = fsi_update(pr, uc[j + 2], ep[j], vtau, valpha, em[j] != 0);
+            const bool row = Yg + j < H;
+            if (ref) {
+                // pixels outside the image read 0 for the reference; add 0
+                const double du = row && out_col ? (double)un : 0.0;
+                const double dd = du - (row ? (double)ef[j] : 0.0);
+                d2 = fma(dd, dd, d2);
+                n2 = fma(du, du, n2);
+            }
+            store_row(rs_o, j, un);
+            if constexpr (VST) store_row(rs_v, j, v[j + 2]);
+        }
+    }
+    if (ref) block_sum2<NTH>(d2, n2, reinterpret_cast<double *>(smem), partial);
 }
 
 // Workgroup -> tile map that gives each XCD (workgroups are dealt round-robin
