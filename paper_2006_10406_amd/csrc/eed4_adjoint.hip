@@ -1118,7 +1118,8 @@ static int adjoint_shape(const eed4_params *p, RevStep t, hipStream_t s, int *sh
             t.fresh = 0;                       // ac was cleared above
             return (int)EED4_OK;
         },
-        [&](int) { return launch_reverse_step(t, p, p->cycle_len - 1, s); }, "adjoint autotune",
+        [&](int, hipStream_t q) { return launch_reverse_step(t, p, p->cycle_len - 1, q); },
+        "adjoint autotune",
         &best, nullptr);
     if (rc != EED4_OK) return rc;
     tune_remember(key, best);

@@ -372,7 +372,9 @@ int tune_single_step(const eed4_params *p, int B, int H, int W, float *S, float 
     for (int i = 0; i < nc; ++i) margins[i] = tune_margin(first, order[i]);
     const int rc = tune_pick(
         order, nc, s, [](int) { return (int)EED4_OK; },
-        [&](int sh) { return launch_step(R, sh, S, S, X, nullptr, mask, B, H, W, a, nullptr, s); },
+        [&](int sh, hipStream_t q) {
+            return launch_step(R, sh, S, S, X, nullptr, mask, B, H, W, a, nullptr, q);
+        },
         "step autotune", shape, nullptr, margins);
     if (rc != EED4_OK) return rc;
     tune_remember(single_tune_key(R, B, H, W), *shape);

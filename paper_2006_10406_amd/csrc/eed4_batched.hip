@@ -474,9 +474,9 @@ static int autotune(const eed4_image *im, int B, const eed4_params *p, char *bas
             a = make_args(p->sigma, r.R, p->tau, 1.0f, 0);
             return rc;
         },
-        [&](int sh) {
+        [&](int sh, hipStream_t q) {
             return launch_bstep(r.R, sh, r.grid, r.dimg, r.dqueue, r.dqlen, 0, 0, 1, false, a,
-                                r.dpartials, s);
+                                r.dpartials, q);
         },
         "autotune timing", best_shape, best_ms);
 }

@@ -113,21 +113,26 @@ inline float tune_margin(int first, int shape)
     return first == kShapeStrip && refetch ? kTuneMarginRefetch : kTuneMargin;
 }
 
+int capture_graph(const std::function<int(hipStream_t)> &enqueue, hipGraphExec_t *exec);
+
 // Chooses one of n candidate shapes (cands[0] the default) by timing on stream
 // s.  prepare(shape) sets up a candidate outside the timed region (EED4 code);
-// launch(shape) enqueues one launch of it.  Every candidate is sampled in two
-// round-robin passes of one warm-up launch and two timed samples of
-// kTuneLaunches back-to-back launches, and keeps its fastest sample, so the
-// clock ramp at the start of tuning does not favour the candidates timed later
-// and a fixed cost per launch (e.g. a profiler's) does not decide between
-// shapes a few percent apart.  A candidate replaces the current choice only
+// launch(shape, stream) enqueues one launch of it.  A candidate is timed as it
+// will run, as kTuneLaunches launches replayed from one graph: launched one by
+// one from the host, kernels of less than about 5 us all take as long as the
+// host needs to launch them, and the choice between them is noise (16 x 256^2
+// got a shape 20 % slower than the best that way).  Every candidate is sampled
+// in two round-robin passes of one warm-up replay and two timed ones and keeps
+// its fastest sample, so the clock ramp at the start of tuning does not favour
+// the candidates timed later.  A candidate replaces the current choice only
 // when it is faster by more than kTuneMargin (or its own entry of margins).
-constexpr int kTuneLaunches = 4;
+constexpr int kTuneLaunches = 8;
 template <typename Prepare, typename Launch>
 int tune_pick(const int *cands, int n, hipStream_t s, Prepare &&prepare, Launch &&launch,
               const char *where, int *best, float *best_ms, const float *margins = nullptr)
 {
     hipEvent_t e0 = nullptr, e1 = nullptr;
+    hipGraphExec_t exec[kNumShapes] = {};
     hipError_t e = hipEventCreate(&e0);
     if (e == hipSuccess) e = hipEventCreate(&e1);
     float tmin[kNumShapes];
@@ -136,10 +141,21 @@ int tune_pick(const int *cands, int n, hipStream_t s, Prepare &&prepare, Launch 
     for (int pass = 0; pass < 2 && e == hipSuccess && rc == EED4_OK; ++pass)
         for (int i = 0; i < n && e == hipSuccess && rc == EED4_OK; ++i) {
             if ((rc = prepare(cands[i])) != EED4_OK) break;
+            if (!exec[i]) {
+                rc = capture_graph(
+                    [&](hipStream_t cs) {
+                        for (int l = 0; l < kTuneLaunches; ++l) {
+                            const hipError_t le = launch(cands[i], cs);
+                            if (le != hipSuccess) return hip_fail(le, where);
+                        }
+                        return (int)EED4_OK;
+                    },
+                    &exec[i]);
+                if (rc != EED4_OK) break;
+            }
             for (int rep = 0; rep < 3 && e == hipSuccess; ++rep) {
                 e = hipEventRecord(e0, s);
-                for (int l = 0; l < (rep > 0 ? kTuneLaunches : 1) && e == hipSuccess; ++l)
-                    e = launch(cands[i]);
+                if (e == hipSuccess) e = hipGraphLaunch(exec[i], s);
                 if (e == hipSuccess) e = hipEventRecord(e1, s);
                 if (e == hipSuccess) e = hipEventSynchronize(e1);
                 float ms = 0.0f;
@@ -147,6 +163,9 @@ int tune_pick(const int *cands, int n, hipStream_t s, Prepare &&prepare, Launch 
                 if (e == hipSuccess && rep > 0) tmin[i] = std::fmin(tmin[i], ms);
             }
         }
+    if (rc != EED4_OK || e != hipSuccess) (void)hipStreamSynchronize(s);
+    for (int i = 0; i < n; ++i)
+        if (exec[i]) (void)hipGraphExecDestroy(exec[i]);
     if (e0) (void)hipEventDestroy(e0);
     if (e1) (void)hipEventDestroy(e1);
     if (rc != EED4_OK) return rc;
@@ -172,7 +191,6 @@ hipStream_t recompute_stream();
 void cycle_roles(int k, int n, float *S, float *X, float *Y, float **cur, float **prev,
                  float **out);
 int enqueue_cycle(const CycleJob &j, hipStream_t s);
-int capture_graph(const std::function<int(hipStream_t)> &enqueue, hipGraphExec_t *exec);
 int capture_cycle(const CycleJob &j, hipGraphExec_t *exec, int nc = 1);
 size_t backward_workspace(int B, int H, int W, const eed4_params *p);
 
