@@ -122,9 +122,9 @@ int capture_graph(const std::function<int(hipStream_t)> &enqueue, hipGraphExec_t
 // one from the host, kernels of less than about 5 us all take as long as the
 // host needs to launch them, and the choice between them is noise (16 x 256^2
 // got a shape 20 % slower than the best that way).  Every candidate is sampled
-// in two round-robin passes of one warm-up replay and two timed ones and keeps
-// its fastest sample, so the clock ramp at the start of tuning does not favour
-// the candidates timed later.  A candidate replaces the current choice only
+// in two round-robin passes of one warm-up and two timed samples and keeps its
+// fastest sample, so the clock ramp at the start of tuning does not favour the
+// candidates timed later.  A candidate replaces the current choice only
 // when it is faster by more than kTuneMargin (or its own entry of margins).
 constexpr int kTuneLaunches = 8;
 template <typename Prepare, typename Launch>
@@ -154,8 +154,11 @@ int tune_pick(const int *cands, int n, hipStream_t s, Prepare &&prepare, Launch 
                 if (rc != EED4_OK) break;
             }
             for (int rep = 0; rep < 3 && e == hipSuccess; ++rep) {
-                e = hipEventRecord(e0, s);
-                if (e == hipSuccess) e = hipGraphLaunch(exec[i], s);
+                // the replay ahead of the first event keeps the GPU busy while
+                // the host queues the timed ones
+                e = hipGraphLaunch(exec[i], s);
+                if (e == hipSuccess) e = hipEventRecord(e0, s);
+                for (int l = 0; l < 2 && e == hipSuccess; ++l) e = hipGraphLaunch(exec[i], s);
                 if (e == hipSuccess) e = hipEventRecord(e1, s);
                 if (e == hipSuccess) e = hipEventSynchronize(e1);
                 float ms = 0.0f;
