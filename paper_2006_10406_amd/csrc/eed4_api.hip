@@ -123,8 +123,9 @@ int enqueue_cycle(const CycleJob &j, hipStream_t s)
         const bool last = (k == n - 1);
         if (last && (n > 1 || dst != j.S)) out = dst;
         StepArgs a = make_args(j.sigma, j.R, j.tau, j.lambda, k, j.model);
-        hipError_t e = launch_step(j.R, j.shape, cur, prev, out, last ? j.S : nullptr, j.mask,
-                                   j.B, j.H, j.W, a, last ? j.partials : nullptr, s);
+        const bool res = last && j.residual;
+        hipError_t e = launch_step(j.R, j.shape, cur, prev, out, res ? j.S : nullptr, j.mask,
+                                   j.B, j.H, j.W, a, res ? j.partials : nullptr, s);
         if (e != hipSuccess) return hip_fail(e, "fsi step launch");
     }
     if (n == 1 && dst == j.S) {
@@ -132,6 +133,7 @@ int enqueue_cycle(const CycleJob &j, hipStream_t s)
                                       hipMemcpyDeviceToDevice, s);
         if (e != hipSuccess) return hip_fail(e, "cycle copy");
     }
+    if (!j.residual) return EED4_OK;
     hipError_t e = launch_reduce(j.partials, tiles_per_image(j.shape, j.R, j.H, j.W), j.B, j.sums, s);
     if (e != hipSuccess) return hip_fail(e, "residual reduce launch");
     return EED4_OK;
@@ -187,13 +189,13 @@ constexpr size_t kMaxCachedGraphs = 64;
 constexpr int kGraphCycles = 4;    // cycles per graph when no host work sits between cycles
 
 struct CycleKey {
-    int dev, nc;                   // device, cycles per graph
+    int dev, nc, residual;         // device, cycles per graph, residual formed
     const void *S, *X, *Y, *Out, *mask, *partials, *sums;
     int B, H, W, R, shape, n, model;
     float sigma, tau, lambda;      // finite (checked), so < is a strict order
     auto tie() const
     {
-        return std::tie(dev, nc, S, X, Y, Out, mask, partials, sums, B, H, W, R, shape, n,
+        return std::tie(dev, nc, residual, S, X, Y, Out, mask, partials, sums, B, H, W, R, shape, n,
                         model, sigma, tau, lambda);
     }
     bool operator<(const CycleKey &o) const { return tie() < o.tie(); }
@@ -209,6 +211,7 @@ int cycle_graph(const CycleJob &j, int nc, hipGraphExec_t *exec, bool *owned)
 {
     CycleKey k;
     k.nc = nc;
+    k.residual = j.residual;
     hipError_t e = hipGetDevice(&k.dev);
     if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
     k.S = j.S; k.X = j.X; k.Y = j.Y; k.Out = j.Out ? j.Out : j.S; k.mask = j.mask;
@@ -530,29 +533,36 @@ static int run_to_tolerance(const CycleJob &j, float *T, const eed4_params *p,
 }
 
 // M cycles in place on j.S with one stop-rule evaluation at the end (tol 0,
-// or a single cycle).  Without checkpoints or history nothing is read between
-// cycles: whole groups of kGraphCycles cycles run as one graph each (one
-// launch, and one gap between launches, per group), the rest one by one.  The
-// group size is fixed, so calls of any length share one cached graph.
+// or a single cycle).  Without a history only the last cycle's residual is
+// ever read, so the others are not formed (a residual step and its reduction
+// cost 3 us on 64^2, where a cycle of 10 takes 32, and 25 us on 4096^2).
+// Without checkpoints or history nothing sits between the cycles: whole groups
+// of kGraphCycles cycles run as one graph each (one launch, and one gap between
+// launches, per group), the rest one by one.  The group size is fixed, so calls
+// of any length share one cached graph.
 static int run_fixed(const CycleJob &j, int M, const eed4_params *p, float *ckpt,
                      double *hist_dev, hipStream_t s, RunResult *out)
 {
     const int B = j.B;
     const size_t N = (size_t)B * j.H * j.W;
-    hipGraphExec_t exec = nullptr, multi = nullptr;
-    bool own_exec = false, own_multi = false;
+    CycleJob plain = j;                    // a cycle whose residual nobody reads
+    plain.residual = hist_dev != nullptr;
+    hipGraphExec_t exec = nullptr, last = nullptr, multi = nullptr;
+    bool own_exec = false, own_last = false, own_multi = false;
     int rc = EED4_OK;
     hipError_t e = hipSuccess;
-    if (!(p->flags & EED4_NO_GRAPH)) rc = cycle_graph(j, 1, &exec, &own_exec);
+    const bool graphs = !(p->flags & EED4_NO_GRAPH);
     int m = 0;
-    if (rc == EED4_OK && exec && !ckpt && !hist_dev && M >= kGraphCycles) {
-        rc = cycle_graph(j, kGraphCycles, &multi, &own_multi);
-        for (; rc == EED4_OK && m + kGraphCycles <= M; m += kGraphCycles) {
+    if (graphs && !ckpt && !hist_dev && M > kGraphCycles) {
+        rc = cycle_graph(plain, kGraphCycles, &multi, &own_multi);
+        for (; rc == EED4_OK && m + kGraphCycles < M; m += kGraphCycles) {
             trace_mark("eed4 cycles %d-%d queued", m, m + kGraphCycles - 1);
             e = hipGraphLaunch(multi, s);
             if (e != hipSuccess) rc = hip_fail(e, "graph launch");
         }
     }
+    if (rc == EED4_OK && graphs && m < M - 1) rc = cycle_graph(plain, 1, &exec, &own_exec);
+    if (rc == EED4_OK && graphs) rc = cycle_graph(j, 1, &last, &own_last);
     for (; rc == EED4_OK && m < M; ++m) {
         trace_mark("eed4 cycle %d queued", m);
         if (ckpt) {
@@ -560,10 +570,10 @@ static int run_fixed(const CycleJob &j, int M, const eed4_params *p, float *ckpt
                                hipMemcpyDeviceToDevice, s);
             if (e != hipSuccess) { rc = hip_fail(e, "checkpoint copy"); break; }
         }
-        if (exec) {
-            e = hipGraphLaunch(exec, s);
+        if (graphs) {
+            e = hipGraphLaunch(m == M - 1 ? last : exec, s);
             if (e != hipSuccess) { rc = hip_fail(e, "graph launch"); break; }
-        } else if ((rc = enqueue_cycle(j, s)) != EED4_OK) {
+        } else if ((rc = enqueue_cycle(m == M - 1 ? j : plain, s)) != EED4_OK) {
             break;
         }
         if (hist_dev) {
@@ -581,6 +591,7 @@ static int run_fixed(const CycleJob &j, int M, const eed4_params *p, float *ckpt
     }
     out->cycles = M;
     if (exec && own_exec) (void)hipGraphExecDestroy(exec);
+    if (last && own_last) (void)hipGraphExecDestroy(last);
     if (multi && own_multi) (void)hipGraphExecDestroy(multi);
     return rc;
 }

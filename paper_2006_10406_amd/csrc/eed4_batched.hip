@@ -418,7 +418,7 @@ static void roles(int k, int n, int *sc, int *sp, int *so)
     if (k == n - 1 && n > 1) *so = 0;
 }
 
-static int enqueue_bcycle(const BatchRun &r, hipStream_t s)
+static int enqueue_bcycle(const BatchRun &r, bool residual, hipStream_t s)
 {
     hipError_t e;
     for (int k = 0; k < r.n; ++k) {
@@ -426,7 +426,7 @@ static int enqueue_bcycle(const BatchRun &r, hipStream_t s)
         roles(k, r.n, &sc, &sp, &so);
         StepArgs a = make_args(r.p->sigma, r.R, r.p->tau, 1.0f, k, model_of_flags(r.p->flags));
         e = launch_bstep(r.R, r.shape, r.grid, r.dimg, r.dqueue, r.dqlen, sc, sp,
-                         so, k == r.n - 1, a, r.dpartials, s);
+                         so, residual && k == r.n - 1, a, r.dpartials, s);
         if (e != hipSuccess) return hip_fail(e, "batched step launch");
     }
     if (r.n == 1) {
@@ -435,6 +435,7 @@ static int enqueue_bcycle(const BatchRun &r, hipStream_t s)
         e = hipGetLastError();
         if (e != hipSuccess) return hip_fail(e, "batched copy");
     }
+    if (!residual) return EED4_OK;
     hipLaunchKernelGGL(breduce_kernel, dim3(r.B), dim3(256), 0, s, r.dpartials, r.dslot0,
                        r.dnslot, r.dsums);
     e = hipGetLastError();
@@ -557,12 +558,16 @@ extern "C" int eed4_inpaint_batched(const eed4_image *imgs, int B, const eed4_pa
     if ((rc = prepare(r, imgs, B, p, shape, base, L, s)) != EED4_OK) return rc;
 
     hipGraphExec_t exec = nullptr;
-    if (!(p->flags & EED4_NO_GRAPH)) {
-        rc = capture_graph([&](hipStream_t cs) { return enqueue_bcycle(r, cs); }, &exec);
+    // Without a tolerance only the last cycle's residual is read: the graph
+    // holds the cycles before it, without one, and the last cycle is launched
+    // step by step.
+    const int M = p->max_cycles;
+    const bool tol = p->tol > 0.0f;
+    if (!(p->flags & EED4_NO_GRAPH) && (tol || M > 1)) {
+        rc = capture_graph([&](hipStream_t cs) { return enqueue_bcycle(r, tol, cs); }, &exec);
         if (rc != EED4_OK) return rc;
     }
 
-    const int M = p->max_cycles;
     std::vector<char> active(B, 1);
     std::vector<double> host(2 * (size_t)B);
     std::vector<eed4_stats> st(B);
@@ -570,13 +575,13 @@ extern "C" int eed4_inpaint_batched(const eed4_image *imgs, int B, const eed4_pa
     int nactive = B;
     bool diverged = false;
     for (int m = 0; m < M && nactive > 0 && rc == EED4_OK; ++m) {
-        if (exec) {
+        const bool need = tol || m == M - 1;
+        if (exec && (tol || !need)) {
             e = hipGraphLaunch(exec, s);
             if (e != hipSuccess) { rc = hip_fail(e, "graph launch"); break; }
-        } else if ((rc = enqueue_bcycle(r, s)) != EED4_OK) {
+        } else if ((rc = enqueue_bcycle(r, need, s)) != EED4_OK) {
             break;
         }
-        const bool need = p->tol > 0.0f || m == M - 1;
         if (!need) {
             for (int i = 0; i < B; ++i)
                 if (active[i]) st[i].cycles = m + 1;

@@ -49,6 +49,7 @@ struct CycleJob {
     int model;                 // tensor variant (0: FOEED)
     double *partials;          // per-tile residual partials
     double *sums;              // [B][2] residual sums
+    bool residual = true;      // form the cycle's residual sums
 };
 
 extern thread_local std::string g_last_hip;
