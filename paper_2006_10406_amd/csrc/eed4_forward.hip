@@ -129,47 +129,47 @@ __global__ __launch_bounds__(256) void strip_keepv_kernel(const float *ucur, con
 }
 
 // v = K_sigma * u on the mirror-extended image (the presmoothing of Sec. 2.2)
-// over 64 x 16 tiles: the same taps in the same order as the x and y passes of
-// the fused step, so v is bitwise the one a step from u computes.
+// over the 64 x 16 tiles of the fused step: its stages A and B and its y pass,
+// so v is bitwise the one a step from u computes.  (One LDS read per tap and
+// pixel, as before, took 29.8 us on 2048^2 at R = 6, three times a copy.)
 constexpr int kBlurTW = 64, kBlurTH = 16;
 template <int R>
 __global__ __launch_bounds__(256) void blur_kernel(const float *u_all, float *v_all, int H, int W,
                                                    int nbx, int tiles_per_img, StepArgs a)
 {
-    constexpr int TW = kBlurTW, TH = kBlurTH, SH = TH + 2 * R, SWu = TW + 2 * R;
-    __shared__ float su[SH * SWu];
-    __shared__ float sx[SH * TW];
-    const int tile = xcd_tile(blockIdx.x, gridDim.x);
+    using G = TileGeo<R, kBlurTW, kBlurTH>;
+    __shared__ __attribute__((aligned(16))) float smem[G::SMEM];
+    float *sU = smem, *sX = smem + G::NU;
+    const int tile = __builtin_amdgcn_readfirstlane(xcd_tile(blockIdx.x, gridDim.x));
     const int b = tile / tiles_per_img;
     const int t = tile - b * tiles_per_img;
-    const int y0 = (t / nbx) * TH, x0 = (t - (t / nbx) * nbx) * TW;
-    const float *u = u_all + (size_t)b * H * W;
-    float *v = v_all + (size_t)b * H * W;
-    if constexpr (kLdsSentinel) {
-        sentinel_fill_block(su, SH * SWu);
-        sentinel_fill_block(sx, SH * TW);
-    }
-    for (int k = threadIdx.x; k < SH * SWu; k += 256) {
-        const int rr = k / SWu, cc = k - rr * SWu;
-        const int y = mirror_reflect(y0 - R + rr, H), x = mirror_reflect(x0 - R + cc, W);
-        su[k] = u[(size_t)y * W + x];
-    }
+    const int Y0 = (t / nbx) * kBlurTH, X0 = (t - (t / nbx) * nbx) * G::SW;
+    const int lane = threadIdx.x & 63;
+    const int grp = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), Yg = Y0 + grp * G::OH;
+    if constexpr (kLdsSentinel) sentinel_fill_block(smem, G::SMEM);
+    const unsigned W4 = 4u * (unsigned)W;
+    const int y0 = Y0 - G::h, b0 = y0 > 0 ? y0 : 0;
+    const int nb = H - b0 < G::UH ? H - b0 : G::UH;
+    const size_t base = (size_t)b * H * W + (size_t)b0 * W;
+    const __amdgpu_buffer_rsrc_t rs_u = buffer_rsrc(u_all + base, (unsigned)nb * W4);
+    const __amdgpu_buffer_rsrc_t rs_v = buffer_rsrc(v_all + base, (unsigned)nb * W4);
+    f32x4 st[G::IA];
+    tile_load<G, kThreads>(st, rs_u, X0 - G::SC, y0, b0, H, W);
+    tile_put<G, kThreads>(sU, st);
+    float wv[2 * R + 1];
+    vector_weights<R>(a.w, wv);
     __syncthreads();
-    for (int k = threadIdx.x; k < SH * TW; k += 256) {
-        const int rr = k / TW, c = k - rr * TW;
-        const float *row = su + rr * SWu + c;
-        float acc = a.w[0] * row[0];
+    tile_xpass<R, kBlurTW, G, kThreads>(sU, sX, wv);
+    __syncthreads();
+    const int c = X0 - 2 + lane;
+    const unsigned vo = lane >= 2 && lane < 62 && c < W ? 4u * (unsigned)c : kOffNone;
+    const float *px = sX + 64 * (grp * G::OH + 2) + lane;            // row Yg - R
 #pragma unroll
-        for (int j = 1; j <= 2 * R; ++j) acc = fmaf(a.w[j], row[j], acc);
-        sx[k] = acc;
-    }
-    __syncthreads();
-    for (int k = threadIdx.x; k < TH * TW; k += 256) {
-        const int r = k / TW, c = k - r * TW;
-        const int y = y0 + r, x = x0 + c;
-        if (y >= H || x >= W) continue;
-        const float *colp = sx + (r + R) * TW + c;
-        v[(size_t)y * W + x] = ypass_sym<R>(a.w, [&](int j) { return colp[j * TW]; });
+    for (int j = 0; j < G::OH; ++j) {
+        const float x = ypass_sym<R>(wv, [&](int t) { return px[64 * (j + R + t)]; });
+        if (Yg + j < H)
+            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(x), rs_v, vo,
+                                                  uniform_row(Yg + j - b0) * W4, 0);
     }
 }
 
@@ -313,7 +313,8 @@ template <int R>
 static hipError_t launch_blur_r(const float *u, float *v, int B, int H, int W, const StepArgs &a,
                                 hipStream_t s)
 {
-    const int nbx = (W + kBlurTW - 1) / kBlurTW, nby = (H + kBlurTH - 1) / kBlurTH;
+    const int nbx = (W + tile_cols(kBlurTW) - 1) / tile_cols(kBlurTW);
+    const int nby = (H + kBlurTH - 1) / kBlurTH;
     const long long ntiles = (long long)nbx * nby * B;
     if (ntiles <= 0 || ntiles > 0x7fffffffLL) return hipErrorInvalidValue;
     hipLaunchKernelGGL((blur_kernel<R>), dim3((unsigned)ntiles), dim3(256), 0, s, u, v, H, W, nbx,

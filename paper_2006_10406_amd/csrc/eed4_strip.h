@@ -185,6 +185,14 @@ __device__ __forceinline__ float buf_f32(__amdgpu_buffer_rsrc_t r, unsigned voff
     return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, voff, soff, 0));
 }
 
+// A wave-uniform row index in a scalar register.  The compiler may form such a
+// value with a vector instruction (v_min3), and would then wrap every access
+// that takes it as its scalar offset in a loop over distinct lane values.
+__device__ __forceinline__ unsigned uniform_row(int r)
+{
+    return (unsigned)__builtin_amdgcn_readfirstlane(r);
+}
+
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ f32x4 buf_f32x4(__amdgpu_buffer_rsrc_t r, unsigned voff)

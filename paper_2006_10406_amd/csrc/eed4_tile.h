@@ -43,13 +43,14 @@ __device__ __forceinline__ int mirror_index(int i, int n)
     return m < n ? m : p - 1 - m;
 }
 
-// Half-sample mirror of -n <= i < 2n (one reflection), clamped to the image
-// for indices beyond that (no needed value comes from those).
+// Half-sample mirror of -n <= i < 2n (one reflection at each end: -1 - i == ~i).
+// Indices beyond that give a value the caller clamps (nothing needed comes from
+// them).
 __device__ __forceinline__ int mirror_once(int i, int n)
 {
-    i = i < 0 ? -1 - i : i;
-    i = i >= n ? 2 * n - 1 - i : i;
-    return i < 0 ? 0 : (i >= n ? n - 1 : i);
+    const int m = i > ~i ? i : ~i;
+    const int r = 2 * n - 1 - m;
+    return m < r ? m : r;
 }
 
 template <int R, int TW, int TH, int NTH = kThreads>
@@ -70,7 +71,85 @@ struct TileGeo {
     static constexpr int NU = UH * UW, NX = UH * TW;
     static constexpr int SMEM = NU + NX;                  // floats of LDS
     static constexpr int NV = OH + 4, NT = OH + 2;        // rows of v and of T per group
+    static constexpr int IA = (NA + NTH - 1) / NTH;       // stage A items per thread
 };
+
+// Stage A: 16 bytes of u per item, from row y0 / column xs of the mirrored
+// image (b0: image row of the resource's base), ...
+template <typename G, int NTH>
+__device__ __forceinline__ void tile_load(f32x4 (&st)[G::IA], __amdgpu_buffer_rsrc_t rs, int xs,
+                                          int y0, int b0, int H, int W)
+{
+    const unsigned W4 = 4u * (unsigned)W;
+    if (H >= G::UH && xs >= 0 && xs + 4 * G::UQ <= W) {
+#pragma unroll
+        for (int k = 0; k < G::IA; ++k) {
+            const int it = threadIdx.x + k * NTH, r = it / G::UQ, q = it - r * G::UQ;
+            int y = mirror_once(y0 + r, H);
+            y = y < b0 ? b0 : y;
+            const unsigned vo = it < G::NA ? (unsigned)(y - b0) * W4 + 4u * (unsigned)(xs + 4 * q)
+                                           : kOffNone;
+            st[k] = buf_f32x4(rs, vo);
+        }
+    } else {
+        const bool tiny = H < G::UH || W < 4 * G::UQ;     // may need repeated reflection
+#pragma unroll
+        for (int k = 0; k < G::IA; ++k) {
+            const int it = threadIdx.x + k * NTH, r = it / G::UQ, q = it - r * G::UQ;
+            int y = tiny ? mirror_index(y0 + r, H) : mirror_once(y0 + r, H);
+            y = y < b0 ? b0 : y;
+            const unsigned ro = (unsigned)(y - b0) * W4;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int x = xs + 4 * q + e;
+                int xm = tiny ? mirror_index(x, W) : mirror_once(x, W);
+                xm = xm < 0 ? 0 : xm;
+                st[k][e] = buf_f32(rs, it < G::NA ? ro + 4u * (unsigned)xm : kOffNone, 0);
+            }
+        }
+    }
+}
+
+// ... and into LDS.
+template <typename G, int NTH>
+__device__ __forceinline__ void tile_put(float *sU, const f32x4 (&st)[G::IA])
+{
+#pragma unroll
+    for (int k = 0; k < G::IA; ++k) {
+        const int it = threadIdx.x + k * NTH, r = it / G::UQ, q = it - r * G::UQ;
+        if (it < G::NA) *reinterpret_cast<f32x4 *>(sU + r * G::UW + 4 * q) = st[k];
+    }
+}
+
+// Stage B: x pass of every staged row, four columns per item.
+template <int R, int TW, typename G, int NTH>
+__device__ __forceinline__ void tile_xpass(const float *sU, float *sX, const float (&wv)[2 * R + 1])
+{
+#pragma unroll
+    for (int k = 0; k < (G::NB + NTH - 1) / NTH; ++k) {
+        const int it = threadIdx.x + k * NTH;
+        if (G::NB % NTH == 0 || it < G::NB) {
+            const int r = it / G::NQ, q = it % G::NQ;
+            const f32x4 *src = reinterpret_cast<const f32x4 *>(sU + r * G::UW + 4 * q);
+            float win[4 * G::NF4];
+#pragma unroll
+            for (int f = 0; f < G::NF4; ++f) {
+                const f32x4 t = src[f];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) win[4 * f + e] = t[e];
+            }
+            f32x4 o;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                float acc = wv[0] * win[G::OFF + e];
+#pragma unroll
+                for (int j = 1; j <= 2 * R; ++j) acc = fmaf(wv[j], win[G::OFF + e + j], acc);
+                o[e] = acc;
+            }
+            *reinterpret_cast<f32x4 *>(sX + TW * r + 4 * q) = o;
+        }
+    }
+}
 
 // Accumulates sum (un - ref)^2 and sum un^2 of the tile in FP64 and writes
 // them to out[0..1] (thread 0).  Fixed reduction order: deterministic.
@@ -133,43 +212,19 @@ __device__ __forceinline__ void step_tile(float *smem, const float *ucur, const 
     const __amdgpu_buffer_rsrc_t rs_m = buffer_rsrc(mask + base, (unsigned)nb * (unsigned)W);
 
     // ---- A: loads ----
-    constexpr int IA = (G::NA + NTH - 1) / NTH;
-    f32x4 st[IA];
-    const int xs = X0 - G::SC;                            // image column of staged column 0
-    if (H >= G::UH && xs >= 0 && xs + 4 * G::UQ <= W) {
-#pragma unroll
-        for (int k = 0; k < IA; ++k) {
-            const int it = tid + k * NTH, r = it / G::UQ, q = it - r * G::UQ;
-            int y = mirror_once(y0 + r, H);
-            y = y < b0 ? b0 : y;
-            const unsigned vo = it < G::NA ? (unsigned)(y - b0) * W4 + 4u * (unsigned)(xs + 4 * q)
-                                           : kOffNone;
-            st[k] = buf_f32x4(rs_u, vo);
-        }
-    } else {
-        const bool tiny = H < G::UH || W < 4 * G::UQ;     // may need repeated reflection
-#pragma unroll
-        for (int k = 0; k < IA; ++k) {
-            const int it = tid + k * NTH, r = it / G::UQ, q = it - r * G::UQ;
-            int y = tiny ? mirror_index(y0 + r, H) : mirror_once(y0 + r, H);
-            y = y < b0 ? b0 : y;
-            const unsigned ro = (unsigned)(y - b0) * W4;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int x = xs + 4 * q + e;
-                const int xm = tiny ? mirror_index(x, W) : mirror_once(x, W);
-                st[k][e] = buf_f32(rs_u, it < G::NA ? ro + 4u * (unsigned)xm : kOffNone, 0);
-            }
-        }
-    }
+    f32x4 st[G::IA];
+    tile_load<G, NTH>(st, rs_u, X0 - G::SC, y0, b0, H, W);
     const int c = X0 - 2 + lane;                          // this lane's column
     const bool out_col = lane >= 2 && lane < TW - 2 && c < W;
     const unsigned vo4 = out_col ? 4u * (unsigned)c : kOffNone;
     const unsigned vo1 = out_col ? (unsigned)c : kOffNone;
     // byte offsets of the group's rows: scalar where a group is a whole wave
+    auto in_row = [&](int j) {
+        const int r = (Yg + j < H ? Yg + j : H - 1) - b0;
+        return TW == 64 ? uniform_row(r) : (unsigned)r;
+    };
     auto load_row = [&](__amdgpu_buffer_rsrc_t rs, int j) {
-        const unsigned ro = (unsigned)((Yg + j < H ? Yg + j : H - 1) - b0) * W4;
-        return TW == 64 ? buf_f32(rs, vo4, ro) : buf_f32(rs, vo4 + ro, 0);
+        return TW == 64 ? buf_f32(rs, vo4, in_row(j) * W4) : buf_f32(rs, vo4 + in_row(j) * W4, 0);
     };
     auto store_row = [&](__amdgpu_buffer_rsrc_t rs, int j, float x) {
         const unsigned ro = (unsigned)(Yg + j - b0) * W4;
@@ -185,7 +240,7 @@ __device__ __forceinline__ void step_tile(float *smem, const float *ucur, const 
     unsigned em[OH];
 #pragma unroll
     for (int j = 0; j < OH; ++j) {
-        const unsigned ro = (unsigned)((Yg + j < H ? Yg + j : H - 1) - b0) * (unsigned)W;
+        const unsigned ro = in_row(j) * (unsigned)W;
         ep[j] = load_row(rs_p, j);
         em[j] = TW == 64 ? __builtin_amdgcn_raw_buffer_load_b8(rs_m, vo1, ro, 0)
                          : __builtin_amdgcn_raw_buffer_load_b8(rs_m, vo1 + ro, 0, 0);
@@ -196,41 +251,13 @@ __device__ __forceinline__ void step_tile(float *smem, const float *ucur, const 
 #pragma unroll
         for (int j = 0; j < OH; ++j) ef[j] = load_row(rs_r, j);
     }
-#pragma unroll
-    for (int k = 0; k < IA; ++k) {
-        const int it = tid + k * NTH, r = it / G::UQ, q = it - r * G::UQ;
-        if (it < G::NA) *reinterpret_cast<f32x4 *>(sU + r * G::UW + 4 * q) = st[k];
-    }
+    tile_put<G, NTH>(sU, st);
     float wv[2 * R + 1], vtau = tau, valpha = alpha, vil2q = il2q;
     vector_weights<R>(w, wv);
     asm volatile("" : "+v"(vtau), "+v"(valpha), "+v"(vil2q));
     __syncthreads();
 
-    // ---- B: x pass ----
-#pragma unroll
-    for (int k = 0; k < (G::NB + NTH - 1) / NTH; ++k) {
-        const int it = tid + k * NTH;
-        if (G::NB % NTH == 0 || it < G::NB) {
-            const int r = it / G::NQ, q = it % G::NQ;
-            const f32x4 *src = reinterpret_cast<const f32x4 *>(sU + r * G::UW + 4 * q);
-            float win[4 * G::NF4];
-#pragma unroll
-            for (int f = 0; f < G::NF4; ++f) {
-                const f32x4 t = src[f];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) win[4 * f + e] = t[e];
-            }
-            f32x4 o;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                float acc = wv[0] * win[G::OFF + e];
-#pragma unroll
-                for (int j = 1; j <= 2 * R; ++j) acc = fmaf(wv[j], win[G::OFF + e + j], acc);
-                o[e] = acc;
-            }
-            *reinterpret_cast<f32x4 *>(sX + TW * r + 4 * q) = o;
-        }
-    }
+    tile_xpass<R, TW, G, NTH>(sU, sX, wv);                // ---- B ----
     __syncthreads();
 
     // ---- C: the group's rows; row j of xw, u and v is image row Yg - h + j,
