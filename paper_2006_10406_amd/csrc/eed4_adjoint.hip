@@ -16,14 +16,18 @@
 // transpose exact: q_x comes out odd across vertical borders and even across
 // horizontal ones, q_y the reverse.
 //
-// Two implementations of a reverse step:
-//  - workgroup tiles: pass A computes P(u) r, q and de/dlambda into global
-//    buffers; pass B applies C^T q = K_sigma (-div q) and the update;
-//  - wave strips (one launch): a wave streams down a strip and carries every
-//    intermediate in registers and per-wave LDS, as the forward strip kernel
-//    does.  It reads the presmoothed image K_sigma * u^k, which the forward
-//    recompute keeps, instead of blurring u^k again: that saves the blur's
-//    arithmetic and R rows of halo at each end of a segment.
+// Two implementations of a reverse step, each one launch that reads the
+// presmoothed image K_sigma * u^k, which the forward recompute keeps, instead
+// of blurring u^k again:
+//  - workgroup tiles: q and P(u) r of the tile and its halo in registers, d =
+//    -div q and its x pass through LDS (small and medium problems);
+//  - wave strips: a wave streams down a strip and carries every intermediate
+//    in registers and per-wave LDS, as the forward strip kernel does (fewer
+//    instructions a pixel: large problems).
+// Per step, tiles against the best strip: 512^2 (R = 5) 7.7 against 12.3 us,
+// 16 x 256^2 (R = 3) 12.8 against 15.6, 1024^2 (R = 6) 14.9 against 22.5,
+// 2048^2 (R = 8) 46 against 58, (R = 6) 39 against 38, 4096^2 (R = 6) 146
+// against 114.
 // Known pixels: r is 0 there, so ubar on a known pixel feeds nothing but fbar.
 // Both implementations therefore keep on known pixels the running sum of ubar
 // over the reverse steps done so far; fbar is that sum at the end.  lambdabar
@@ -38,8 +42,6 @@
 #include <vector>
 
 namespace eed4 {
-
-constexpr int kAdjTW = 64, kAdjTH = 16;
 
 // Per-point pieces of the adjoint.  (gx, gy) = G = grad u_sigma; A = Hessian
 // of r, H = Hessian of u.  Outputs: D(G) : A, q = de/dG and s de/ds with
@@ -100,6 +102,7 @@ __device__ __forceinline__ void adjoint_point(float gx, float gy, float inv_lam2
                                               float hxy, float &txx, float &tyy, float &txy,
                                               float &qx, float &qy, float &sds, int model = 0)
 {
+#pragma clang fp contract(off)
     const float s2 = fmaf(gx, gx, gy * gy);
     float mu1, mu3;
     MuData md{};
@@ -155,238 +158,273 @@ __device__ __forceinline__ void adjoint_point(float gx, float gy, float inv_lam2
     sds = s * de_ds;
 }
 
-// The workgroup's sum of v, on thread 0: a pairwise tree over the lanes of
-// each wave, then over the four waves (FP32, fixed order: deterministic).
-__device__ __forceinline__ float block_sum(float v, float *scratch)
+// The rest of a reverse step's arithmetic, shared by its kernels like the point
+// quantities above, with contraction off and every fused multiply-add written
+// out: all kernel shapes give bitwise the same gradients of f and u_init.
+//
+// P(u) r at a pixel from D:A = T there and around it (as outer_div), ...
+__device__ __forceinline__ float adj_outer(float txx_c, float tyy_c, float sxx, float syy, float zd,
+                                           float zu)
 {
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    __syncthreads();
-    if (lane == 0) scratch[wv] = v;
-    __syncthreads();
-    return (scratch[0] + scratch[1]) + (scratch[2] + scratch[3]);
+#pragma clang fp contract(off)
+    return fmaf(0.5f, zd - zu, fmaf(-2.0f, txx_c + tyy_c, sxx + syy));
+}
+// ... d = -div q from q_x(x+1) - q_x(x-1) and q_y(y+1) - q_y(y-1), ...
+__device__ __forceinline__ float adj_div(float ex, float ey)
+{
+#pragma clang fp contract(off)
+    return -0.5f * (ex + ey);
+}
+// ... and the update from pr = P(u) r, cq = C^T q, ubar^{k+1} and ubar^k.  back
+// is (1 - alpha) r, which goes to ubar^k itself at k = 0 (keep_back 1, else 0).
+__device__ __forceinline__ float adj_update(float pr, float cq, float an, float ac, bool known,
+                                            float tau, float alpha, float keep_back, float &back)
+{
+#pragma clang fp contract(off)
+    const float rv = known ? 0.0f : an;
+    back = (1.0f - alpha) * rv;
+    const float acv = fmaf(keep_back, back, fmaf(alpha, fmaf(-tau, pr + cq, rv), ac));
+    return known ? acv + an : acv;                            // known pixel: running sum
 }
 
-template <int R>
-struct AdjAGeo {
-    static constexpr int TW = kAdjTW, TH = kAdjTH;
-    static constexpr int h = R + 2;
-    static constexpr int UH = TH + 2 * h, UWr = TW + 2 * h, UW = (UWr + 3) & ~3;
-    static constexpr int XW = TW + 4, VH = TH + 4;
-    static constexpr int RH = TH + 4, RW = TW + 4;      // r with halo 2
-    static constexpr int PH = TH + 2, PW = TW + 2, NP = PH * PW;
-    static constexpr int NU = UH * UW, NX = UH * XW, NV = VH * XW, NR = RH * RW, NT = 3 * NP;
-    static constexpr int REGA = (NU + NX > NT) ? NU + NX : NT;
-    static constexpr int SMEM = REGA + NV + NR;
-    static constexpr int NPT = (NP + kThreads - 1) / kThreads;
+// ---- fused reverse step on workgroup tiles ----
+//
+// A group of 64 lanes holds 64 consecutive columns c = X0-2-R .. X0+61-R; the
+// NTH / 64 groups stack to QH rows of adjoint point quantities, Y0-1-R ..
+// Y0+TH+R, for the 60-2R x TH outputs of the tile:
+//   Q  every group forms D:A, q and s de/ds of its OQ rows in registers, from v
+//      = K_sigma * u^k, u^k and r = mbar ubar^{k+1} of those rows and the two
+//      around them (all loads of the group in flight at once, lane neighbours
+//      by DPP); the first and last row's T_yy, x difference of T_xy and q_y go
+//      through LDS to the groups above and below
+//   D  d = -div q and P(u) r, into LDS
+//   X  x pass of d, four columns per item from 16-byte LDS reads
+//   F  y pass of d (C^T q) and the reverse update, OF rows per group
+// Like the forward tile it is a chain of a load, a few barriers and the
+// arithmetic of OQ independent rows; the strips below issue fewer instructions
+// a pixel on large images but need one dependent row after the other.  The
+// values are formed by the same operations in the same order as there.
+template <int R, int NTH, int OQ>
+struct AdjTileGeo {
+    static constexpr int NG = NTH / 64;
+    static constexpr int QH = NG * OQ;                        // rows of q
+    static constexpr int TH = QH - 2 * (R + 1);               // output rows
+    static constexpr int OF = (TH + NG - 1) / NG;             // output rows per group
+    static constexpr int h = R + 2, hc = R + 2;               // input halo, first output lane
+    static constexpr int SW = 64 - 2 * hc;
+    static constexpr int DH = TH + 2 * R;                     // rows of d
+    static constexpr int C4 = (R + 3) / 4, OFF = 4 * C4 - R;  // x-pass window: quads to the left, first tap
+    static constexpr int NF4 = (OFF + 4 + 2 * R + 3) / 4;
+    static constexpr int Q0 = hc / 4, NQ = (63 - hc) / 4 - Q0 + 1;   // quads with output lanes
+    static constexpr int PL = 4 * (C4 > Q0 ? C4 - Q0 : 0);    // pad left of lane 0 in a d row
+    static constexpr int DSn = PL + 4 * (Q0 + NQ - 1 - C4 + NF4);
+    static constexpr int DS = DSn > PL + 64 ? DSn : PL + 64;  // row stride of d (a multiple of 4)
+    static constexpr int NE = 6 * NG * 64, ND = DH * DS, NX = DH * 64, NP = TH * 64;
+    static constexpr int LDS = NE + ND + NX + NP;
+    static_assert(TH > 0, "tile height");
 };
 
-// Pass A on one 64 x 16 tile.  r = (mask ? 0 : abar_next) is formed on the fly.
-template <int R>
-__global__ __launch_bounds__(256) void adjoint_a_kernel(const float *u_all, const float *an_all,
-                                                        const uint8_t *__restrict__ mask_all,
-                                                        int H, int W, int nbx, int tiles_per_img,
-                                                        StepArgs a, float lam_scale,
-                                                        float *qx_all, float *qy_all,
-                                                        float *pr_all, float *lam_partials,
-                                                        int lam_stride)
+// Wave-tree sum of v, then the groups' sums in order; thread 0 writes scale * sum.
+template <int NG>
+__device__ __forceinline__ void group_sum(float v, float *scratch, float scale, float *out)
 {
-    using G = AdjAGeo<R>;
-    constexpr int TW = G::TW, TH = G::TH;
-    __shared__ __attribute__((aligned(16))) float smem[G::SMEM];
-    float *sU = smem, *sX = smem + G::NU, *sT = smem;
-    float *sV = smem + G::REGA, *sR = sV + G::NV;
-    const int tile = xcd_tile(blockIdx.x, gridDim.x);
-    const int bimg = tile / tiles_per_img, t = tile - bimg * tiles_per_img;
-    const int ty = t / nbx, tx = t - ty * nbx;
-    const size_t off = (size_t)bimg * H * W;
-    const float *u = u_all + off, *an = an_all + off;
-    const uint8_t *mask = mask_all + off;
-    const int tid = threadIdx.x, gx0 = tx * TW, gy0 = ty * TH;
-    if constexpr (kLdsSentinel) sentinel_fill_block(smem, G::SMEM);
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
+    if ((threadIdx.x & 63) == 0) scratch[threadIdx.x >> 6] = v;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        float t[NG];
+#pragma unroll
+        for (int i = 0; i < NG; ++i) t[i] = scratch[i];
+#pragma unroll
+        for (int w = NG / 2; w > 0; w >>= 1)
+#pragma unroll
+            for (int i = 0; i < w; ++i) t[i] += t[i + w];
+        *out = scale * t[0];
+    }
+}
 
-    // ---- load u (halo R+2) and r (halo 2) ----
-    for (int i = tid; i < G::UH * G::UWr; i += kThreads) {
-        int r = i / G::UWr, c = i - r * G::UWr;
-        int yy = mirror_index(gy0 - G::h + r, H), xx = mirror_index(gx0 - G::h + c, W);
-        sU[r * G::UW + c] = u[(size_t)yy * W + xx];
-    }
-    for (int i = tid; i < G::NR; i += kThreads) {
-        int r = i / G::RW, c = i - r * G::RW;
-        int yy = mirror_index(gy0 - 2 + r, H), xx = mirror_index(gx0 - 2 + c, W);
-        size_t gi = (size_t)yy * W + xx;
-        sR[i] = mask[gi] ? 0.0f : an[gi];
-    }
-    __syncthreads();
-    // ---- presmoothing: x pass then y pass (same layout as the forward tile) ----
-    for (int i = tid; i < G::UH * G::XW; i += kThreads) {
-        int r = i / G::XW, c = i - r * G::XW;
-        const float *src = sU + r * G::UW + c;
-        float s = a.w[0] * src[0];
+template <int R, int NTH, int OQ>
+__global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(4))) void adjoint_tile_kernel(
+    const float *v_all, const float *u_all, const float *an_all, float *ac_all, float *ap_all,
+    const uint8_t *__restrict__ mask_all, int H, int W, int nbx, int tiles_per_img, StepArgs a,
+    float lam_scale, int kflags, float *lam_partials, int lam_stride)
+{
+    using G = AdjTileGeo<R, NTH, OQ>;
+    constexpr int OF = G::OF, h = G::h;
+    __shared__ __attribute__((aligned(16))) float smem[G::LDS];
+    float *sE = smem, *sD = smem + G::NE, *sX = sD + G::ND, *sP = sX + G::NX;
+    const int tile = __builtin_amdgcn_readfirstlane(xcd_tile(blockIdx.x, gridDim.x));
+    const int bimg = tile / tiles_per_img, tl = tile - bimg * tiles_per_img;
+    const int ty = tl / nbx, tx = tl - ty * nbx;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int grp = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int X0 = tx * G::SW, Y0 = ty * G::TH;
+    if constexpr (kLdsSentinel) sentinel_fill_block(smem, G::LDS);
+
+    // resources based at the lowest row a needed value comes from
+    const unsigned W4 = 4u * (unsigned)W;
+    const int b0 = Y0 - h > 0 ? Y0 - h : 0;
+    const int nrow = G::QH + 2;
+    const int nb = H - b0 < nrow ? H - b0 : nrow;
+    const size_t base = (size_t)bimg * H * W + (size_t)b0 * W;
+    const __amdgpu_buffer_rsrc_t rs_v = buffer_rsrc(v_all + base, (unsigned)nb * W4);
+    const __amdgpu_buffer_rsrc_t rs_u = buffer_rsrc(u_all + base, (unsigned)nb * W4);
+    const __amdgpu_buffer_rsrc_t rs_an = buffer_rsrc(an_all + base, (unsigned)nb * W4);
+    const __amdgpu_buffer_rsrc_t rs_m = buffer_rsrc(mask_all + base, (unsigned)nb * (unsigned)W);
+    const int first = kflags & 1, fresh = kflags & 2;
+    const __amdgpu_buffer_rsrc_t rs_ac = buffer_rsrc(ac_all + base, (unsigned)nb * W4);
+    // ubar^k as read: no records in a cycle's first reverse step, where it is 0
+    const __amdgpu_buffer_rsrc_t rs_acl = buffer_rsrc(ac_all + base, fresh ? 0u : (unsigned)nb * W4);
+    // at k = 0 the (1 - alpha) r term stays in ubar^k: stores to ubar^{k-1} are dropped
+    const __amdgpu_buffer_rsrc_t rs_ap = buffer_rsrc(ap_all + base, first ? 0u : (unsigned)nb * W4);
+
+    const int cl = X0 - G::hc + lane;
+    const unsigned cm = (unsigned)mirror_index(cl, W);
+    const bool out_lane = lane >= G::hc && lane < 64 - G::hc && cl < W;
+    const unsigned vo4 = out_lane ? 4u * (unsigned)cl : kOffNone;
+    const unsigned vo1 = out_lane ? (unsigned)cl : kOffNone;
+
+    // ---- Q ----
+    const int q0 = Y0 - (R + 1) + grp * OQ;                   // image row of the group's q row 0
+    float v[OQ + 2], u[OQ + 2], r[OQ + 2];
+    unsigned mk[OQ + 2];
+    const bool tiny = H < nrow;                               // may need repeated reflection
 #pragma unroll
-        for (int j = 1; j <= 2 * R; ++j) s = fmaf(a.w[j], src[j], s);
-        sX[r * G::XW + c] = s;
+    for (int t = 0; t < OQ + 2; ++t) {
+        int y = tiny ? mirror_reflect(q0 - 1 + t, H) : mirror_once(q0 - 1 + t, H);
+        y = y < b0 ? b0 : y;                                  // rows no needed value comes from
+        const unsigned ro = uniform_row((y < b0 + nb ? y : b0 + nb - 1) - b0);
+        v[t] = buf_f32(rs_v, 4u * cm, ro * W4);
+        u[t] = buf_f32(rs_u, 4u * cm, ro * W4);
+        r[t] = buf_f32(rs_an, 4u * cm, ro * W4);
+        mk[t] = __builtin_amdgcn_raw_buffer_load_b8(rs_m, cm, ro * (unsigned)W, 0);
     }
-    __syncthreads();
-    for (int i = tid; i < G::VH * G::XW; i += kThreads) {
-        int r = i / G::XW, c = i - r * G::XW;
-        float s = a.w[0] * sX[r * G::XW + c];
+    float il2 = a.inv_lam2;
+    asm volatile("" : "+v"(il2));
+    float su[OQ + 2], du[OQ + 2], sr[OQ + 2], dr[OQ + 2];
 #pragma unroll
-        for (int j = 1; j <= 2 * R; ++j) s = fmaf(a.w[j], sX[(r + j) * G::XW + c], s);
-        sV[r * G::XW + c] = s;
+    for (int t = 0; t < OQ + 2; ++t) {
+        r[t] = mk[t] ? 0.0f : r[t];
+        const float pu = from_prev_lane(u[t]), nu = from_next_lane(u[t]);
+        const float pr = from_prev_lane(r[t]), nr = from_next_lane(r[t]);
+        su[t] = pu + nu;
+        du[t] = nu - pu;
+        sr[t] = pr + nr;
+        dr[t] = nr - pr;
+    }
+    float txx[OQ], tyy[OQ], z[OQ], ex[OQ], qy[OQ], dsum = 0.0f;
+#pragma unroll
+    for (int t = 0; t < OQ; ++t) {
+        const float gxs = from_next_lane(v[t + 1]) - from_prev_lane(v[t + 1]);   // 2 gx
+        const float gys = v[t + 2] - v[t];                                       // 2 gy
+        const float hxx = fmaf(-2.0f, u[t + 1], su[t + 1]);
+        const float hyy = fmaf(-2.0f, u[t + 1], u[t] + u[t + 2]);
+        const float hxy = 0.25f * (du[t + 2] - du[t]);
+        const float axx = fmaf(-2.0f, r[t + 1], sr[t + 1]);
+        const float ayy = fmaf(-2.0f, r[t + 1], r[t] + r[t + 2]);
+        const float axy = 0.25f * (dr[t + 2] - dr[t]);
+        float txy, qx, sds;
+        adjoint_point(0.5f * gxs, 0.5f * gys, il2, axx, ayy, axy, hxx, hyy, hxy, txx[t],
+                           tyy[t], txy, qx, qy[t], sds);
+        const int g = q0 + t;                                 // image row
+        dsum += (g >= Y0 && g < Y0 + G::TH && g < H && out_lane) ? sds : 0.0f;
+        z[t] = from_next_lane(txy) - from_prev_lane(txy);
+        ex[t] = from_next_lane(qx) - from_prev_lane(qx);
+    }
+    float *e0 = sE + grp * 384 + lane;
+    e0[0] = tyy[0];
+    e0[64] = z[0];
+    e0[128] = qy[0];
+    e0[192] = tyy[OQ - 1];
+    e0[256] = z[OQ - 1];
+    e0[320] = qy[OQ - 1];
+    // what the update of the group's output rows reads
+    const int Yf = Y0 + grp * OF;
+    float an[OF], ac[OF];
+    unsigned om[OF];
+#pragma unroll
+    for (int j = 0; j < OF; ++j) {
+        const int o = Yf + j < H ? Yf + j : H - 1;
+        const unsigned ro = uniform_row((o < b0 + nb ? o : b0 + nb - 1) - b0);
+        an[j] = buf_f32(rs_an, vo4, ro * W4);
+        ac[j] = buf_f32(rs_acl, vo4, ro * W4);
+        om[j] = __builtin_amdgcn_raw_buffer_load_b8(rs_m, vo1, ro * (unsigned)W, 0);
     }
     __syncthreads();
 
-    // ---- per point: tensor applied to Hess(r); q and de/dlambda inside the tile ----
-    float txx[G::NPT], tyy[G::NPT], txy[G::NPT];
-    float dlsum = 0.0f;
+    // ---- D: rows above the group's first and below its last from its neighbours
+    // (the outermost rows of the tile are not needed) ----
+    {
+        const float *eu = sE + (grp > 0 ? grp - 1 : 0) * 384 + lane;
+        const float *ed = sE + (grp + 1 < G::NG ? grp + 1 : grp) * 384 + lane;
+        const float tyu = eu[192], zu = eu[256], qu = eu[320], tyd = ed[0], zd = ed[64], qd = ed[128];
 #pragma unroll
-    for (int k = 0; k < G::NPT; ++k) {
-        int p = tid + k * kThreads;
-        txx[k] = tyy[k] = txy[k] = 0.0f;
-        if (p < G::NP) {
-            int pr = p / G::PW, pc = p - pr * G::PW;
-            const float *v = sV + (pr + 1) * G::XW + (pc + 1);
-            float gx = 0.5f * (v[1] - v[-1]);
-            float gy = 0.5f * (v[G::XW] - v[-G::XW]);
-            const float *uu = sU + (pr + G::h - 1) * G::UW + (pc + G::h - 1);
-            float uc = uu[0];
-            float hxx = (uu[-1] - uc) + (uu[1] - uc);
-            float hyy = (uu[-G::UW] - uc) + (uu[G::UW] - uc);
-            float hxy = 0.25f * ((uu[G::UW + 1] + uu[-G::UW - 1]) - (uu[G::UW - 1] + uu[-G::UW + 1]));
-            const float *rr = sR + (pr + 1) * G::RW + (pc + 1);
-            float rc = rr[0];
-            float axx = (rr[-1] - rc) + (rr[1] - rc);
-            float ayy = (rr[-G::RW] - rc) + (rr[G::RW] - rc);
-            float axy = 0.25f * ((rr[G::RW + 1] + rr[-G::RW - 1]) - (rr[G::RW - 1] + rr[-G::RW + 1]));
-            float qx, qy, sds;
-            adjoint_point(gx, gy, a.inv_lam2, axx, ayy, axy, hxx, hyy, hxy, txx[k], tyy[k], txy[k],
-                          qx, qy, sds);
-            int yy = gy0 + pr - 1, xx = gx0 + pc - 1;
-            if (pr >= 1 && pr <= TH && pc >= 1 && pc <= TW && yy < H && xx < W) {
-                size_t gi = off + (size_t)yy * W + xx;
-                qx_all[gi] = qx;
-                qy_all[gi] = qy;
-                dlsum += sds;
+        for (int t = 0; t < OQ; ++t) {
+            const float qn = t + 1 < OQ ? qy[t + 1 < OQ ? t + 1 : 0] : qd;
+            const float qp = t > 0 ? qy[t > 0 ? t - 1 : 0] : qu;
+            const int dr_ = grp * OQ + t - 1;                 // row of d
+            if (dr_ >= 0 && dr_ < G::DH) sD[dr_ * G::DS + G::PL + lane] = adj_div(ex[t], qn - qp);
+            const int o = dr_ - R;                            // output row
+            if (o >= 0 && o < G::TH) {
+                const float sxx = from_prev_lane(txx[t]) + from_next_lane(txx[t]);
+                const float tn = t + 1 < OQ ? tyy[t + 1 < OQ ? t + 1 : 0] : tyd;
+                const float tp = t > 0 ? tyy[t > 0 ? t - 1 : 0] : tyu;
+                const float zn = t + 1 < OQ ? z[t + 1 < OQ ? t + 1 : 0] : zd;
+                const float zp = t > 0 ? z[t > 0 ? t - 1 : 0] : zu;
+                sP[o * 64 + lane] = adj_outer(txx[t], tyy[t], sxx, tp + tn, zn, zp);
             }
         }
     }
+    float wv[2 * R + 1], alpha = a.alpha, tau = a.tau, keep_back = first ? 1.0f : 0.0f;
+    vector_weights<R>(a.w, wv);
+    asm volatile("" : "+v"(alpha), "+v"(tau), "+v"(keep_back));
     __syncthreads();
-    if constexpr (kLdsSentinel) sentinel_fill_block(sT, G::NT);
+
+    // ---- X ----
 #pragma unroll
-    for (int k = 0; k < G::NPT; ++k) {
-        int p = tid + k * kThreads;
-        if (p < G::NP) {
-            sT[p] = txx[k];
-            sT[G::NP + p] = tyy[k];
-            sT[2 * G::NP + p] = txy[k];
+    for (int k = 0; k < (G::DH * G::NQ + NTH - 1) / NTH; ++k) {
+        const int it = tid + k * NTH;
+        if (it < G::DH * G::NQ) {
+            const int row = it / G::NQ, q = it - row * G::NQ + G::Q0;
+            const f32x4 *src = reinterpret_cast<const f32x4 *>(sD + row * G::DS + G::PL + 4 * (q - G::C4));
+            float win[4 * G::NF4];
+#pragma unroll
+            for (int f = 0; f < G::NF4; ++f) {
+                const f32x4 x = src[f];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) win[4 * f + e] = x[e];
+            }
+            f32x4 o;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                float acc = wv[0] * win[G::OFF + e];
+#pragma unroll
+                for (int j = 1; j <= 2 * R; ++j) acc = fmaf(wv[j], win[G::OFF + e + j], acc);
+                o[e] = acc;
+            }
+            *reinterpret_cast<f32x4 *>(sX + 64 * row + 4 * q) = o;
         }
     }
     __syncthreads();
-    // ---- outer differences: P(u) r ----
-    const int c = tid % TW, r0 = tid / TW;
-    for (int r = r0; r < TH; r += kThreads / TW) {
-        int yy = gy0 + r, xx = gx0 + c;
-        if (yy < H && xx < W) {
-            int p = (r + 1) * G::PW + (c + 1);
-            const float *Txx = sT + p, *Tyy = sT + G::NP + p, *Txy = sT + 2 * G::NP + p;
-            float pu = ((Txx[-1] - Txx[0]) + (Txx[1] - Txx[0])) +
-                       ((Tyy[-G::PW] - Tyy[0]) + (Tyy[G::PW] - Tyy[0])) +
-                       0.5f * ((Txy[G::PW + 1] + Txy[-G::PW - 1]) - (Txy[G::PW - 1] + Txy[-G::PW + 1]));
-            pr_all[off + (size_t)yy * W + xx] = pu;
+
+    // ---- F ----
+    if (Yf < H) {
+        const float *px = sX + 64 * (grp * OF) + lane, *pp = sP + 64 * (grp * OF) + lane;
+#pragma unroll
+        for (int j = 0; j < OF; ++j) {
+            if (grp * OF + j >= G::TH || Yf + j >= H) break;  // (wave-uniform)
+            float cq = 0.0f;
+#pragma unroll
+            for (int t = 0; t <= 2 * R; ++t) cq = fmaf(wv[t], px[64 * (j + t)], cq);
+            float back;
+            const float acv = adj_update(pp[64 * j], cq, an[j], ac[j], om[j] != 0, tau, alpha,
+                                         keep_back, back);
+            const unsigned ro = (unsigned)(Yf + j - b0) * W4;
+            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(back), rs_ap, vo4, ro, 0);
+            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acv), rs_ac, vo4, ro, 0);
         }
     }
-    __syncthreads();
-    const float tot = block_sum(dlsum, smem);
-    if (threadIdx.x == 0) lam_partials[(size_t)bimg * lam_stride + t] = lam_scale * tot;
-}
-
-template <int R>
-struct AdjBGeo {
-    static constexpr int TW = kAdjTW, TH = kAdjTH;
-    static constexpr int QH = TH + 2 * R + 2, QW = TW + 2 * R + 2;   // q with halo R+1
-    static constexpr int DH = TH + 2 * R, DW = TW + 2 * R;           // -div q with halo R
-    static constexpr int NQ = QH * QW, ND = DH * DW, NX = DH * TW;
-    static constexpr int SMEM = 2 * NQ + ND + NX;
-};
-
-// q with the parity of a gradient component across the mirror borders.
-__device__ __forceinline__ float load_q(const float *q, int y, int x, int H, int W, bool odd_x)
-{
-    int py = 2 * H, px = 2 * W;
-    int my = y % py, mx = x % px;
-    if (my < 0) my += py;
-    if (mx < 0) mx += px;
-    bool fy = my >= H, fx = mx >= W;
-    int yy = fy ? py - 1 - my : my, xx = fx ? px - 1 - mx : mx;
-    float v = q[(size_t)yy * W + xx];
-    bool flip = odd_x ? fx : fy;
-    return flip ? -v : v;
-}
-
-// Pass B on one 64 x 16 tile: C^T q and the pointwise reverse-step update.
-template <int R>
-__global__ __launch_bounds__(256) void adjoint_b_kernel(const float *qx_all, const float *qy_all,
-                                                        const float *pr_all, const float *an_all,
-                                                        float *ac_all, float *ap_all,
-                                                        const uint8_t *__restrict__ mask_all,
-                                                        int H, int W, int nbx,
-                                                        int tiles_per_img, StepArgs a, int kflags)
-{
-    using G = AdjBGeo<R>;
-    constexpr int TW = G::TW, TH = G::TH;
-    __shared__ float smem[G::SMEM];
-    float *sQx = smem, *sQy = smem + G::NQ, *sD = smem + 2 * G::NQ, *sX = sD + G::ND;
-    const int tile = xcd_tile(blockIdx.x, gridDim.x);
-    const int bimg = tile / tiles_per_img, t = tile - bimg * tiles_per_img;
-    const int ty = t / nbx, tx = t - ty * nbx;
-    const size_t off = (size_t)bimg * H * W;
-    const int tid = threadIdx.x, gx0 = tx * TW, gy0 = ty * TH;
-    if constexpr (kLdsSentinel) sentinel_fill_block(smem, G::SMEM);
-
-    for (int i = tid; i < G::NQ; i += kThreads) {
-        int r = i / G::QW, c = i - r * G::QW;
-        int yy = gy0 - R - 1 + r, xx = gx0 - R - 1 + c;
-        sQx[i] = load_q(qx_all + off, yy, xx, H, W, true);
-        sQy[i] = load_q(qy_all + off, yy, xx, H, W, false);
-    }
-    __syncthreads();
-    // d = -div q = -(D_x q_x + D_y q_y) with central differences
-    for (int i = tid; i < G::ND; i += kThreads) {
-        int r = i / G::DW, c = i - r * G::DW;
-        int p = (r + 1) * G::QW + (c + 1);
-        sD[i] = -0.5f * ((sQx[p + 1] - sQx[p - 1]) + (sQy[p + G::QW] - sQy[p - G::QW]));
-    }
-    __syncthreads();
-    for (int i = tid; i < G::NX; i += kThreads) {
-        int r = i / TW, c = i - r * TW;
-        const float *src = sD + r * G::DW + c;
-        float s = a.w[0] * src[0];
-#pragma unroll
-        for (int j = 1; j <= 2 * R; ++j) s = fmaf(a.w[j], src[j], s);
-        sX[i] = s;
-    }
-    __syncthreads();
-    const int c = tid % TW, r0 = tid / TW;
-    for (int r = r0; r < TH; r += kThreads / TW) {
-        int yy = gy0 + r, xx = gx0 + c;
-        if (yy >= H || xx >= W) continue;
-        float cq = a.w[0] * sX[r * TW + c];
-#pragma unroll
-        for (int j = 1; j <= 2 * R; ++j) cq = fmaf(a.w[j], sX[(r + j) * TW + c], cq);
-        size_t gi = off + (size_t)yy * W + xx;
-        const float anv = an_all[gi];
-        const bool m = mask_all[gi] != 0;
-        const float rv = m ? 0.0f : anv;
-        const float z = pr_all[gi] + cq;
-        const float acold = (kflags & 2) ? 0.0f : ac_all[gi];  // a cycle's first reverse step
-        float acv = fmaf(a.alpha, fmaf(-a.tau, z, rv), acold);
-        const float back = (1.0f - a.alpha) * rv;
-        if (kflags & 1) acv += back;
-        else ap_all[gi] = back;
-        if (m) acv += anv;              // known pixel: running sum of ubar
-        ac_all[gi] = acv;
-    }
+    group_sum<G::NG>(dsum, sE, lam_scale, lam_partials + (size_t)bimg * lam_stride + tl);
 }
 
 // ---- fused reverse step on wave strips ----
@@ -481,6 +519,13 @@ __device__ __forceinline__ void adjoint_strip_step(float *lds, const AdjStripArg
     float *dw = lds + lane;
     float *prr = lds + G::ND + lane;
 
+    float wv[2 * R + 1];
+    if constexpr (!GEN) {
+        vector_weights<R>(w, wv);
+    } else {                          // the variants have no registers left at 4 waves a SIMD
+#pragma unroll
+        for (int j = 0; j <= 2 * R; ++j) wv[j] = w[j];
+    }
     float dwin[P];                    // x-pass d; stream row j in slot j % P
 #pragma unroll
     for (int j = 0; j < P; ++j) dwin[j] = 0.0f;
@@ -600,13 +645,13 @@ __device__ __forceinline__ void adjoint_strip_step(float *lds, const AdjStripArg
 
             // ---- S4 at row g - 1: P(u) r and d = -div q ----
             const float sxx = from_prev_lane(txx_p) + from_next_lane(txx_p);
-            const float pr = fmaf(-2.0f, txx_p + tyy_p, sxx + (tyy_pp + ty_)) + 0.5f * (z - z_pp);
-            const float d = -0.5f * ((from_next_lane(qx_p) - from_prev_lane(qx_p)) + (qy - qy_pp));
+            const float pr = adj_outer(txx_p, tyy_p, sxx, tyy_pp + ty_, z, z_pp);
+            const float d = adj_div(from_next_lane(qx_p) - from_prev_lane(qx_p), qy - qy_pp);
             dw[R] = d;
             wave_lds_sync();
-            float dx = w[0] * dw[0];
+            float dx = wv[0] * dw[0];
 #pragma unroll
-            for (int j = 1; j <= 2 * R; ++j) dx = fmaf(w[j], dw[j], dx);
+            for (int j = 1; j <= 2 * R; ++j) dx = fmaf(wv[j], dw[j], dx);
             const int jd = ((ph - 2) % P + P) % P;                    // slot of stream row i - 2
             dwin[jd] = dx;
             prr[jd * 64] = pr;
@@ -625,18 +670,16 @@ __device__ __forceinline__ void adjoint_strip_step(float *lds, const AdjStripArg
                 float cq = 0.0f;                                     // stream rows i-h-R .. i-2
 #pragma unroll
                 for (int j = 0; j <= 2 * R; ++j)
-                    cq = fmaf(w[j], dwin[((ph - h - R + j) % P + P) % P], cq);
+                    cq = fmaf(wv[j], dwin[((ph - h - R + j) % P + P) % P], cq);
                 const float pro = prr[((ph - h) % P + P) % P * 64];
                 const int so = ((ph - h) % U + U) % U;              // stream row i - h
                 const float anv = OREG ? rnq[so] : cur.oa;
                 const bool mk = (OREG ? rmq[so] : cur.omk) != 0;
-                const float rv = mk ? 0.0f : anv;
-                float acv = fmaf(s.alpha, fmaf(-s.tau, pro + cq, rv), cur.oc);
-                const float back = (1.0f - s.alpha) * rv;
+                float back;
+                const float acv = adj_update(pro, cq, anv, cur.oc, mk, s.tau, s.alpha, keep_back,
+                                             back);
                 const unsigned ro = (unsigned)(o - b0) * W4;
-                acv = fmaf(keep_back, back, acv);
                 __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(back), rs_ap, vo4, ro, 0);
-                if (mk) acv += anv;                                  // known pixel: running sum
                 __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acv), rs_ac, vo4, ro, 0);
             }
         }
@@ -821,9 +864,17 @@ static unsigned grid_for(size_t n)
     return (unsigned)(b > 8192 ? 8192 : (b < 1 ? 1 : b));
 }
 
-static int adjoint_tiles_per_image(int H, int W)
+// Reverse tile of a forward tile shape: threads and q rows per group.
+#define EED4_ADJ_TILES(CALL)                                          \
+    case 0: return CALL(512, 6);                                      \
+    case 1: return CALL(256, 6);                                      \
+    default: return CALL(512, 4);
+
+template <int R, int NTH, int OQ>
+static int adj_tile_items_t(int H, int W)
 {
-    return ((W + kAdjTW - 1) / kAdjTW) * ((H + kAdjTH - 1) / kAdjTH);
+    using G = AdjTileGeo<R, NTH, OQ>;
+    return ((W + G::SW - 1) / G::SW) * ((H + G::TH - 1) / G::TH);
 }
 
 template <int R, int ROWS>
@@ -847,7 +898,9 @@ static int adj_items_r(int shape, int H, int W)
     case kShapeStripShort:
     case kShapeStripWideShort: return adj_strip_items_t<R, 28>(H, W);
     case kShapeStripTiny: return adj_strip_items_t<R, 8>(H, W);
-    default: return adjoint_tiles_per_image(H, W);
+#define EED4_CALL_T(nth, oq) adj_tile_items_t<R, nth, oq>(H, W)
+    EED4_ADJ_TILES(EED4_CALL_T)
+#undef EED4_CALL_T
     }
 }
 
@@ -859,8 +912,7 @@ static int adj_items_r(int shape, int H, int W)
     default: break;                                                                 \
     }
 
-// Work items per image of a reverse step: tiles (every tile shape, one adjoint
-// tile shape) or strip segments of the given height.
+// Work items per image of a reverse step: tiles or strip segments.
 static int adjoint_items(int R, int shape, int H, int W)
 {
 #define EED4_CALL_N(r) adj_items_r<r>(shape, H, W)
@@ -878,10 +930,9 @@ static int max_adjoint_items(int R, int H, int W)
 
 // Buffers of one reverse step.
 struct RevStep {
-    const float *v;          // K_sigma * u^k (strip path only)
+    const float *v;          // K_sigma * u^k
     const float *u, *an;     // u^k, ubar^{k+1}
     float *ac, *ap;          // ubar^k (in place), ubar^{k-1} contribution
-    float *qx, *qy, *pr;     // tile path only
     const uint8_t *mask;
     float *lp;               // lambda partials of this step: image b, item r at lp[b * ls + r]
     int ls;                  // ... image stride (cycle_len * items per image)
@@ -890,19 +941,16 @@ struct RevStep {
     int kflags() const { return (first ? 1 : 0) | (fresh ? 2 : 0); }
 };
 
-template <int R>
-static hipError_t launch_rev_tile(const RevStep &t, const StepArgs &a, float ls,
-                                  hipStream_t s)
+template <int R, int NTH, int OQ>
+static hipError_t launch_rev_tile(const RevStep &t, const StepArgs &a, float ls, hipStream_t s)
 {
-    const int nbx = (t.W + kAdjTW - 1) / kAdjTW;
-    const int tpi = adjoint_tiles_per_image(t.H, t.W);
-    hipLaunchKernelGGL((adjoint_a_kernel<R>), dim3((unsigned)(tpi * t.B)), dim3(256), 0, s, t.u,
-                       t.an, t.mask, t.H, t.W, nbx, tpi, a, ls, t.qx, t.qy, t.pr, t.lp,
-                       t.ls);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((adjoint_b_kernel<R>), dim3((unsigned)(tpi * t.B)), dim3(256), 0, s, t.qx,
-                       t.qy, t.pr, t.an, t.ac, t.ap, t.mask, t.H, t.W, nbx, tpi, a, t.kflags());
+    using G = AdjTileGeo<R, NTH, OQ>;
+    const int nbx = (t.W + G::SW - 1) / G::SW;
+    const int tpi = adj_tile_items_t<R, NTH, OQ>(t.H, t.W);
+    if ((long long)tpi * t.B > 0x7fffffffLL) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((adjoint_tile_kernel<R, NTH, OQ>), dim3((unsigned)(tpi * t.B)), dim3(NTH),
+                       0, s, t.v, t.u, t.an, t.ac, t.ap, t.mask, t.H, t.W, nbx, tpi, a, ls,
+                       t.kflags(), t.lp, t.ls);
     return hipGetLastError();
 }
 
@@ -973,7 +1021,9 @@ static hipError_t launch_rev_r(const RevStep &t, const StepArgs &a, float ls,
     case kShapeStripShort:
     case kShapeStripWideShort: return launch_rev_strip<R, 28>(t, a, ls, s);
     case kShapeStripTiny: return launch_rev_strip<R, 8>(t, a, ls, s);
-    default: return launch_rev_tile<R>(t, a, ls, s);
+#define EED4_CALL_T(nth, oq) launch_rev_tile<R, nth, oq>(t, a, ls, s)
+    EED4_ADJ_TILES(EED4_CALL_T)
+#undef EED4_CALL_T
     }
 }
 
@@ -1043,7 +1093,7 @@ static hipError_t launch_adjoint_final(const float *abar0, const uint8_t *mask, 
 
 // ---- workspace layout of eed4_backward ----
 struct BackwardLayout {
-    size_t U, V, an, ac, ap, qx, qy, pr, lp, t1, t2, cyc, slots, total;
+    size_t U, V, an, ac, ap, lp, t1, t2, cyc, slots, total;
 };
 
 static BackwardLayout backward_layout(int B, int H, int W, int n, int R)
@@ -1058,9 +1108,6 @@ static BackwardLayout backward_layout(int B, int H, int W, int n, int R)
     L.an = o; o = align_up(o + sizeof(float) * N);
     L.ac = o; o = align_up(o + sizeof(float) * N);
     L.ap = o; o = align_up(o + sizeof(float) * N);
-    L.qx = o; o = align_up(o + sizeof(float) * N);
-    L.qy = o; o = align_up(o + sizeof(float) * N);
-    L.pr = o; o = align_up(o + sizeof(float) * N);
     // lambda: one FP32 partial per work item and reverse step of a cycle, the
     // pairwise passes over them, the cycle sum and 32 cascade slots (per image)
     const size_t per_img = (size_t)(n > 0 ? n : 1) * (size_t)max_adjoint_items(R, H, W);
@@ -1102,7 +1149,7 @@ static int adjoint_shape(const eed4_params *p, RevStep t, hipStream_t s, int *sh
     const std::string key = adjoint_tune_key(t.R, t.B, t.H, t.W);
     if (tune_lookup(key, shape)) return EED4_OK;
     // the wide forward shapes map onto the same reverse strips as their heights
-    const int cands[] = {kShapeStrip, 0, kShapeStripTall, kShapeStripShort, kShapeStripTiny};
+    const int cands[] = {kShapeStrip, 0, 1, 2, kShapeStripTall, kShapeStripShort, kShapeStripTiny};
     const size_t N = (size_t)t.B * t.H * t.W;
     // the strip candidates read the presmoothed state t.v
     const StepArgs a0 = make_args(p->sigma, t.R, p->tau, p->lambda, 0, model_of_flags(p->flags));
@@ -1154,9 +1201,6 @@ extern "C" int eed4_backward(const float *ckpt, const uint8_t *mask, const float
     t.an = (float *)(base + L.an);
     t.ac = (float *)(base + L.ac);
     t.ap = (float *)(base + L.ap);
-    t.qx = (float *)(base + L.qx);
-    t.qy = (float *)(base + L.qy);
-    t.pr = (float *)(base + L.pr);
     t.mask = mask;
     t.lp = lp;
     t.ls = n * max_adjoint_items(R, H, W);     // the tuner's steps below write within this
@@ -1180,7 +1224,6 @@ extern "C" int eed4_backward(const float *ckpt, const uint8_t *mask, const float
         probe.v = Vbuf;
         if ((rc = adjoint_shape(p, probe, s, &t.shape)) != EED4_OK) return rc;
     }
-    const bool keep_v = is_strip(t.shape);      // the strip reverse step reads K_sigma * u^k
     const int items = adjoint_items(R, t.shape, H, W);
     t.ls = n * items;
     EED4_TRY(hipMemcpyAsync((void *)t.an, grad_u, sizeof(float) * N, hipMemcpyDeviceToDevice, s),
@@ -1217,19 +1260,14 @@ extern "C" int eed4_backward(const float *ckpt, const uint8_t *mask, const float
         for (int k = 0; k + 1 < n; ++k) {
             float *out = Uset[m & 1] + (size_t)k * N;
             StepArgs a = make_args(p->sigma, R, p->tau, p->lambda, k, model_of_flags(p->flags));
-            hipError_t r = keep_v
-                ? launch_step_keepv(R, fshape, U[k], U[k > 0 ? k - 1 : 0], out, V + (size_t)k * N,
-                                    mask, B, H, W, a, s1)
-                : launch_step(R, fshape, U[k], U[k > 0 ? k - 1 : 0], out, nullptr, mask, B, H, W,
-                              a, nullptr, s1);
+            hipError_t r = launch_step_keepv(R, fshape, U[k], U[k > 0 ? k - 1 : 0], out,
+                                             V + (size_t)k * N, mask, B, H, W, a, s1);
             if (r != hipSuccess) return r;
             U[k + 1] = out;
         }
-        if (keep_v) {
-            const StepArgs a = make_args(p->sigma, R, p->tau, p->lambda, 0, model_of_flags(p->flags));
-            hipError_t r = launch_blur(R, U[n - 1], V + (size_t)(n - 1) * N, B, H, W, a, s1);
-            if (r != hipSuccess) return r;
-        }
+        const StepArgs a = make_args(p->sigma, R, p->tau, p->lambda, 0, model_of_flags(p->flags));
+        const hipError_t r = launch_blur(R, U[n - 1], V + (size_t)(n - 1) * N, B, H, W, a, s1);
+        if (r != hipSuccess) return r;
         return hipEventRecord(rec[m & 1], s1);
     };
     float *an = (float *)t.an, *ac = t.ac, *ap = t.ap;

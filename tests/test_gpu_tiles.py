@@ -55,3 +55,28 @@ def test_variant_tiles_equal_variant_strips(B, H, W, sigma, d, r):
     got = cycle(b, sigma, 2, fl)
     assert np.array_equal(got[0], ref[0])
     np.testing.assert_allclose(got[1], ref[1], rtol=1e-12, atol=0)
+
+
+@pytest.mark.parametrize("sigma", [0.0, 0.3, 1.0, 1.5, 2.0, 2.6])
+@pytest.mark.parametrize("H,W", [(10, 48), (34, 49), (35, 97), (24, 54), (25, 55), (1, 70), (70, 1),
+                                 (3, 3), (120, 130)])
+def test_reverse_tiles_equal_reverse_strips(H, W, sigma):
+    # all reverse shapes form every value the same way: gradients of f and u_init bitwise equal
+    # (dL/dlambda sums the same terms in another grouping; the oracle tests bound it)
+    announce(f"reverse tiles vs strips {H}x{W} sigma={sigma}")
+    b = batch(2, H, W, 90 + H + W)
+    mask, known = to_dev(b["mask"]), to_dev(b["known"])
+    gu = torch.from_numpy(np.random.default_rng(H * W).standard_normal((2, H, W)).astype(np.float32)).cuda()
+    out = {}
+    for shape in (6, 0, 1, 2):
+        p = eed4.params(0.03, sigma, 0.05, 3, 2, flags=eed4.EED4_FORCE_SHAPE(shape))
+        u = to_dev(b["u_init"])
+        ck = torch.empty((2, 2, H, W), device="cuda")
+        eed4.eed4_inpaint(u, mask, known, p, ckpt=ck)
+        g = [torch.empty_like(gu), torch.empty_like(gu), torch.empty(2, device="cuda")]
+        eed4.eed4_backward(ck, mask, known, p, 2, gu, *g)
+        torch.cuda.synchronize()
+        out[shape] = g
+    for shape in (0, 1, 2):
+        assert torch.equal(out[shape][0], out[6][0]) and torch.equal(out[shape][1], out[6][1]), shape
+        assert torch.isfinite(out[shape][2]).all()
