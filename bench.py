@@ -56,22 +56,25 @@ def flops_per_update(R):
     differences 13, FSI update and hold 5."""
     return 4 * (2 * R + 1) + 70
 # kernel behind each fused-step shape (template arguments: radius, residual
-# variant, least segment rows, columns per lane; or tile width and height)
-STRIP_GEOMETRY = {"strip": (64, 1), "strip_tall": (136, 1), "strip_short": (28, 1),
-                  "strip_tiny": (8, 1), "strip_wide": (64, 2), "strip_wide_short": (28, 2)}
+# variant, then the least segment rows of the 60-column strips, or the keep-v
+# variant of the 124-column strips; or tile width and height)
+STRIP_ROWS = {"strip_short": 28, "strip_tiny": 8}
+PAIR_SHAPES = ("strip", "strip_tall", "strip_wide", "strip_wide_short")
 TILE_GEOMETRY = {"tile64x32": (64, 32), "tile64x16": (64, 16), "tile32x32": (32, 32),
                  "tile32x16": (32, 16), "tile16x16": (16, 16)}
 
 
 def kernel_name(shape_name, R):
-    if shape_name in STRIP_GEOMETRY:
-        rows, cpl = STRIP_GEOMETRY[shape_name]
-        return f"strip_kernel<{R}, false, {rows}, {cpl}>"
+    if shape_name in PAIR_SHAPES:
+        return f"pair_kernel<{R}, false, false>"
+    if shape_name in STRIP_ROWS:
+        return f"strip_kernel<{R}, false, {STRIP_ROWS[shape_name]}>"
     tw, th = TILE_GEOMETRY[shape_name]
     return f"step_kernel<{R}, {tw}, {th}, false, false, false>"
 
 
 KERNEL_SOURCES = ("paper_2006_10406_amd/csrc/eed4_strip.h",
+                  "paper_2006_10406_amd/csrc/eed4_pair.h",
                   "paper_2006_10406_amd/csrc/eed4_forward.hip",
                   "paper_2006_10406_amd/csrc/eed4_tile.h",
                   "paper_2006_10406_amd/csrc/eed4_pointwise.h",

@@ -134,7 +134,7 @@ int enqueue_cycle(const CycleJob &j, hipStream_t s)
         if (e != hipSuccess) return hip_fail(e, "cycle copy");
     }
     if (!j.residual) return EED4_OK;
-    hipError_t e = launch_reduce(j.partials, tiles_per_image(j.shape, j.R, j.H, j.W), j.B, j.sums, s);
+    hipError_t e = launch_reduce(j.partials, tiles_per_image(j.shape, j.R, j.B, j.H, j.W), j.B, j.sums, s);
     if (e != hipSuccess) return hip_fail(e, "residual reduce launch");
     return EED4_OK;
 }
@@ -247,11 +247,11 @@ struct InpaintLayout {
 };
 
 // residual partials: enough for the largest per-image count of any kernel shape
-int max_partials_per_image(int R, int H, int W)
+int max_partials_per_image(int R, int B, int H, int W)
 {
     int m = 0;
     for (int sh = 0; sh < kNumShapes; ++sh) {
-        int t = tiles_per_image(sh, R, H, W);
+        int t = tiles_per_image(sh, R, B, H, W);
         if (t > m) m = t;
     }
     return m;
@@ -261,7 +261,7 @@ InpaintLayout inpaint_layout(int op, int B, int H, int W, int R, int M)
 {
     InpaintLayout L{};
     size_t N = (size_t)B * H * W;
-    size_t tiles = (size_t)max_partials_per_image(R, H, W) * B;
+    size_t tiles = (size_t)max_partials_per_image(R, B, H, W) * B;
     size_t o = 0;
     L.X = o; o = align_up(o + sizeof(float) * N);
     L.Y = o; o = align_up(o + sizeof(float) * N);
@@ -356,18 +356,24 @@ int run_shape(const eed4_params *p, int B, int H, int W)
 
 int default_step_shape(int R, int B, int H, int W)
 {
-    const long long waves = (long long)tiles_per_image(kShapeStrip, R, H, W) * B;
-    return waves < kMinStripWaves ? 2 : kShapeStrip;
+    const long long blocks = (long long)((W + 59) / 60) * ((H + 63) / 64) * B;
+    return blocks < kMinStripBlocks ? 2 : kShapeStrip;
 }
 
-// Times one inner step (k = 0, S -> X; S is not modified) of every candidate
-// shape (tune_candidates) and remembers the fastest for this problem size.
+// Times the inner steps of every candidate shape (tune_candidates) and remembers
+// the fastest for this problem size.  A step reads u^k = S (not modified) and
+// u^{k-1} = X and writes X, three planes as in a run; the first of every
+// kTuneLaunches is step 0, S -> X.  (Timed on step 0 alone, which reads one
+// plane less, the 28-row strips were chosen at 2900^2, R = 6, though the default
+// is 5 % faster there in a run.)
 int tune_single_step(const eed4_params *p, int B, int H, int W, float *S, float *X,
                      const uint8_t *mask, hipStream_t s, int *shape)
 {
     TraceRange range("eed4 step-shape tuning %dx%dx%d", B, H, W);
     const int R = eed4_radius(p->sigma);
-    const StepArgs a = make_args(p->sigma, R, p->tau, p->lambda, 0);
+    const StepArgs a0 = make_args(p->sigma, R, p->tau, p->lambda, 0);
+    const StepArgs a1 = make_args(p->sigma, R, p->tau, p->lambda, 1);
+    unsigned launched = 0;
     int order[kNumShapes];
     const int first = default_step_shape(R, B, H, W);
     const int nc = tune_candidates(first, order);
@@ -376,7 +382,9 @@ int tune_single_step(const eed4_params *p, int B, int H, int W, float *S, float 
     const int rc = tune_pick(
         order, nc, s, [](int) { return (int)EED4_OK; },
         [&](int sh, hipStream_t q) {
-            return launch_step(R, sh, S, S, X, nullptr, mask, B, H, W, a, nullptr, q);
+            const bool head = launched++ % kTuneLaunches == 0;
+            return launch_step(R, sh, S, head ? S : X, X, nullptr, mask, B, H, W, head ? a0 : a1,
+                               nullptr, q);
         },
         "step autotune", shape, nullptr, margins);
     if (rc != EED4_OK) return rc;

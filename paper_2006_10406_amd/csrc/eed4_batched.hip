@@ -19,6 +19,7 @@
 #include "eed4.h"
 #include "eed4_host.h"
 #include "eed4_internal.h"
+#include "eed4_pair.h"
 #include "eed4_strip.h"
 #include "eed4_tile.h"
 
@@ -64,14 +65,37 @@ __device__ __forceinline__ T *uni(T *p)
     return (T *)(((unsigned long long)hi << 32) | lo);
 }
 
+// The strip of a queue entry, as StripArgs.
+__device__ __forceinline__ StripArgs bstrip_item(const BImage &d, const BItem &t, int sc, int sp,
+                                                 int so, int sw, int oh, const StepArgs &a)
+{
+    StripArgs s;
+    s.ucur = uni(pick(d, sc));
+    s.uprev = uni(pick(d, sp));
+    s.uout = uni(pick(d, so));
+    s.ref = uni(d.buf[0]);
+    s.vout = nullptr;
+    s.mask = uni(d.mask);
+    s.H = uni(d.H);
+    s.W = uni(d.W);
+    s.X0 = uni(t.ix) * sw;
+    s.Y0 = uni(t.iy) * oh;
+    s.tau = a.tau;
+    s.alpha = a.alpha;
+    s.il2q = 0.25f * __int_as_float(uni(__float_as_int(d.inv_lam2)));
+    s.model = a.model;
+    s.up = 0;
+    return s;
+}
+
 // Wave-strip shapes: wave w of the launch takes items w, w + nw, w + 2 nw, ...
 // (w counted in XCD-contiguous order).  GEN: tensor variant chosen at run time.
-template <int R, int ROWS, bool RES, int CPL, bool GEN>
+template <int R, int ROWS, bool RES, bool GEN>
 __device__ __forceinline__ void bstrip_body(const BImage *imgs, const BItem *queue,
                                             const int *qlen_p, int sc, int sp, int so,
                                             const StepArgs &a, double *partials)
 {
-    using G = StripGeo<R, ROWS, CPL>;
+    using G = StripGeo<R, ROWS>;
     __shared__ float lds[4 * G::LDS];
     const int wave = threadIdx.x >> 6;
     const int nw = 4 * gridDim.x;
@@ -80,32 +104,41 @@ __device__ __forceinline__ void bstrip_body(const BImage *imgs, const BItem *que
     for (int it = w0; it < qlen; it += nw) {
         const BItem t = queue[it];
         const BImage d = imgs[t.img];
-        StripArgs s;
-        s.ucur = uni(pick(d, sc));
-        s.uprev = uni(pick(d, sp));
-        s.uout = uni(pick(d, so));
-        s.ref = uni(d.buf[0]);
-        s.mask = uni(d.mask);
-        s.H = uni(d.H);
-        s.W = uni(d.W);
-        s.X0 = uni(t.ix) * G::SW;
-        s.Y0 = uni(t.iy) * G::OH;
-        s.tau = a.tau;
-        s.alpha = a.alpha;
-        s.il2q = 0.25f * __int_as_float(uni(__float_as_int(d.inv_lam2)));
-        s.model = a.model;
-        s.up = strip_alternates(ROWS) ? uni(t.iy) & 1 : 0;   // as in the single-image kernels
-        strip_step<R, RES, ROWS, CPL, GEN>(lds + wave * G::LDS, s, a.w,
-                                           partials + 2 * (size_t)uni(t.slot));
+        const StripArgs s = bstrip_item(d, t, sc, sp, so, G::SW, G::OH, a);
+        strip_step<R, RES, ROWS, GEN>(lds + wave * G::LDS, s, a.w,
+                                      partials + 2 * (size_t)uni(t.slot));
     }
 }
 
-template <int R, int ROWS, bool RES, int CPL>
+template <int R, int ROWS, bool RES>
 __global__ __launch_bounds__(256) void bstrip_kernel(const BImage *imgs, const BItem *queue,
                                                      const int *qlen_p, int sc, int sp, int so,
                                                      StepArgs a, double *partials)
 {
-    bstrip_body<R, ROWS, RES, CPL, false>(imgs, queue, qlen_p, sc, sp, so, a, partials);
+    bstrip_body<R, ROWS, RES, false>(imgs, queue, qlen_p, sc, sp, so, a, partials);
+}
+
+// 124-column strips of `rows` rows.
+template <int R, bool RES>
+__global__ __launch_bounds__(256) void bpair_kernel(const BImage *imgs, const BItem *queue,
+                                                           const int *qlen_p, int sc, int sp,
+                                                           int so, int rows, StepArgs a,
+                                                           double *partials)
+{
+    using G = PairGeo<R>;
+    __shared__ __attribute__((aligned(16))) float lds[4 * G::LDS];
+    const int wave = threadIdx.x >> 6;
+    const int nw = 4 * gridDim.x;
+    const int w0 = __builtin_amdgcn_readfirstlane(xcd_tile(blockIdx.x, gridDim.x) * 4 + wave);
+    const int qlen = *qlen_p;
+    for (int it = w0; it < qlen; it += nw) {
+        const BItem t = queue[it];
+        const BImage d = imgs[t.img];
+        StripArgs s = bstrip_item(d, t, sc, sp, so, G::SW, rows, a);
+        s.up = uni(t.iy) & 1;                    // as in the single-image kernel
+        pair_strip<R, RES, false>(lds + wave * G::LDS, s, a.w, rows,
+                                  partials + 2 * (size_t)uni(t.slot));
+    }
 }
 
 // The tensor variants (diffusivities of Table 7, mu3 choices of Sec. 3.1) on
@@ -115,7 +148,7 @@ __global__ __launch_bounds__(256) void bstrip_model_kernel(const BImage *imgs, c
                                                            const int *qlen_p, int sc, int sp,
                                                            int so, StepArgs a, double *partials)
 {
-    bstrip_body<R, 28, RES, 1, true>(imgs, queue, qlen_p, sc, sp, so, a, partials);
+    bstrip_body<R, 28, RES, true>(imgs, queue, qlen_p, sc, sp, so, a, partials);
 }
 
 // Workgroup-tile shapes: workgroup g takes tiles g, g + G, g + 2 G, ...
@@ -199,33 +232,43 @@ __global__ __launch_bounds__(256) void bhold_kernel(const BImage *imgs, int per)
 
 // ---------------------------------------------------------------- host side
 
-// item size of a shape in pixels
-static void item_dims(int shape, int R, int *iw, int *ih)
+// item size of a shape in pixels, for a batch of these images
+static void item_dims(int shape, int R, int B, const eed4_image *im, int *iw, int *ih)
 {
     if (is_strip(shape)) {
+        std::vector<int> H(B), W(B);
+        for (int i = 0; i < B; ++i) {
+            H[i] = im[i].H;
+            W[i] = im[i].W;
+        }
         *iw = strip_width(shape);
-        *ih = strip_rows(R, shape);
+        *ih = strip_rows(R, shape, B, H.data(), W.data(), 1);
         return;
     }
     *iw = tile_cols(kTileShapes[tile_index(shape)].tw);
     *ih = kTileShapes[tile_index(shape)].th;
 }
 
+static long long items_of(const eed4_image &im, int iw, int ih)
+{
+    return (long long)((im.W + iw - 1) / iw) * ((im.H + ih - 1) / ih);
+}
+
 template <int R>
 static hipError_t launch_bstep_r(int shape, int grid, const BImage *imgs, const BItem *queue,
-                                 const int *qlen, int sc, int sp, int so, bool res,
+                                 const int *qlen, int sc, int sp, int so, int ih, bool res,
                                  const StepArgs &a, double *partials, hipStream_t s)
 {
     dim3 g(grid), b(256);
 #define EED4_BTILE(TW, TH)                                                             \
     hipLaunchKernelGGL((btile_kernel<R, TW, TH>), g, b, 0, s, imgs, queue, qlen, sc, sp, so, \
                        res ? 1 : 0, a, partials)
-#define EED4_BSTRIP(ROWS, CPL)                                                           \
+#define EED4_BSTRIP(ROWS)                                                                \
     if (res)                                                                             \
-        hipLaunchKernelGGL((bstrip_kernel<R, ROWS, true, CPL>), g, b, 0, s, imgs, queue, \
+        hipLaunchKernelGGL((bstrip_kernel<R, ROWS, true>), g, b, 0, s, imgs, queue,      \
                            qlen, sc, sp, so, a, partials);                               \
     else                                                                                 \
-        hipLaunchKernelGGL((bstrip_kernel<R, ROWS, false, CPL>), g, b, 0, s, imgs, queue, \
+        hipLaunchKernelGGL((bstrip_kernel<R, ROWS, false>), g, b, 0, s, imgs, queue,     \
                            qlen, sc, sp, so, a, partials)
     if (a.model != 0) {              // tensor variants: one kernel shape
         if (shape != kShapeStripShort) return hipErrorInvalidValue;
@@ -241,12 +284,16 @@ static hipError_t launch_bstep_r(int shape, int grid, const BImage *imgs, const 
     case 0: EED4_BTILE(64, 32); break;
     case 1: EED4_BTILE(64, 16); break;
     case 2: EED4_BTILE(32, 32); break;
-    case kShapeStrip: EED4_BSTRIP(64, 1); break;
-    case kShapeStripTall: EED4_BSTRIP(136, 1); break;
-    case kShapeStripShort: EED4_BSTRIP(28, 1); break;
-    case kShapeStripTiny: EED4_BSTRIP(8, 1); break;
-    case kShapeStripWide: EED4_BSTRIP(64, 2); break;
-    case kShapeStripWideShort: EED4_BSTRIP(28, 2); break;
+    case kShapeStripShort: EED4_BSTRIP(28); break;
+    case kShapeStripTiny: EED4_BSTRIP(8); break;
+    case kShapeStrip: case kShapeStripTall: case kShapeStripWide: case kShapeStripWideShort:
+        if (res)
+            hipLaunchKernelGGL((bpair_kernel<R, true>), g, b, 0, s, imgs, queue, qlen, sc, sp, so,
+                               ih, a, partials);
+        else
+            hipLaunchKernelGGL((bpair_kernel<R, false>), g, b, 0, s, imgs, queue, qlen, sc, sp, so,
+                               ih, a, partials);
+        break;
     case kShapeTile32x16: EED4_BTILE(32, 16); break;
     case kShapeTile16x16: EED4_BTILE(16, 16); break;
     default: return hipErrorInvalidValue;
@@ -257,12 +304,12 @@ static hipError_t launch_bstep_r(int shape, int grid, const BImage *imgs, const 
 }
 
 static hipError_t launch_bstep(int R, int shape, int grid, const BImage *imgs, const BItem *queue,
-                               const int *qlen, int sc, int sp, int so, bool res,
+                               const int *qlen, int sc, int sp, int so, int ih, bool res,
                                const StepArgs &a, double *partials, hipStream_t s)
 {
     switch (R) {
 #define EED4_CASE(r) \
-    case r: return launch_bstep_r<r>(shape, grid, imgs, queue, qlen, sc, sp, so, res, a, partials, s);
+    case r: return launch_bstep_r<r>(shape, grid, imgs, queue, qlen, sc, sp, so, ih, res, a, partials, s);
         EED4_CASE(0) EED4_CASE(1) EED4_CASE(2) EED4_CASE(3) EED4_CASE(4)
         EED4_CASE(5) EED4_CASE(6) EED4_CASE(7) EED4_CASE(8)
 #undef EED4_CASE
@@ -279,8 +326,10 @@ static int max_items(int B, const eed4_image *im, int R)
 {
     int m = 0;
     for (int sh = 0; sh < kNumShapes; ++sh) {
+        int iw, ih;
+        item_dims(sh, R, B, im, &iw, &ih);
         long long t = 0;
-        for (int i = 0; i < B; ++i) t += tiles_per_image(sh, R, im[i].H, im[i].W);
+        for (int i = 0; i < B; ++i) t += items_of(im[i], iw, ih);
         if (t > m) m = (int)std::min<long long>(t, 0x7fffffff);
     }
     return m;
@@ -366,7 +415,7 @@ static int prepare(BatchRun &r, const eed4_image *im, int B, const eed4_params *
     r.n = p->cycle_len;
     r.B = B;
     r.p = p;
-    item_dims(shape, r.R, &r.iw, &r.ih);
+    item_dims(shape, r.R, B, im, &r.iw, &r.ih);
     r.himg.resize(B);
     r.slot0.resize(B);
     r.nslot.resize(B);
@@ -384,7 +433,7 @@ static int prepare(BatchRun &r, const eed4_image *im, int B, const eed4_params *
         d.nx = (im[i].W + r.iw - 1) / r.iw;
         r.himg[i] = d;
         r.slot0[i] = slot;
-        r.nslot[i] = tiles_per_image(shape, r.R, im[i].H, im[i].W);
+        r.nslot[i] = (int)items_of(im[i], r.iw, r.ih);
         slot += r.nslot[i];
     }
     r.dimg = (BImage *)(base + L.imgs);
@@ -431,7 +480,7 @@ static int enqueue_bcycle(const BatchRun &r, bool residual, hipStream_t s)
         roles(k, r.n, &sc, &sp, &so);
         StepArgs a = make_args(r.p->sigma, r.R, r.p->tau, 1.0f, k, model_of_flags(r.p->flags));
         e = launch_bstep(r.R, r.shape, r.grid, r.dimg, r.dqueue, r.dqlen, sc, sp,
-                         so, residual && k == r.n - 1, a, r.dpartials, s);
+                         so, r.ih, residual && k == r.n - 1, a, r.dpartials, s);
         if (e != hipSuccess) return hip_fail(e, "batched step launch");
     }
     if (r.n == 1) {
@@ -464,25 +513,29 @@ static std::string batch_tune_key(const eed4_image *im, int B, int R)
     return buf;
 }
 
-// Times one inner step (k = 0: S -> X, S unchanged) of every shape on the batch.
+// Times the inner steps of every shape on the batch (as tune_single_step: u^k = S,
+// unchanged, u^{k-1} = X, out X; the first of a graph S -> X).
 static int autotune(const eed4_image *im, int B, const eed4_params *p, char *base,
                     const BatchLayout &L, hipStream_t s, int *best_shape, float *best_ms)
 {
     int order[kNumShapes];
     tune_order(kShapeStrip, order);
     BatchRun r;
-    StepArgs a;
+    StepArgs a0, a1;
+    unsigned launched = 0;
     return tune_pick(
         order, kNumShapes, s,
         [&](int sh) {
             r = BatchRun();
             const int rc = prepare(r, im, B, p, sh, base, L, s);
-            a = make_args(p->sigma, r.R, p->tau, 1.0f, 0);
+            a0 = make_args(p->sigma, r.R, p->tau, 1.0f, 0);
+            a1 = make_args(p->sigma, r.R, p->tau, 1.0f, 1);
             return rc;
         },
         [&](int sh, hipStream_t q) {
-            return launch_bstep(r.R, sh, r.grid, r.dimg, r.dqueue, r.dqlen, 0, 0, 1, false, a,
-                                r.dpartials, q);
+            const bool head = launched++ % kTuneLaunches == 0;
+            return launch_bstep(r.R, sh, r.grid, r.dimg, r.dqueue, r.dqlen, 0, head ? 0 : 1, 1,
+                                r.ih, false, head ? a0 : a1, r.dpartials, q);
         },
         "autotune timing", best_shape, best_ms);
 }

@@ -3,6 +3,7 @@
 // deterministic FP64 reduction of the per-tile cycle residuals.
 #include "eed4_internal.h"
 #include "eed4_tile.h"
+#include "eed4_pair.h"
 #include "eed4_strip.h"
 
 namespace eed4 {
@@ -49,23 +50,12 @@ __global__ __launch_bounds__(256) void step_kernel(
         a.model, VST ? vout + off : nullptr);
 }
 
-// Fused step over wave strips.  GEN selects the tensor variant at run time
-// (StepArgs::model); without it the kernel is the FOEED tensor.  VST also
-// writes the presmoothed image K_sigma * u^k (into vout).
-template <int R, bool RES, int ROWS, int CPL, bool GEN, bool VST = false>
-__device__ __forceinline__ void strip_kernel_body(const float *ucur, const float *uprev,
-                                                  float *uout, const float *ref,
-                                                  const uint8_t *__restrict__ mask, int H, int W,
-                                                  int nstrip, int per_img, int nitems,
-                                                  const StepArgs &a, double *partials,
-                                                  float *vout = nullptr)
+// The strip of a work item in the grid of strips and segments, as StripArgs.
+__device__ __forceinline__ StripArgs strip_item(const float *ucur, const float *uprev, float *uout,
+                                                const float *ref, float *vout, const uint8_t *mask,
+                                                int H, int W, int nstrip, int per_img, int item,
+                                                int sw, int oh, const StepArgs &a, int *seg_out)
 {
-    using G = StripGeo<R, ROWS, CPL>;
-    __shared__ float lds[4 * G::LDS];
-    const int wave = threadIdx.x >> 6;
-    // wave-uniform: keep the work item (and all that derives from it) in SGPRs
-    const int item = __builtin_amdgcn_readfirstlane(xcd_tile(blockIdx.x, gridDim.x) * 4 + wave);
-    if (item >= nitems) return;  // whole wave; the kernel has no workgroup barrier
     const int b = item / per_img;
     const int r = item - b * per_img;
     const int seg = r / nstrip, strip = r - seg * nstrip;
@@ -74,31 +64,77 @@ __device__ __forceinline__ void strip_kernel_body(const float *ucur, const float
     s.ucur = ucur + off;
     s.uprev = uprev + off;
     s.uout = uout + off;
-    s.ref = RES ? ref + off : nullptr;
-    s.vout = VST ? vout + off : nullptr;
+    s.ref = ref ? ref + off : nullptr;
+    s.vout = vout ? vout + off : nullptr;
     s.mask = mask + off;
     s.H = H;
     s.W = W;
-    s.X0 = strip * G::SW;
-    s.Y0 = seg * G::OH;
+    s.X0 = strip * sw;
+    s.Y0 = seg * oh;
     s.tau = a.tau;
     s.alpha = a.alpha;
     s.il2q = 0.25f * a.inv_lam2;
     s.model = a.model;
-    s.up = strip_alternates(ROWS) ? seg & 1 : 0;
-    strip_step<R, RES, ROWS, CPL, GEN, VST>(lds + wave * G::LDS, s, a.w,
-                                            RES ? partials + 2 * (size_t)item : nullptr);
+    s.up = 0;
+    *seg_out = seg;
+    return s;
 }
 
-template <int R, bool RES, int ROWS, int CPL>
+// Fused step over 60-column wave strips.  GEN selects the tensor variant at run
+// time (StepArgs::model); without it the kernel is the FOEED tensor.  VST also
+// writes the presmoothed image K_sigma * u^k (into vout).
+template <int R, bool RES, int ROWS, bool GEN, bool VST = false>
+__device__ __forceinline__ void strip_kernel_body(const float *ucur, const float *uprev,
+                                                  float *uout, const float *ref,
+                                                  const uint8_t *__restrict__ mask, int H, int W,
+                                                  int nstrip, int per_img, int nitems,
+                                                  const StepArgs &a, double *partials,
+                                                  float *vout = nullptr)
+{
+    using G = StripGeo<R, ROWS>;
+    __shared__ float lds[4 * G::LDS];
+    const int wave = threadIdx.x >> 6;
+    // wave-uniform: keep the work item (and all that derives from it) in SGPRs
+    const int item = __builtin_amdgcn_readfirstlane(xcd_tile(blockIdx.x, gridDim.x) * 4 + wave);
+    if (item >= nitems) return;  // whole wave; the kernel has no workgroup barrier
+    int seg;
+    const StripArgs s = strip_item(ucur, uprev, uout, RES ? ref : nullptr, VST ? vout : nullptr,
+                                   mask, H, W, nstrip, per_img, item, G::SW, G::OH, a, &seg);
+    strip_step<R, RES, ROWS, GEN, VST>(lds + wave * G::LDS, s, a.w,
+                                       RES ? partials + 2 * (size_t)item : nullptr);
+}
+
+template <int R, bool RES, int ROWS>
 __global__ __launch_bounds__(256) void strip_kernel(const float *ucur, const float *uprev,
                                                     float *uout, const float *ref,
                                                     const uint8_t *__restrict__ mask, int H, int W,
                                                     int nstrip, int per_img, int nitems, StepArgs a,
                                                     double *partials)
 {
-    strip_kernel_body<R, RES, ROWS, CPL, false>(ucur, uprev, uout, ref, mask, H, W, nstrip,
-                                                per_img, nitems, a, partials);
+    strip_kernel_body<R, RES, ROWS, false>(ucur, uprev, uout, ref, mask, H, W, nstrip, per_img,
+                                           nitems, a, partials);
+}
+
+// Fused step over 124-column wave strips of `rows` rows (also VST: the step of
+// the adjoint's recompute that keeps K_sigma * u^k).
+template <int R, bool RES, bool VST>
+__global__ __launch_bounds__(256) void pair_kernel(const float *ucur, const float *uprev,
+                                                   float *uout, const float *ref, float *vout,
+                                                   const uint8_t *__restrict__ mask, int H, int W,
+                                                   int nstrip, int per_img, int nitems, int rows,
+                                                   StepArgs a, double *partials)
+{
+    using G = PairGeo<R>;
+    __shared__ __attribute__((aligned(16))) float lds[4 * G::LDS];
+    const int wave = threadIdx.x >> 6;
+    const int item = __builtin_amdgcn_readfirstlane(xcd_tile(blockIdx.x, gridDim.x) * 4 + wave);
+    if (item >= nitems) return;
+    int seg;
+    StripArgs s = strip_item(ucur, uprev, uout, RES ? ref : nullptr, VST ? vout : nullptr, mask, H,
+                             W, nstrip, per_img, item, G::SW, rows, a, &seg);
+    s.up = seg & 1;
+    pair_strip<R, RES, VST>(lds + wave * G::LDS, s, a.w, rows,
+                            RES ? partials + 2 * (size_t)item : nullptr);
 }
 
 // The tensor variants (diffusivities of Table 7, mu3 choices of Sec. 3.1) on
@@ -110,22 +146,22 @@ __global__ __launch_bounds__(256) void strip_model_kernel(const float *ucur, con
                                                           int W, int nstrip, int per_img,
                                                           int nitems, StepArgs a, double *partials)
 {
-    strip_kernel_body<R, RES, 28, 1, true>(ucur, uprev, uout, ref, mask, H, W, nstrip, per_img,
-                                           nitems, a, partials);
+    strip_kernel_body<R, RES, 28, true>(ucur, uprev, uout, ref, mask, H, W, nstrip, per_img,
+                                        nitems, a, partials);
 }
 
 // The step of the adjoint's forward recompute: u^{k+1} as strip_kernel (or
 // strip_model_kernel when GEN) computes it, and K_sigma * u^k for the reverse
 // step.
-template <int R, int ROWS, bool GEN>
+template <int R, bool GEN>
 __global__ __launch_bounds__(256) void strip_keepv_kernel(const float *ucur, const float *uprev,
                                                           float *uout, float *vout,
                                                           const uint8_t *__restrict__ mask, int H,
                                                           int W, int nstrip, int per_img,
                                                           int nitems, StepArgs a)
 {
-    strip_kernel_body<R, false, ROWS, 1, GEN, true>(ucur, uprev, uout, nullptr, mask, H, W, nstrip,
-                                                    per_img, nitems, a, nullptr, vout);
+    strip_kernel_body<R, false, 28, GEN, true>(ucur, uprev, uout, nullptr, mask, H, W, nstrip,
+                                               per_img, nitems, a, nullptr, vout);
 }
 
 // v = K_sigma * u on the mirror-extended image (the presmoothing of Sec. 2.2)
@@ -211,23 +247,52 @@ hipError_t launch_hold(float *u, const uint8_t *mask, const float *known, size_t
     return hipGetLastError();
 }
 
-template <int R>
-static int strip_oh(int shape)
+// Segment height of the default 124-column strips in a launch of `waves(rows)`
+// waves.  A wave's time is proportional to the rows it streams (the outputs,
+// four more, and the prologue, of which a row costs about half) and, per row,
+// measured on full launches of 1, 2, 3 and 4 waves a SIMD (4096^2 and 2900^2,
+// R = 5 and 6): 0.475, 0.6, 0.8 and 1.03 us.  Three waves fit a SIMD's
+// registers from R = 6 on, four below.  So a launch that leaves a few waves for
+// another round on the SIMDs costs a whole round: 4096^2 at R = 6 takes 47.9 us
+// with 48 rows (2924 waves for 3072 places), 52.3 us with 36 (3876), 54.6 with
+// 64 (2176).
+template <typename Waves>
+static int fit_strip_rows(int R, Waves &&waves)
 {
-    switch (shape) {
-    case kShapeStripTall: return StripGeo<R, 136>::OH;
-    case kShapeStripShort: return StripGeo<R, 28>::OH;
-    case kShapeStripTiny: return StripGeo<R, 8>::OH;
-    case kShapeStripWideShort: return StripGeo<R, 28, 2>::OH;
-    case kShapeStripWide: return StripGeo<R, 64, 2>::OH;
-    default: return StripGeo<R, 64>::OH;
+    constexpr double kRowTime[5] = {0.0, 0.475, 0.6, 0.8, 1.03};
+    constexpr long long kSimds = 1024;
+    const long long fit = R <= 5 ? 4 : 3;
+    int best = 0;
+    double best_cost = 0.0;
+    for (int rows = 28; rows <= 136; rows += 4) {
+        const long long n = (waves(rows) + kSimds - 1) / kSimds;      // waves per SIMD
+        const double cost = ((double)(n / fit) * kRowTime[fit] + kRowTime[n % fit]) * (rows + R + 6);
+        if (best == 0 || cost < best_cost) {
+            best = rows;
+            best_cost = cost;
+        }
     }
+    return best;
 }
 
-int strip_rows(int R, int shape)
+int strip_rows(int R, int shape, int B, const int *H, const int *W, int copies)
 {
+    switch (shape) {
+    case kShapeStripTall: return 136;
+    case kShapeStripWide: return 64;
+    case kShapeStripWideShort: return 28;
+    case kShapeStrip:
+        return fit_strip_rows(R, [&](int rows) {
+            long long n = 0;
+            for (int i = 0; i < B; ++i)
+                n += (long long)((W[i] + 123) / 124) * ((H[i] + rows - 1) / rows);
+            return n * copies;
+        });
+    default: break;
+    }
     switch (R) {
-#define EED4_CASE(r) case r: return strip_oh<r>(shape);
+#define EED4_CASE(r) \
+    case r: return shape == kShapeStripShort ? StripGeo<r, 28>::OH : StripGeo<r, 8>::OH;
         EED4_CASE(0) EED4_CASE(1) EED4_CASE(2) EED4_CASE(3) EED4_CASE(4)
         EED4_CASE(5) EED4_CASE(6) EED4_CASE(7) EED4_CASE(8)
 #undef EED4_CASE
@@ -235,10 +300,10 @@ int strip_rows(int R, int shape)
     }
 }
 
-int tiles_per_image(int shape, int R, int H, int W)
+int tiles_per_image(int shape, int R, int B, int H, int W)
 {
     if (is_strip(shape)) {
-        const int oh = strip_rows(R, shape), sw = strip_width(shape);
+        const int oh = strip_rows(R, shape, 1, &H, &W, B), sw = strip_width(shape);
         if (oh <= 0) return 0;
         return ((W + sw - 1) / sw) * ((H + oh - 1) / oh);
     }
@@ -255,23 +320,23 @@ int tiles_per_image(int shape, int R, int H, int W)
 // 28-row strips 20.6 us).
 int variant_shape(int R, int B, int H, int W)
 {
-    const long long waves = (long long)tiles_per_image(kShapeStripShort, R, H, W) * B;
+    const long long waves = (long long)tiles_per_image(kShapeStripShort, R, B, H, W) * B;
     if (waves >= 3072) return kShapeStripShort;
-    return (long long)tiles_per_image(0, R, H, W) * B >= 1024 ? 0 : 1;
+    return (long long)tiles_per_image(0, R, B, H, W) * B >= 1024 ? 0 : 1;
 }
 
-template <int R, int ROWS, int CPL = 1, bool GEN = false>
+template <int R, int ROWS, bool GEN = false>
 static hipError_t launch_strip_t(const float *ucur, const float *uprev, float *uout,
                                  const float *ref, const uint8_t *mask, int B, int H, int W,
                                  const StepArgs &a, double *partials, hipStream_t s)
 {
-    using G = StripGeo<R, ROWS, CPL>;
+    using G = StripGeo<R, ROWS>;
     const int nstrip = (W + G::SW - 1) / G::SW;
     const int per_img = nstrip * ((H + G::OH - 1) / G::OH);
     const long long nitems = (long long)per_img * B;
     const long long nblk = (nitems + 3) / 4;
     if (nitems <= 0 || nblk > 0x7fffffffLL) return hipErrorInvalidValue;
-    static_assert(!GEN || (ROWS == 28 && CPL == 1), "tensor variants run 28-row strips");
+    static_assert(!GEN || ROWS == 28, "tensor variants run 28-row strips");
     if constexpr (GEN) {
         if (ref)
             hipLaunchKernelGGL((strip_model_kernel<R, true>), dim3((unsigned)nblk), dim3(256), 0, s,
@@ -282,29 +347,54 @@ static hipError_t launch_strip_t(const float *ucur, const float *uprev, float *u
                                ucur, uprev, uout, ref, mask, H, W, nstrip, per_img, (int)nitems, a,
                                partials);
     } else if (ref) {
-        hipLaunchKernelGGL((strip_kernel<R, true, ROWS, CPL>), dim3((unsigned)nblk), dim3(256), 0, s,
+        hipLaunchKernelGGL((strip_kernel<R, true, ROWS>), dim3((unsigned)nblk), dim3(256), 0, s,
                            ucur, uprev, uout, ref, mask, H, W, nstrip, per_img, (int)nitems, a,
                            partials);
     } else {
-        hipLaunchKernelGGL((strip_kernel<R, false, ROWS, CPL>), dim3((unsigned)nblk), dim3(256), 0, s,
+        hipLaunchKernelGGL((strip_kernel<R, false, ROWS>), dim3((unsigned)nblk), dim3(256), 0, s,
                            ucur, uprev, uout, ref, mask, H, W, nstrip, per_img, (int)nitems, a,
                            partials);
     }
     return hipGetLastError();
 }
 
-template <int R, int ROWS, bool GEN>
+// A pair shape; with vout the recompute step that keeps K_sigma * u^k.
+template <int R>
+static hipError_t launch_pair_r(int shape, const float *ucur, const float *uprev, float *uout,
+                                const float *ref, float *vout, const uint8_t *mask, int B, int H,
+                                int W, const StepArgs &a, double *partials, hipStream_t s)
+{
+    const int rows = strip_rows(R, shape, 1, &H, &W, B);
+    const int nstrip = (W + PairGeo<R>::SW - 1) / PairGeo<R>::SW;
+    const int per_img = nstrip * ((H + rows - 1) / rows);
+    const long long nitems = (long long)per_img * B;
+    const long long nblk = (nitems + 3) / 4;
+    if (nitems <= 0 || nblk > 0x7fffffffLL) return hipErrorInvalidValue;
+    const dim3 g((unsigned)nblk), b(256);
+    if (vout)
+        hipLaunchKernelGGL((pair_kernel<R, false, true>), g, b, 0, s, ucur, uprev, uout, nullptr,
+                           vout, mask, H, W, nstrip, per_img, (int)nitems, rows, a, nullptr);
+    else if (ref)
+        hipLaunchKernelGGL((pair_kernel<R, true, false>), g, b, 0, s, ucur, uprev, uout, ref,
+                           nullptr, mask, H, W, nstrip, per_img, (int)nitems, rows, a, partials);
+    else
+        hipLaunchKernelGGL((pair_kernel<R, false, false>), g, b, 0, s, ucur, uprev, uout, nullptr,
+                           nullptr, mask, H, W, nstrip, per_img, (int)nitems, rows, a, nullptr);
+    return hipGetLastError();
+}
+
+template <int R, bool GEN>
 static hipError_t launch_keepv_t(const float *ucur, const float *uprev, float *uout, float *vout,
                                  const uint8_t *mask, int B, int H, int W, const StepArgs &a,
                                  hipStream_t s)
 {
-    using G = StripGeo<R, ROWS, 1>;
+    using G = StripGeo<R, 28>;
     const int nstrip = (W + G::SW - 1) / G::SW;
     const int per_img = nstrip * ((H + G::OH - 1) / G::OH);
     const long long nitems = (long long)per_img * B;
     const long long nblk = (nitems + 3) / 4;
     if (nitems <= 0 || nblk > 0x7fffffffLL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((strip_keepv_kernel<R, ROWS, GEN>), dim3((unsigned)nblk), dim3(256), 0, s,
+    hipLaunchKernelGGL((strip_keepv_kernel<R, GEN>), dim3((unsigned)nblk), dim3(256), 0, s,
                        ucur, uprev, uout, vout, mask, H, W, nstrip, per_img, (int)nitems, a);
     return hipGetLastError();
 }
@@ -364,7 +454,7 @@ static hipError_t launch_step_r(int shape, const float *ucur, const float *uprev
         switch (shape) {
         case 0: return launch_step_t<R, 64, 32, true>(ucur, uprev, uout, ref, mask, B, H, W, a, partials, s);
         case 1: return launch_step_t<R, 64, 16, true>(ucur, uprev, uout, ref, mask, B, H, W, a, partials, s);
-        case kShapeStripShort: return launch_strip_t<R, 28, 1, true>(ucur, uprev, uout, ref, mask, B, H, W, a, partials, s);
+        case kShapeStripShort: return launch_strip_t<R, 28, true>(ucur, uprev, uout, ref, mask, B, H, W, a, partials, s);
         default: return hipErrorInvalidValue;
         }
     }
@@ -372,20 +462,18 @@ static hipError_t launch_step_r(int shape, const float *ucur, const float *uprev
     case 0: return launch_step_t<R, 64, 32>(ucur, uprev, uout, ref, mask, B, H, W, a, partials, s);
     case 1: return launch_step_t<R, 64, 16>(ucur, uprev, uout, ref, mask, B, H, W, a, partials, s);
     case 2: return launch_step_t<R, 32, 32>(ucur, uprev, uout, ref, mask, B, H, W, a, partials, s);
-    case kShapeStrip: return launch_strip_t<R, 64>(ucur, uprev, uout, ref, mask, B, H, W, a, partials, s);
-    case kShapeStripTall: return launch_strip_t<R, 136>(ucur, uprev, uout, ref, mask, B, H, W, a, partials, s);
     case kShapeStripShort: return launch_strip_t<R, 28>(ucur, uprev, uout, ref, mask, B, H, W, a, partials, s);
     case kShapeStripTiny: return launch_strip_t<R, 8>(ucur, uprev, uout, ref, mask, B, H, W, a, partials, s);
-    case kShapeStripWide: return launch_strip_t<R, 64, 2>(ucur, uprev, uout, ref, mask, B, H, W, a, partials, s);
-    case kShapeStripWideShort: return launch_strip_t<R, 28, 2>(ucur, uprev, uout, ref, mask, B, H, W, a, partials, s);
+    case kShapeStrip: case kShapeStripTall: case kShapeStripWide: case kShapeStripWideShort:
+        return launch_pair_r<R>(shape, ucur, uprev, uout, ref, nullptr, mask, B, H, W, a, partials, s);
     case kShapeTile32x16: return launch_step_t<R, 32, 16>(ucur, uprev, uout, ref, mask, B, H, W, a, partials, s);
     case kShapeTile16x16: return launch_step_t<R, 16, 16>(ucur, uprev, uout, ref, mask, B, H, W, a, partials, s);
     default: return hipErrorInvalidValue;
     }
 }
 
-// The keep-v step of a forward step shape: a strip shape keeps its height (wide
-// shapes map to their height), a tile shape runs the tile of its width class.
+// The keep-v step of a forward step shape: a strip shape keeps its own (8-row
+// strips aside), a tile shape runs the tile of its width class.
 template <int R, bool GEN>
 static hipError_t launch_keepv_r(int shape, const float *ucur, const float *uprev, float *uout,
                                  float *vout, const uint8_t *mask, int B, int H, int W,
@@ -393,10 +481,12 @@ static hipError_t launch_keepv_r(int shape, const float *ucur, const float *upre
 {
     switch (shape) {
     case 0: return launch_keepv_tile<R, 64, 32, GEN>(ucur, uprev, uout, vout, mask, B, H, W, a, s);
-    case kShapeStripShort: case kShapeStripWideShort:
-        return launch_keepv_t<R, 28, GEN>(ucur, uprev, uout, vout, mask, B, H, W, a, s);
-    case kShapeStrip: case kShapeStripTall: case kShapeStripWide:
-        if constexpr (!GEN) return launch_keepv_t<R, 64, false>(ucur, uprev, uout, vout, mask, B, H, W, a, s);
+    case kShapeStripShort:
+        return launch_keepv_t<R, GEN>(ucur, uprev, uout, vout, mask, B, H, W, a, s);
+    case kShapeStrip: case kShapeStripTall: case kShapeStripWide: case kShapeStripWideShort:
+        if constexpr (!GEN)
+            return launch_pair_r<R>(shape, ucur, uprev, uout, nullptr, vout, mask, B, H, W, a,
+                                    nullptr, s);
         return hipErrorInvalidValue;
     default: return launch_keepv_tile<R, 64, 16, GEN>(ucur, uprev, uout, vout, mask, B, H, W, a, s);
     }

@@ -60,10 +60,12 @@ int check_ws(void *ws, size_t ws_bytes, size_t need);
 int step_shape(const eed4_params *p, int B, int H, int W);
 int run_shape(const eed4_params *p, int B, int H, int W);
 
-// Without a tuned choice, the single-image path uses workgroup tiles when
-// the default strips would give fewer waves than this (too few to fill the
-// chip), and strips otherwise.
-constexpr long long kMinStripWaves = 2048;
+// Without a tuned choice, the single-image path uses workgroup tiles when the
+// problem has fewer 60 x 64 blocks than this, and strips otherwise.  Measured,
+// 60 x 32 tiles against the strips: 2048^2 (1155 blocks) 17.6 against 21.5 us at
+// R = 3, 23.0 against 28.4 at R = 8; 2560^2 (1720) 24.5 against 21.9 and 31.1
+// against 30.4; 4096^2 55.5 against 43.6 and 68.8 against 55.2.
+constexpr long long kMinStripBlocks = 1700;
 
 // The autotuners keep the default shape unless another is faster by more than
 // this factor, so shapes within timing noise of each other do not swap between
@@ -81,7 +83,8 @@ inline void tune_order(int first, int (&order)[kNumShapes])
 // Candidates of the single-image tuner, `first` (the size rule's default)
 // first; returns their count.  Where the default is a strip (enough work for
 // the strips to fill the chip) only the 64 x 32 tile of the tiles is timed: it
-// is level with the strips at about 9 million pixels and 15 % slower at 4096^2.
+// is level with the strips at about 7 million pixels (613x12000, R = 6: 30.5 us
+// against 29.8) and 27 % slower at 4096^2.
 // Where the default is a tile the 28- and 8-row strips are the strips that can
 // compete.
 inline int tune_candidates(int first, int (&order)[kNumShapes])
@@ -100,13 +103,11 @@ inline int tune_candidates(int first, int (&order)[kNumShapes])
 int default_step_shape(int R, int B, int H, int W);
 
 // Margin a candidate of the single-image tuner must beat the current choice
-// by.  Where the default is the 64-row strip (images large enough for it),
-// the 28-row strips, which fetch the halo rows their neighbours share again
-// (1.20x the algorithmic bytes against 1.006x for the 64-row strips, whose
-// segments alternate direction), have to be clearly faster: in sustained
-// runs at 4096^2 they are level with the 64-row strip or a few percent
-// slower, and slower once the image leaves the Infinity Cache, while a short
-// tuning burst has at times put them 2 % ahead.
+// by.  Where the default is a strip (images large enough for it), the 28-row
+// strips, which fetch more of the halo rows their neighbours share again, have
+// to be clearly faster: in sustained runs they are at best level with the
+// default (8 x 1037x771 at R = 3: 25.9 against 25.8 us; 2560^2 24.9 and 22.9),
+// while a short tuning burst has at times put them a few percent ahead.
 constexpr float kTuneMarginRefetch = 0.95f;
 inline float tune_margin(int first, int shape)
 {

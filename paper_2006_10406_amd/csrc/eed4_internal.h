@@ -62,32 +62,29 @@ constexpr int tile_cols(int tw) { return tw - 4; }
 
 // Kernel shapes compiled into the library (index = config id): 0..2 and
 // 9..10 are workgroup tiles (tw - 4 columns x th rows per 256 threads);
-// 3..8 are wave strips (60 or 124 columns x a segment of rows per wave).  The
+// 3..8 are wave strips: 3, 4, 7 and 8 of 124 columns (eed4_pair.h), 5 and 6 of
+// 60 (eed4_strip.h), by a segment of rows per wave.  The
 // small tiles (9, 10) give images of a few hundred pixels a side more
 // workgroups than the chip has CUs.
 constexpr int kNumTileShapes = 5;
 constexpr TileShape kTileShapes[kNumTileShapes] = {{64, 32}, {64, 16}, {32, 32}, {32, 16}, {16, 16}};
-constexpr int kShapeStrip = 3;       // wave strips of >= 64 output rows
-constexpr int kShapeStripTall = 4;   // >= 136 rows
-constexpr int kShapeStripShort = 5;  // >= 28 rows (more waves for small images)
-constexpr int kShapeStripTiny = 6;   // >= 8 rows (shortest row pipeline per wave)
-constexpr int kShapeStripWide = 7;       // two columns per lane (124 per wave), >= 64 rows
-constexpr int kShapeStripWideShort = 8;  // two columns per lane, >= 28 rows
+constexpr int kShapeStrip = 3;           // segment height by fit_strip_rows
+constexpr int kShapeStripTall = 4;       // 136 rows
+constexpr int kShapeStripShort = 5;      // >= 28 rows (more waves for small images)
+constexpr int kShapeStripTiny = 6;       // >= 8 rows (shortest row pipeline per wave)
+constexpr int kShapeStripWide = 7;       // 64 rows
+constexpr int kShapeStripWideShort = 8;  // 28 rows
 constexpr int kShapeTile32x16 = 9;
 constexpr int kShapeTile16x16 = 10;
 constexpr int kNumShapes = 11;
 constexpr bool is_strip(int shape) { return shape >= kShapeStrip && shape <= kShapeStripWideShort; }
 // index into kTileShapes of a tile shape
 constexpr int tile_index(int shape) { return shape < kShapeStrip ? shape : shape - 6; }
-constexpr int strip_target_rows(int shape)
+constexpr bool is_pair(int shape)
 {
-    return shape == kShapeStripTall ? 136
-         : shape == kShapeStripShort || shape == kShapeStripWideShort ? 28
-         : shape == kShapeStripTiny  ? 8
-                                     : 64;
+    return is_strip(shape) && shape != kShapeStripShort && shape != kShapeStripTiny;
 }
-constexpr int strip_cols_per_lane(int shape) { return shape >= kShapeStripWide ? 2 : 1; }
-constexpr int strip_width(int shape) { return 64 * strip_cols_per_lane(shape) - 4; }
+constexpr int strip_width(int shape) { return is_pair(shape) ? 124 : 60; }
 
 // ---- launchers (eed4_forward.hip) ----
 hipError_t launch_hold(float *u, const uint8_t *mask, const float *known, size_t n,
@@ -105,8 +102,11 @@ hipError_t launch_blur(int R, const float *u, float *v, int B, int H, int W, con
                        hipStream_t s);
 hipError_t launch_reduce(const double *partials, int tiles_per_img, int B, double *sums,
                          hipStream_t s);
-int tiles_per_image(int shape, int R, int H, int W);  // residual partials per image
+// residual partials per image of a launch over B images of H x W
+int tiles_per_image(int shape, int R, int B, int H, int W);
 int variant_shape(int R, int B, int H, int W);        // kernel shape of a tensor variant
-int strip_rows(int R, int shape);                      // output rows per strip segment
+// output rows per strip segment in a launch over B images of the sizes
+// (H[i], W[i]) with `copies` copies of each
+int strip_rows(int R, int shape, int B, const int *H, const int *W, int copies);
 
 }  // namespace eed4

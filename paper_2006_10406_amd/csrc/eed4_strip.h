@@ -1,10 +1,10 @@
 // Device code of one fused FOEED/FSI inner step on a vertical strip, one
-// wavefront per strip, no workgroup barriers.
+// wavefront per strip, no workgroup barriers (the short segments and the tensor
+// variants; eed4_pair.h has the tall ones).
 //
-// A wave owns NL = 64 CPL consecutive columns c = X0-2 .. X0+NL-3 (CPL
-// adjacent columns per lane) and streams down the rows of a segment.  For
-// each input row y it
-//   S1  stages u^k(y, X0-2-R .. X0+NL-3+R) in a per-wave LDS ring (mirrored
+// A wave owns 64 consecutive columns c = X0-2 .. X0+61, one per lane, and
+// streams down the rows of a segment.  For each input row y it
+//   S1  stages u^k(y, X0-2-R .. X0+61+R) in a per-wave LDS ring (mirrored
 //       indices realise the Neumann condition, Sec. 2.1) and takes the x pass
 //       of the Gaussian presmoothing (Sec. 2.2) at its columns;
 //   S2  completes the y pass at row y-R from a register window of the last
@@ -17,10 +17,9 @@
 //       FSI extrapolation (Sec. 3.3), Dirichlet hold; optional FP64 residual;
 //       optionally also the presmoothed image v = K_sigma * u^k at row o (the
 //       adjoint's recompute keeps it for the reverse step).
-// Horizontal neighbours inside a lane are its own registers; across lanes
-// they come from DPP wave shifts.  Outputs are the NL-4 columns X0 ..
-// X0+NL-5.  Every intermediate lives on the mirror-extended image, so P stays
-// symmetric, and each pixel's arithmetic is the same for every CPL.
+// Horizontal neighbours across lanes come from DPP wave shifts.  Outputs are
+// the 60 columns X0 .. X0+59.  Every intermediate lives on the mirror-extended
+// image, so P stays symmetric.
 #pragma once
 
 #include "eed4_internal.h"
@@ -72,15 +71,14 @@ __device__ __forceinline__ void wave_lds_sync()
 // neighbours) as compile-time offsets from its own column, which stay within
 // the reach of paired LDS reads, and the odd stride CS keeps the 64 lanes on
 // distinct banks.
-template <int R, int ROWS = 64, int CPL = 1>
+template <int R, int ROWS>
 struct StripGeo {
     static constexpr int P = 2 * R + 1;                       // y window length
     static constexpr int U = P * ((R + 3 + P - 1) / P);       // unroll = LDS ring depth
     static constexpr int D = U;                               // (a multiple of P, >= R+3)
     static constexpr int h = R + 2;                           // input halo
-    static constexpr int NL = 64 * CPL;                       // columns held by the lanes
-    static constexpr int SW = NL - 4;                         // output columns per wave
-    static constexpr int NU = NL + 2 * R;                     // staged u columns per row
+    static constexpr int SW = 60;                             // output columns per wave
+    static constexpr int NU = 64 + 2 * R;                     // staged u columns per row
     static constexpr int CS = D | 1;                          // ring column stride (odd)
     static constexpr int M = (ROWS + 4 + U - 1) / U;          // main-loop iterations
     static constexpr int NROW = 2 * R + M * U;                // rows streamed per wave
@@ -98,7 +96,7 @@ struct StripArgs {
     int H, W, X0, Y0;
     float tau, alpha, il2q;     // il2q = 1 / (4 lambda^2)
     int model;                  // tensor variant (GEN kernels only)
-    int up;                     // stream the segment bottom up (see strip_step)
+    int up;                     // stream the segment bottom up (eed4_pair.h only)
 };
 
 // mu1 = g(x) and mu3 of the tensor variants, x = (s/lambda)^2: the
@@ -237,62 +235,33 @@ struct RowTrack {
     }
 };
 
-// Global loads of one stream row: u^k of the row itself (the lane's columns
-// and one right-halo column), and u^{k-1}, the mask and the residual
-// reference of the output row it serves.
-template <int CPL>
+// Global loads of one stream row: u^k of the row itself (the lane's column and
+// one right-halo column), and u^{k-1}, the mask and the residual reference of
+// the output row it serves.
 struct StripRow {
-    float a[CPL], b, pv[CPL], rf[CPL];
-    unsigned mk[CPL];
+    float a, b, pv, rf;
+    unsigned mk;
 };
-
-// Column q's left / right neighbour of a per-column register quantity.
-template <int CPL>
-__device__ __forceinline__ float left_of(const float (&x)[CPL], int q)
-{
-    return q > 0 ? x[q - 1] : from_prev_lane(x[CPL - 1]);
-}
-template <int CPL>
-__device__ __forceinline__ float right_of(const float (&x)[CPL], int q)
-{
-    return q < CPL - 1 ? x[q + 1] : from_next_lane(x[0]);
-}
 
 // Addressing: every plane is seen through a buffer resource based at image
 // row b0 = max(Y0 - h, 0) (the lowest row a needed value comes from) and
 // covering nb = min(H - b0, NROW) rows, so a row offset is one 32-bit scalar
 // (the library keeps NROW * W * 4 below 2^31) and the per-lane column offsets
 // stay fixed for the whole strip.
-//
-// Direction: with segments of >= 64 rows, callers stream odd segments bottom
-// up and even ones top down, so the 2h rows two neighbouring segments share
-// are read by both at nearly the same time (near the end of both streams, or
-// near the start of both) and the second read usually hits in L2; with every
-// segment streaming down, one reads them first and the other last, a whole
-// launch later.  (Measured at 4096^2 and 8192^2: the 64-row strips as fast in
-// the cache-resident case and 5 % faster out of it; 28-row strips 8 % slower,
-// so they all stream down.)  The stencils are symmetric in y: streaming up
-// only negates the y-odd quantities (G_y, u_xy, T_xy and its x differences)
-// exactly, and the y pass is symmetric, so u^{k+1} (and the kept v) are
-// bitwise those of the downward stream; only the FP64 residual partials add
-// the rows in the other order.
-constexpr bool strip_alternates(int rows) { return rows >= 64; }
 
-template <int R, bool RES, int ROWS = 64, int CPL = 1, bool GEN = false, bool VST = false>
+template <int R, bool RES, int ROWS, bool GEN = false, bool VST = false>
 __device__ __forceinline__ void strip_step(float *ring, const StripArgs &s,
                                            const float (&w)[2 * kRMax + 1], double *partial)
 {
-    using G = StripGeo<R, ROWS, CPL>;
-    constexpr int P = G::P, U = G::U, D = G::D, NL = G::NL, CS = G::CS;
+    using G = StripGeo<R, ROWS>;
+    constexpr int P = G::P, U = G::U, D = G::D, CS = G::CS;
     const int lane = threadIdx.x & 63;
     const int H = s.H, W = s.W;
     const unsigned W4 = 4u * (unsigned)W;
     if constexpr (kLdsSentinel) sentinel_fill_wave(ring, G::LDS);
 
-    const int ybase = s.Y0 - G::h;                            // top streamed row
-    const int dir = s.up ? -1 : 1;                            // image rows per stream row
-    const int ystart = s.up ? ybase + G::NROW - 1 : ybase;    // image row of stream row 0
-    const int b0 = ybase > 0 ? ybase : 0;
+    const int ystart = s.Y0 - G::h;                           // image row of stream row 0
+    const int b0 = ystart > 0 ? ystart : 0;
     const int nb = (H - b0 < G::NROW) ? H - b0 : G::NROW;
     const size_t base = (size_t)b0 * W;
     const __amdgpu_buffer_rsrc_t rs_u = buffer_rsrc(s.ucur + base, (unsigned)nb * W4);
@@ -305,108 +274,69 @@ __device__ __forceinline__ void strip_step(float *ring, const StripArgs &s,
     if constexpr (VST) rs_v = buffer_rsrc(s.vout + base, (unsigned)nb * W4);
 
     // Staged columns (fixed for the whole strip): staged column j is image
-    // column X0-2-R+j.  Lane l stages j = CPL l + q (q < CPL), and the 2R
-    // right-halo columns j = NL .. NL+2R-1 go to lane l = j - NL mod 2R
-    // (lanes with the same halo column load and write the same value).
+    // column X0-2-R+j.  Lane l stages j = l, and the 2R right-halo columns
+    // j = 64 .. 63+2R go to lane l = j - 64 mod 2R (lanes with the same halo
+    // column load and write the same value).
     const int lb = R > 0 ? lane % (2 * R > 0 ? 2 * R : 1) : 0;
-    const unsigned cb = 4u * (unsigned)mirror_reflect(s.X0 - 2 - R + NL + lb, W);
-    unsigned ca[CPL], vo4[CPL], vo1[CPL];
-    bool out_col[CPL];
-#pragma unroll
-    for (int q = 0; q < CPL; ++q) {
-        const int j = CPL * lane + q;                        // this column, within the wave
-        const int cl = s.X0 - 2 + j;                         // ... and in the image
-        ca[q] = 4u * (unsigned)mirror_reflect(cl - R, W);
-        out_col[q] = j >= 2 && j < NL - 2 && cl < W;
-        vo4[q] = out_col[q] ? 4u * (unsigned)cl : kOffNone;
-        vo1[q] = out_col[q] ? (unsigned)cl : kOffNone;
-    }
-    float *col = ring + (CPL * lane + 1) * CS;               // ring column of staged column CPL l
-    float *bcol = ring + (NL + lb + 1) * CS;                 // right-halo column it stages
+    const unsigned cb = 4u * (unsigned)mirror_reflect(s.X0 - 2 - R + 64 + lb, W);
+    const int cl = s.X0 - 2 + lane;                           // this lane's image column
+    const unsigned ca = 4u * (unsigned)mirror_reflect(cl - R, W);
+    const bool out_col = lane >= 2 && lane < 62 && cl < W;
+    const unsigned vo4 = out_col ? 4u * (unsigned)cl : kOffNone;
+    const unsigned vo1 = out_col ? (unsigned)cl : kOffNone;
+    float *col = ring + (lane + 1) * CS;                     // ring column of staged column l
+    float *bcol = ring + (64 + lb + 1) * CS;                 // right-halo column it stages
 
-    float win[CPL][P];        // x-pass values, row i in slot i % P
+    float win[P];                                        // x-pass values, row i in slot i % P
 #pragma unroll
-    for (int q = 0; q < CPL; ++q)
-#pragma unroll
-        for (int j = 0; j < P; ++j) win[q][j] = 0.0f;
-    float v_m1[CPL], v_m2[CPL];                          // v at rows g, g-1 (before update)
-    float txx_p[CPL], tyy_p[CPL], tyy_pp[CPL];           // T at rows g-1 (and g-2 for Tyy)
-    float z_p[CPL], z_pp[CPL];                           // Txy(c+1)-Txy(c-1) at rows g-1, g-2
-    float uc_p[CPL];                                     // u^k(g-1, c)
-#pragma unroll
-    for (int q = 0; q < CPL; ++q)
-        v_m1[q] = v_m2[q] = txx_p[q] = tyy_p[q] = tyy_pp[q] = z_p[q] = z_pp[q] = uc_p[q] = 0.0f;
+    for (int j = 0; j < P; ++j) win[j] = 0.0f;
+    float v_m1 = 0.0f, v_m2 = 0.0f;                      // v at rows g, g-1 (before update)
+    float txx_p = 0.0f, tyy_p = 0.0f, tyy_pp = 0.0f;     // T at rows g-1 (and g-2 for Tyy)
+    float z_p = 0.0f, z_pp = 0.0f;                       // Txy(c+1)-Txy(c-1) at rows g-1, g-2
+    float uc_p = 0.0f;                                   // u^k(g-1, c)
     double d2 = 0.0, n2 = 0.0;
 
     // the next row to prefetch: its mirrored image row and the output row it serves
     RowTrack ty;
     ty.init(ystart, H);
-    if (s.up) ty.dir = -ty.dir;
-    int on = ystart - dir * (R + 2);
+    int on = ystart - (R + 2);
 
     // Loads run two stream rows ahead, always in the same order, so waiting
     // for one row never waits for a later row's loads.
-    auto prefetch = [&](StripRow<CPL> &r) {
+    auto prefetch = [&](StripRow &r) {
         const unsigned su = (unsigned)((ty.y > b0 ? ty.y : b0) - b0) * W4;
-#pragma unroll
-        for (int q = 0; q < CPL; ++q) r.a[q] = buf_f32(rs_u, ca[q], su);
+        r.a = buf_f32(rs_u, ca, su);
         if constexpr (R > 0) r.b = buf_f32(rs_u, cb, su);
         int oc = on < b0 ? b0 : on;                      // clamped; unused rows are not stored
         oc = oc > H - 1 ? H - 1 : oc;
         const unsigned ro = (unsigned)(oc - b0);
-#pragma unroll
-        for (int q = 0; q < CPL; ++q) {
-            r.pv[q] = buf_f32(rs_p, vo4[q], ro * W4);
-            r.mk[q] = __builtin_amdgcn_raw_buffer_load_b8(rs_m, vo1[q], ro * (unsigned)W, 0);
-            if constexpr (RES) r.rf[q] = buf_f32(rs_r, vo4[q], ro * W4);
-        }
+        r.pv = buf_f32(rs_p, vo4, ro * W4);
+        r.mk = __builtin_amdgcn_raw_buffer_load_b8(rs_m, vo1, ro * (unsigned)W, 0);
+        if constexpr (RES) r.rf = buf_f32(rs_r, vo4, ro * W4);
         ty.next(H);
-        on += dir;
+        ++on;
     };
-    StripRow<CPL> r0, r1;
+    StripRow r0, r1;
     r0.b = r1.b = 0.0f;
-#pragma unroll
-    for (int q = 0; q < CPL; ++q) r0.rf[q] = r1.rf[q] = 0.0f;
+    r0.rf = r1.rf = 0.0f;
     prefetch(r0);
     prefetch(r1);
 
-    // The Hessian of u at row g needs u(x-1), u(x), u(x+1) at rows g-1, g, g+1.
-    // With segments of >= 64 rows (about 4 waves per SIMD, registers to spare)
-    // they are kept per staged row, as u(x), u(x-1) + u(x+1) and u(x+1) - u(x-1),
-    // in registers indexed like the ring (slot i % D), from the x-pass taps
-    // R-1, R, R+1 of row i; the shorter strips, which need 8 waves per SIMD,
-    // read them back from the ring.
-    constexpr bool HREG = CPL == 1 && ROWS >= 64;
-    constexpr int HD = HREG ? D : 1;
-    float hc[HD], hs[HD], hd[HD];
-#pragma unroll
-    for (int j = 0; j < HD; ++j) hc[j] = hs[j] = hd[j] = 0.0f;
-
     // stage one row of u^k into ring row rr and take its x pass into window slot ws
-    auto stage_xpass = [&](const StripRow<CPL> &cur, int rr, int ws) {
-#pragma unroll
-        for (int q = 0; q < CPL; ++q) col[q * CS + rr] = cur.a[q];
+    auto stage_xpass = [&](const StripRow &cur, int rr, int ws) {
+        col[rr] = cur.a;
         if constexpr (R > 0) bcol[rr] = cur.b;
         wave_lds_sync();
+        float acc = w[0] * col[rr];
 #pragma unroll
-        for (int q = 0; q < CPL; ++q) {
-            float acc = w[0] * col[q * CS + rr];
-#pragma unroll
-            for (int j = 1; j <= 2 * R; ++j) acc = fmaf(w[j], col[(q + j) * CS + rr], acc);
-            win[q][ws] = acc;
-        }
-        if constexpr (HREG) {
-            const float l = col[(R - 1) * CS + rr], c = col[R * CS + rr], r = col[(R + 1) * CS + rr];
-            hc[rr] = c;
-            hs[rr] = l + r;
-            hd[rr] = xdiff(l, r);
-        }
+        for (int j = 1; j <= 2 * R; ++j) acc = fmaf(w[j], col[j * CS + rr], acc);
+        win[ws] = acc;
     };
 
     // ---- prologue: stage rows 0 .. 2R-1 and their x pass ----
 #pragma unroll
     for (int i = 0; i < 2 * R; ++i) {
-        const StripRow<CPL> cur = r0;
+        const StripRow cur = r0;
         r0 = r1;
         prefetch(r1);
         stage_xpass(cur, i % D, i % P);
@@ -418,8 +348,8 @@ __device__ __forceinline__ void strip_step(float *ring, const StripArgs &s,
         // that are behind get the SIMD first and all waves progress together.
         // With the default oldest-first order the early waves finish first and
         // the launch ends with few waves per SIMD to hide latency (about 4.4 of
-        // 8 resident on average at 4096^2); this schedule took the 64-row
-        // strips from 49 to 44.5 us there, with bitwise the same results.
+        // 8 resident on average at 4096^2); this schedule took 64-row strips
+        // from 49 to 44.5 us there, with bitwise the same results.
         // The adjoint's recompute steps (VST) stay at the lowest priority: they
         // run beside the reverse steps, which are the critical path.
         if constexpr (!VST) {
@@ -432,7 +362,7 @@ __device__ __forceinline__ void strip_step(float *ring, const StripArgs &s,
 #pragma unroll
         for (int ph = 0; ph < U; ++ph) {
             const int i = 2 * R + it * U + ph;           // stream row (wave-uniform)
-            const StripRow<CPL> cur = r0;
+            const StripRow cur = r0;
             r0 = r1;
             prefetch(r1);                                 // mirrored: always valid rows
 
@@ -441,89 +371,61 @@ __device__ __forceinline__ void strip_step(float *ring, const StripArgs &s,
 
             // ---- S2: y pass at stream row i - R ----
             // stream row i - R + j is in slot (ph + R + j) % P
-            float v[CPL];
-#pragma unroll
-            for (int q = 0; q < CPL; ++q)
-                v[q] = ypass_sym<R>(w, [&](int j) { return win[q][(ph + R + j) % P]; });
+            const float v = ypass_sym<R>(w, [&](int j) { return win[(ph + R + j) % P]; });
 
             // ---- S3: gradient, tensor, Hessian, contraction at row g = i - R - 1 ----
             // (the first rows of the loop produce values that only feed unstored rows)
-            float txx[CPL], tyy[CPL], txy[CPL], uc[CPL], vo[CPL];
-#pragma unroll
-            for (int q = 0; q < CPL; ++q) {
-                vo[q] = v_m2[q];                                              // v at row g - 1
-                const float gxs = right_of(v_m1, q) - left_of(v_m1, q);      // 2 gx
-                const float gys = v[q] - v_m2[q];                             // 2 gy
-                // rows g-1, g, g+1 are in ring slots sm, sg, sp
-                const int sm = (R - 2 + ph + D) % D, sg = (R - 1 + ph + D) % D, sp = (R + ph) % D;
-                float hxx, hyy, hxy;
-                if constexpr (HREG) {
-                    uc[q] = hc[sg];
-                    hxx = second_diff_sum(hs[sg], uc[q]);
-                    hyy = second_diff(hc[sm], uc[q], hc[sp]);
-                    hxy = mixed_diff(hd[sp], hd[sm]);
-                } else {
-                    // column q of this lane is staged column CPL l + q + R
-                    const float *um = col + (q + R) * CS + sm;
-                    const float *u0 = col + (q + R) * CS + sg;
-                    const float *up = col + (q + R) * CS + sp;
-                    uc[q] = u0[0];
-                    hxx = second_diff(u0[-CS], uc[q], u0[CS]);
-                    hyy = second_diff(um[0], uc[q], up[0]);
-                    hxy = mixed_diff(xdiff(up[-CS], up[CS]), xdiff(um[-CS], um[CS]));
-                }
+            const float vo = v_m2;                                            // v at row g - 1
+            const float gxs = from_next_lane(v_m1) - from_prev_lane(v_m1);   // 2 gx
+            const float gys = v - v_m2;                                       // 2 gy
+            // rows g-1, g, g+1 are in ring slots sm, sg, sp; this lane's column
+            // is staged column l + R
+            const int sm = (R - 2 + ph + D) % D, sg = (R - 1 + ph + D) % D, sp = (R + ph) % D;
+            const float *um = col + R * CS + sm;
+            const float *u0 = col + R * CS + sg;
+            const float *up = col + R * CS + sp;
+            const float uc = u0[0];
+            const float hxx = second_diff(u0[-CS], uc, u0[CS]);
+            const float hyy = second_diff(um[0], uc, up[0]);
+            const float hxy = mixed_diff(xdiff(up[-CS], up[CS]), xdiff(um[-CS], um[CS]));
 
-                const float s2 = grad2_sq(gxs, gys);                          // 4 |grad|^2
-                float mu1, mu3;
-                if constexpr (GEN) {
-                    model_mu(s2 * s.il2q, s.model, mu1, mu3);
-                } else {                                     // FOEED: Charbonnier, sqrt
-                    foeed_mu(s2, s.il2q, mu1, mu3);
-                }
-                contract(gxs, gys, s2, mu1, mu3, hxx, hyy, hxy, txx[q], tyy[q], txy[q]);
+            const float s2 = grad2_sq(gxs, gys);                              // 4 |grad|^2
+            float mu1, mu3;
+            if constexpr (GEN) {
+                model_mu(s2 * s.il2q, s.model, mu1, mu3);
+            } else {                                     // FOEED: Charbonnier, sqrt
+                foeed_mu(s2, s.il2q, mu1, mu3);
             }
-#pragma unroll
-            for (int q = 0; q < CPL; ++q) {
-                v_m2[q] = v_m1[q];
-                v_m1[q] = v[q];
-            }
+            float txx, tyy, txy;
+            contract(gxs, gys, s2, mu1, mu3, hxx, hyy, hxy, txx, tyy, txy);
+            v_m2 = v_m1;
+            v_m1 = v;
 
             // ---- S4: output row o = g - 1 (stream row i - R - 2) ----
-            float z[CPL];
-#pragma unroll
-            for (int q = 0; q < CPL; ++q) z[q] = right_of(txy, q) - left_of(txy, q);
-            const int o = ystart + dir * (i - R - 2);
-            if (i >= 2 * G::h && o < H) {      // first output row: Y0 (down), Y0 + OH - 1 (up)
+            const float z = from_next_lane(txy) - from_prev_lane(txy);
+            const int o = ystart + (i - R - 2);
+            if (i >= 2 * G::h && o < H) {                // the first output row is Y0
                 const unsigned ro = (unsigned)(o - b0) * W4;
-#pragma unroll
-                for (int q = 0; q < CPL; ++q) {
-                    const float sxx = left_of(txx_p, q) + right_of(txx_p, q);
-                    const float pu = outer_div(txx_p[q], tyy_p[q], sxx, tyy_pp[q] + tyy[q], z[q],
-                                               z_pp[q]);
-                    const float un = fsi_update(pu, uc_p[q], cur.pv[q], s.tau, s.alpha,
-                                                cur.mk[q] != 0);
-                    if constexpr (RES) {
-                        // columns without a pixel read 0 for the reference; add 0
-                        const double du = out_col[q] ? (double)un : 0.0;
-                        const double dd = du - (double)cur.rf[q];
-                        d2 = fma(dd, dd, d2);
-                        n2 = fma(du, du, n2);
-                    }
-                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(un), rs_o, vo4[q], ro, 0);
-                    if constexpr (VST)
-                        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(vo[q]), rs_v, vo4[q],
-                                                              ro, 0);
+                const float sxx = from_prev_lane(txx_p) + from_next_lane(txx_p);
+                const float pu = outer_div(txx_p, tyy_p, sxx, tyy_pp + tyy, z, z_pp);
+                const float un = fsi_update(pu, uc_p, cur.pv, s.tau, s.alpha, cur.mk != 0);
+                if constexpr (RES) {
+                    // columns without a pixel read 0 for the reference; add 0
+                    const double du = out_col ? (double)un : 0.0;
+                    const double dd = du - (double)cur.rf;
+                    d2 = fma(dd, dd, d2);
+                    n2 = fma(du, du, n2);
                 }
+                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(un), rs_o, vo4, ro, 0);
+                if constexpr (VST)
+                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(vo), rs_v, vo4, ro, 0);
             }
-#pragma unroll
-            for (int q = 0; q < CPL; ++q) {
-                tyy_pp[q] = tyy_p[q];
-                tyy_p[q] = tyy[q];
-                txx_p[q] = txx[q];
-                z_pp[q] = z_p[q];
-                z_p[q] = z[q];
-                uc_p[q] = uc[q];
-            }
+            tyy_pp = tyy_p;
+            tyy_p = tyy;
+            txx_p = txx;
+            z_pp = z_p;
+            z_p = z;
+            uc_p = uc;
         }
     }
     if constexpr (RES) {

@@ -80,3 +80,32 @@ def test_reverse_tiles_equal_reverse_strips(H, W, sigma):
     for shape in (0, 1, 2):
         assert torch.equal(out[shape][0], out[6][0]) and torch.equal(out[shape][1], out[6][1]), shape
         assert torch.isfinite(out[shape][2]).all()
+
+
+@pytest.mark.parametrize("sigma", [0.0, 0.3, 0.6, 1.0, 1.3, 1.5, 2.0, 2.3, 2.6])
+@pytest.mark.parametrize("H,W", [(28, 124), (29, 125), (57, 126), (65, 127), (60, 249), (3, 251),
+                                 (137, 123), (140, 1), (1, 400), (200, 380)])
+def test_tall_strips_equal_tiles(H, W, sigma):
+    # 124-column strips at their column and segment edges: strips inside the image (8-byte
+    # accesses, odd widths included), strips at and over its borders, segments in both directions
+    announce(f"tall strips vs tiles {H}x{W} sigma={sigma}")
+    b = batch(2, H, W, 20 + H + W)
+    mask, known = to_dev(b["mask"]), to_dev(b["known"])
+    ref = cycle(b, sigma, 3, eed4.EED4_FORCE_SHAPE(0))
+    gu = torch.from_numpy(np.random.default_rng(H * W).standard_normal((2, H, W)).astype(np.float32)).cuda()
+    grads = {}
+    for shape in (0, 3, 4, 7, 8):
+        fl = eed4.EED4_FORCE_SHAPE(shape)
+        got = cycle(b, sigma, 3, fl)
+        assert np.array_equal(got[0], ref[0]), eed4.SHAPE_NAMES[shape]
+        np.testing.assert_allclose(got[1], ref[1], rtol=1e-12, atol=0)
+        # the backward's recompute runs them too, keeping K_sigma * u^k
+        p = eed4.params(0.03, sigma, 0.05, 3, 1, flags=fl)
+        ck = to_dev(b["u_init"])[None].contiguous()
+        g = [torch.empty_like(gu), torch.empty_like(gu), torch.empty(2, device="cuda")]
+        eed4.eed4_backward(ck, mask, known, p, 1, gu, *g)
+        torch.cuda.synchronize()
+        grads[shape] = g
+    for shape in (3, 4, 7, 8):
+        for i in (0, 1):
+            assert torch.equal(grads[shape][i], grads[0][i]), eed4.SHAPE_NAMES[shape]
