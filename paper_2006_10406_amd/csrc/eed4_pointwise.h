@@ -62,11 +62,14 @@ __device__ __forceinline__ float ypass_sym(const float *w, At at)
 
 // Squared norm of twice the regularised gradient: gxs, gys are the central
 // differences v(x+1) - v(x-1), v(y+1) - v(y-1) of the presmoothed image
-// (2 grad u_sigma, Sec. 3.1).
+// (2 grad u_sigma, Sec. 3.1).  The added 1e-36, below half a unit in the last
+// place of any |gradient| above 1e-14, keeps the reciprocal norm finite where
+// the gradient vanishes, in the multiply-add that is there anyway (a maximum
+// issues at half the rate).
 __device__ __forceinline__ float grad2_sq(float gxs, float gys)
 {
 #pragma clang fp contract(off)
-    return fmaf(gxs, gxs, gys * gys);
+    return fmaf(gxs, gxs, fmaf(gys, gys, 1e-36f));
 }
 
 // FOEED eigenvalues (eq. CharDiff, Sec. 3.1): mu1 = g = (1 + |grad|^2 /
@@ -85,13 +88,13 @@ __device__ __forceinline__ void foeed_mu(float s2, float il2q, float &mu1, float
 //   T = H + (mu1 - 1)(E1 : H) E1 + (mu3 - 1)(E3 : H) E3,
 //   (E3 : H) E3 = [c (hyy - hxx) + (a - b) hxy] [[-2c, a - b], [a - b, 2c]],
 // a = nx^2, b = ny^2, c = nx ny, n the unit gradient direction (taken as 0
-// where the gradient vanishes: there mu1 = mu3 = 1 and T = H).
+// where the gradient vanishes: there mu1 = mu3 = 1 and T = H).  s2 is grad2_sq's.
 __device__ __forceinline__ void contract(float gxs, float gys, float s2, float mu1, float mu3,
                                          float hxx, float hyy, float hxy, float &txx, float &tyy,
                                          float &txy)
 {
 #pragma clang fp contract(off)
-    const float rn = __builtin_amdgcn_rsqf(fmaxf(s2, 1e-30f));
+    const float rn = __builtin_amdgcn_rsqf(s2);
     const float nx = gxs * rn, ny = gys * rn;
     const float aa = nx * nx, bb = ny * ny, c = nx * ny;
     const float amb = aa - bb, c2 = c + c;
@@ -99,9 +102,8 @@ __device__ __forceinline__ void contract(float gxs, float gys, float s2, float m
     const float x3 = fmaf(c, hyy - hxx, amb * hxy);
     const float k1 = fmaf(mu1, e1h, -e1h);
     const float k3 = fmaf(mu3, x3, -x3);
-    const float k3c2 = k3 * c2;
-    txx = fmaf(k1, aa, hxx - k3c2);
-    tyy = fmaf(k1, bb, hyy + k3c2);
+    txx = fmaf(k1, aa, fmaf(-k3, c2, hxx));
+    tyy = fmaf(k1, bb, fmaf(k3, c2, hyy));
     txy = fmaf(k1, c, fmaf(k3, amb, hxy));
 }
 
