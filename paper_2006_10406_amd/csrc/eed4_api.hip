@@ -184,8 +184,11 @@ int capture_cycle(const CycleJob &j, hipGraphExec_t *exec, int nc)
 // without a new capture and instantiation.  The cache is bounded; beyond
 // kMaxCachedGraphs jobs a call captures its own graph and destroys it at the
 // end, as without the cache.  Entries are never evicted (a launch of an
-// evicted graph might still be in flight on another stream).
-constexpr size_t kMaxCachedGraphs = 64;
+// evicted graph might still be in flight on another stream).  A run of a fixed
+// number of cycles holds up to three (four cycles, one, and the last one with
+// its residual), two where it has no group of four.  (With the last cycle
+// launched step by step instead, small64 took 667 us against 656.)
+constexpr size_t kMaxCachedGraphs = 128;
 constexpr int kGraphCycles = 4;    // cycles per graph when no host work sits between cycles
 
 struct CycleKey {
