@@ -543,6 +543,16 @@ static int run_to_tolerance(const CycleJob &j, float *T, const eed4_params *p,
     return rc;
 }
 
+// Runs with checkpoints launch their steps one by one, and cycles go from one
+// checkpoint straight into the next, from this problem size and number of
+// cycles on.  Below, a graph per cycle and a copy between cycles is the faster:
+// its steps take less than their launches (4.2 us).  30 cycles of 10, R = 3, with
+// copies against without: 64^2 1170 and 1330 us, 4 x 256^2 1626 and 1654,
+// 2 x 512^2 1930 and 1845, 16 x 256^2 2490 and 2284; 2 cycles on 16 x 256^2, where
+// the first launches are what counts, 210 and 219.
+constexpr size_t kDirectCkptPixels = 1u << 19;
+constexpr int kDirectCkptCycles = 4;
+
 // M cycles in place on j.S with one stop-rule evaluation at the end (tol 0,
 // or a single cycle).  Without a history only the last cycle's residual is
 // ever read, so the others are not formed (a residual step and its reduction
@@ -562,8 +572,16 @@ static int run_fixed(const CycleJob &j, int M, const eed4_params *p, float *ckpt
     bool own_exec = false, own_last = false, own_multi = false;
     int rc = EED4_OK;
     hipError_t e = hipSuccess;
-    const bool graphs = !(p->flags & EED4_NO_GRAPH);
+    // With checkpoints, a cycle can read its start from its checkpoint and leave
+    // its result in the next one, which takes the place of a copy per cycle but
+    // needs its steps launched one by one (a graph holds its buffers).
+    const bool direct = ckpt && N >= kDirectCkptPixels && M >= kDirectCkptCycles;
+    const bool graphs = !(p->flags & EED4_NO_GRAPH) && !direct;
     int m = 0;
+    if (direct) {
+        e = hipMemcpyAsync(ckpt, j.S, sizeof(float) * N, hipMemcpyDeviceToDevice, s);
+        if (e != hipSuccess) rc = hip_fail(e, "checkpoint copy");
+    }
     if (graphs && !ckpt && !hist_dev && M > kGraphCycles) {
         rc = cycle_graph(plain, kGraphCycles, &multi, &own_multi);
         for (; rc == EED4_OK && m + kGraphCycles < M; m += kGraphCycles) {
@@ -576,7 +594,7 @@ static int run_fixed(const CycleJob &j, int M, const eed4_params *p, float *ckpt
     if (rc == EED4_OK && graphs) rc = cycle_graph(j, 1, &last, &own_last);
     for (; rc == EED4_OK && m < M; ++m) {
         trace_mark("eed4 cycle %d queued", m);
-        if (ckpt) {
+        if (ckpt && !direct) {
             e = hipMemcpyAsync(ckpt + (size_t)m * N, j.S, sizeof(float) * N,
                                hipMemcpyDeviceToDevice, s);
             if (e != hipSuccess) { rc = hip_fail(e, "checkpoint copy"); break; }
@@ -584,8 +602,13 @@ static int run_fixed(const CycleJob &j, int M, const eed4_params *p, float *ckpt
         if (graphs) {
             e = hipGraphLaunch(m == M - 1 ? last : exec, s);
             if (e != hipSuccess) { rc = hip_fail(e, "graph launch"); break; }
-        } else if ((rc = enqueue_cycle(m == M - 1 ? j : plain, s)) != EED4_OK) {
-            break;
+        } else {
+            CycleJob c = m == M - 1 ? j : plain;
+            if (direct) {
+                c.Out = m == M - 1 ? j.S : ckpt + (size_t)(m + 1) * N;
+                c.S = ckpt + (size_t)m * N;
+            }
+            if ((rc = enqueue_cycle(c, s)) != EED4_OK) break;
         }
         if (hist_dev) {
             e = hipMemcpyAsync(hist_dev + 2 * (size_t)B * m, j.sums, sizeof(double) * 2 * B,
