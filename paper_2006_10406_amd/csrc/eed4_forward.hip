@@ -473,7 +473,11 @@ static hipError_t launch_step_r(int shape, const float *ucur, const float *uprev
 }
 
 // The keep-v step of a forward step shape: a strip shape keeps its own (8-row
-// strips aside), a tile shape runs the tile of its width class.
+// strips aside); of the 60-column tiles those of 32 rows, which recompute fewer
+// halo rows, run from more than two a CU on (beside the reverse step the sum of
+// the work counts: 16 x 256^2 at R = 3, backward of 50 steps 893 us against 925
+// with 16 rows; 1000^2 872 and 880), those of 16 rows below (700^2 702 against
+// 708, 64 x 100^2 734 against 741).
 template <int R, bool GEN>
 static hipError_t launch_keepv_r(int shape, const float *ucur, const float *uprev, float *uout,
                                  float *vout, const uint8_t *mask, int B, int H, int W,
@@ -488,7 +492,10 @@ static hipError_t launch_keepv_r(int shape, const float *ucur, const float *upre
             return launch_pair_r<R>(shape, ucur, uprev, uout, nullptr, vout, mask, B, H, W, a,
                                     nullptr, s);
         return hipErrorInvalidValue;
-    default: return launch_keepv_tile<R, 64, 16, GEN>(ucur, uprev, uout, vout, mask, B, H, W, a, s);
+    default:
+        if ((long long)tiles_per_image(0, R, B, H, W) * B > 512)
+            return launch_keepv_tile<R, 64, 32, GEN>(ucur, uprev, uout, vout, mask, B, H, W, a, s);
+        return launch_keepv_tile<R, 64, 16, GEN>(ucur, uprev, uout, vout, mask, B, H, W, a, s);
     }
 }
 
