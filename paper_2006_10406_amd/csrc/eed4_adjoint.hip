@@ -885,7 +885,7 @@ static int adj_strip_items_t(int H, int W)
 }
 
 // Segment heights of the strip reverse step per forward strip shape.  The
-// 64-row shapes map to segments of >= 80 rows: at 4096^2 and R = 6 those
+// shapes 3 and 7 map to segments of >= 80 rows: at 4096^2 and R = 6 those
 // launch 4,042 waves, which all fit at once at 4 waves per SIMD (>= 64 rows
 // launch 4,730, and the last 16 % ran as a second, nearly empty round).
 template <int R>
