@@ -113,6 +113,14 @@ void cycle_roles(int k, int n, float *S, float *X, float *Y, float **cur, float 
     if (k == n - 1 && n > 1) *out = S;
 }
 
+// Shape of a cycle's residual step: the cycle's own, but 32 x 16 tiles for 16 x 16
+// ones, whose 12 output columns would need more partials than the workspace has
+// always held (max_partials_per_image).  All shapes give bitwise the same state.
+static int residual_shape(int shape)
+{
+    return shape == kShapeTile16x16 ? kShapeTile32x16 : shape;
+}
+
 int enqueue_cycle(const CycleJob &j, hipStream_t s)
 {
     const int n = j.n;
@@ -124,8 +132,9 @@ int enqueue_cycle(const CycleJob &j, hipStream_t s)
         if (last && (n > 1 || dst != j.S)) out = dst;
         StepArgs a = make_args(j.sigma, j.R, j.tau, j.lambda, k, j.model);
         const bool res = last && j.residual;
-        hipError_t e = launch_step(j.R, j.shape, cur, prev, out, res ? j.S : nullptr, j.mask,
-                                   j.B, j.H, j.W, a, res ? j.partials : nullptr, s);
+        hipError_t e = launch_step(j.R, res ? residual_shape(j.shape) : j.shape, cur, prev, out,
+                                   res ? j.S : nullptr, j.mask, j.B, j.H, j.W, a,
+                                   res ? j.partials : nullptr, s);
         if (e != hipSuccess) return hip_fail(e, "fsi step launch");
     }
     if (n == 1 && dst == j.S) {
@@ -134,7 +143,9 @@ int enqueue_cycle(const CycleJob &j, hipStream_t s)
         if (e != hipSuccess) return hip_fail(e, "cycle copy");
     }
     if (!j.residual) return EED4_OK;
-    hipError_t e = launch_reduce(j.partials, tiles_per_image(j.shape, j.R, j.B, j.H, j.W), j.B, j.sums, s);
+    hipError_t e = launch_reduce(j.partials,
+                                 tiles_per_image(residual_shape(j.shape), j.R, j.B, j.H, j.W), j.B,
+                                 j.sums, s);
     if (e != hipSuccess) return hip_fail(e, "residual reduce launch");
     return EED4_OK;
 }
@@ -249,14 +260,15 @@ struct InpaintLayout {
     size_t X, Y, T, partials, sums, hist, total;
 };
 
-// residual partials: enough for the largest per-image count of any kernel shape
+// Residual partials: enough for the largest per-image count of any residual
+// step, and one to a 16 x 16 block.  The block count decides on most sizes and is
+// no kernel's: it keeps the workspace, and with it the largest problem that fits
+// the static scratch, what it was when 16 x 16 tiles had 16 output columns.
 int max_partials_per_image(int R, int B, int H, int W)
 {
-    int m = 0;
-    for (int sh = 0; sh < kNumShapes; ++sh) {
-        int t = tiles_per_image(sh, R, B, H, W);
-        if (t > m) m = t;
-    }
+    int m = ((W + 15) / 16) * ((H + 15) / 16);
+    for (int sh = 0; sh < kNumShapes; ++sh)
+        m = std::max(m, tiles_per_image(residual_shape(sh), R, B, H, W));
     return m;
 }
 

@@ -175,3 +175,18 @@ def test_static_cycle_size_limit_before_any_gpu_work(lib):
                                      ptr) == e._lib.EED4_EINVAL
     assert lib.eed4_fsi_cycle_static(ptr, ptr, ptr, 1, 8, 8, ctypes.byref(p), None,
                                      None) == e._lib.EED4_EINVAL
+
+
+def test_static_cycle_keeps_its_largest_images(lib):
+    # the residual partials of 2884 x 2884 fit beside its two rotation buffers (one partial to a
+    # 16 x 16 block), those of 2885 x 2885 do not, at every radius and kernel shape
+    import paper_2006_10406_amd as e
+    limit = e._lib.EED4_STATIC_SCRATCH_BYTES
+    for sigma in (0.0, 0.3, 1.0, 1.5, 2.6):
+        for flags in (0, e.EED4_TILE_KERNEL, *(e.EED4_FORCE_SHAPE(s) for s in range(11))):
+            p = e.params(0.03, sigma, 0.05, 10, 1, flags=flags)
+            size = lambda side: e.eed4_workspace_size(e.EED4_OP_CYCLE, 1, side, side, p)
+            assert size(2882) <= limit and size(2884) <= limit < size(2885)
+            # two planes and 181 x 181 partials of 16 bytes, each rounded up to 256, and the sums
+            up = lambda x: (x + 255) // 256 * 256
+            assert size(2884) == 2 * up(4 * 2884 ** 2) + up(16 * 181 ** 2) + 256

@@ -80,3 +80,16 @@ def test_static_cycle_rejects_problems_beyond_its_scratch():
     assert err.value.code == eed4._lib.EED4_ETOOLARGE
     torch.cuda.synchronize()
     assert torch.equal(u, before)
+
+
+@pytest.mark.parametrize("flags", [0, eed4.EED4_FORCE_SHAPE(10), eed4.EED4_FORCE_SHAPE(2)])
+def test_static_cycle_of_the_largest_square_image(flags):
+    # 2884 x 2884, the largest square that fits; 16 x 16 tiles take their residual step on 32 x 16
+    # ones, whose partials fit
+    announce(f"eed4_fsi_cycle_static 2884x2884, n 2, flags {flags:#x}")
+    b = batch(1, 2884, 2884, 4300)
+    (u_ws, s_ws), (u_st, s_st) = both(b, eed4.params(0.03, 1.0, 0.05, 2, 1, flags=flags))
+    assert np.array_equal(u_st, u_ws) and np.array_equal(s_st, s_ws)
+    (u_ref, s_ref), _ = both(b, eed4.params(0.03, 1.0, 0.05, 2, 1, flags=eed4.EED4_FORCE_SHAPE(5)))
+    assert np.array_equal(u_st, u_ref)
+    np.testing.assert_allclose(s_st, s_ref, rtol=1e-12, atol=0)
