@@ -815,10 +815,10 @@ __global__ void lambda_carry_kernel(const float *cyc, float *slots, int B, int t
 // pass (L <= 2048 per image): the same tree and the same cascade, so the same
 // bits, with one launch per cycle instead of two.
 __global__ __launch_bounds__(1024) void lambda_cycle_kernel(const float *in, long long L,
-                                                            float *slots, int B, int t)
+                                                            float *slots, int b0, int B, int t)
 {
     __shared__ float sv[2048];
-    const int b = blockIdx.x, tid = threadIdx.x;
+    const int b = b0 + blockIdx.x, tid = threadIdx.x;
     const float *p = in + (size_t)b * L;
     sv[tid] = tid < L ? p[tid] : 0.0f;
     sv[tid + 1024] = tid + 1024 < L ? p[tid + 1024] : 0.0f;
@@ -943,6 +943,21 @@ struct RevStep {
     int B, H, W, R, shape, first;
     int fresh;               // a cycle's first reverse step: ubar^k starts at 0 (not read)
     int kflags() const { return (first ? 1 : 0) | (fresh ? 2 : 0); }
+    // the step of images b0 .. b0 + n - 1 alone
+    RevStep images(int b0, int n) const
+    {
+        const size_t o = (size_t)b0 * H * W;
+        RevStep q = *this;
+        q.v += o;
+        q.u += o;
+        q.an += o;
+        q.ac += o;
+        q.ap += o;
+        q.mask += o;
+        q.lp += (size_t)b0 * ls;
+        q.B = n;
+        return q;
+    }
 };
 
 template <int R, int NTH, int OQ>
@@ -951,11 +966,12 @@ static hipError_t launch_rev_tile(const RevStep &t, const StepArgs &a, float ls,
     using G = AdjTileGeo<R, NTH, OQ>;
     const int nbx = (t.W + G::SW - 1) / G::SW;
     const int tpi = adj_tile_items_t<R, NTH, OQ>(t.H, t.W);
-    if ((long long)tpi * t.B > 0x7fffffffLL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((adjoint_tile_kernel<R, NTH, OQ>), dim3((unsigned)(tpi * t.B)), dim3(NTH),
-                       0, s, t.v, t.u, t.an, t.ac, t.ap, t.mask, t.H, t.W, nbx, tpi, a, ls,
-                       t.kflags(), t.lp, t.ls);
-    return hipGetLastError();
+    return launch_batches(t.B, tpi, 1, NTH, [&](int b0, int n, unsigned blocks) {
+        const RevStep q = t.images(b0, n);
+        hipLaunchKernelGGL((adjoint_tile_kernel<R, NTH, OQ>), dim3(blocks), dim3(NTH), 0, s, q.v, q.u,
+                           q.an, q.ac, q.ap, q.mask, q.H, q.W, nbx, tpi, a, ls, q.kflags(), q.lp,
+                           q.ls);
+    });
 }
 
 // Waves of kernel k (256-thread workgroups) the current device holds at once;
@@ -980,16 +996,15 @@ static hipError_t launch_rev_strip(const RevStep &t, const StepArgs &a, float ls
     using G = AdjStripGeo<R, ROWS>;
     const int nstrip = (t.W + G::SW - 1) / G::SW;
     const int per_img = adj_strip_items_t<R, ROWS>(t.H, t.W);
-    const long long nitems = (long long)per_img * t.B;
-    if (nitems > (1LL << 31) - 4) return hipErrorInvalidValue;
-    const unsigned nblk = (unsigned)((nitems + 3) / 4);
     // the issue-priority schedule only when every wave is resident at once
     static const long long cap = resident_waves(adjoint_strip_kernel<R, ROWS>);
-    const int prio = nitems <= cap ? 1 : 0;
-    hipLaunchKernelGGL((adjoint_strip_kernel<R, ROWS>), dim3(nblk), dim3(256), 0, s, t.v, t.u, t.an,
-                       t.ac, t.ap, t.mask, t.H, t.W, nstrip, per_img, (int)nitems, a, ls,
-                       t.kflags(), prio, t.lp, t.ls);
-    return hipGetLastError();
+    const int prio = (long long)per_img * t.B <= cap ? 1 : 0;
+    return launch_batches(t.B, per_img, 4, 256, [&](int b0, int n, unsigned blocks) {
+        const RevStep q = t.images(b0, n);
+        hipLaunchKernelGGL((adjoint_strip_kernel<R, ROWS>), dim3(blocks), dim3(256), 0, s, q.v, q.u,
+                           q.an, q.ac, q.ap, q.mask, q.H, q.W, nstrip, per_img, per_img * n, a, ls,
+                           q.kflags(), prio, q.lp, q.ls);
+    });
 }
 
 template <int R>
@@ -999,15 +1014,14 @@ static hipError_t launch_rev_model(const RevStep &t, const StepArgs &a, float ls
     using G = AdjStripGeo<R, 28>;
     const int nstrip = (t.W + G::SW - 1) / G::SW;
     const int per_img = adj_strip_items_t<R, 28>(t.H, t.W);
-    const long long nitems = (long long)per_img * t.B;
-    if (nitems > (1LL << 31) - 4) return hipErrorInvalidValue;
-    const unsigned nblk = (unsigned)((nitems + 3) / 4);
     static const long long cap = resident_waves(adjoint_strip_model_kernel<R>);
-    const int prio = nitems <= cap ? 1 : 0;
-    hipLaunchKernelGGL((adjoint_strip_model_kernel<R>), dim3(nblk), dim3(256), 0, s, t.v, t.u, t.an,
-                       t.ac, t.ap, t.mask, t.H, t.W, nstrip, per_img, (int)nitems, a, ls,
-                       t.kflags(), prio, t.lp, t.ls);
-    return hipGetLastError();
+    const int prio = (long long)per_img * t.B <= cap ? 1 : 0;
+    return launch_batches(t.B, per_img, 4, 256, [&](int b0, int n, unsigned blocks) {
+        const RevStep q = t.images(b0, n);
+        hipLaunchKernelGGL((adjoint_strip_model_kernel<R>), dim3(blocks), dim3(256), 0, s, q.v, q.u,
+                           q.an, q.ac, q.ap, q.mask, q.H, q.W, nstrip, per_img, per_img * n, a, ls,
+                           q.kflags(), prio, q.lp, q.ls);
+    });
 }
 
 template <int R>
@@ -1313,9 +1327,13 @@ extern "C" int eed4_backward(const float *ckpt, const uint8_t *mask, const float
         while ((j >> carries) & 1) ++carries;
         const long long np = (long long)n * items;
         if (np <= 2048) {
-            hipLaunchKernelGGL(lambda_cycle_kernel, dim3(B), dim3(1024), 0, s, lp, np, slots, B,
-                               carries);
-            EED4_TRY2(hipGetLastError(), "lambda sum");
+            EED4_TRY2(launch_batches(B, 1, 1, 1024,
+                                     [&](int b0, int, unsigned blocks) {
+                                         hipLaunchKernelGGL(lambda_cycle_kernel, dim3(blocks),
+                                                            dim3(1024), 0, s, lp, np, slots, b0, B,
+                                                            carries);
+                                     }),
+                      "lambda sum");
         } else {
             EED4_TRY2(launch_pairwise_sum(lp, np, B, (float *)(base + L.t1),
                                           (float *)(base + L.t2), cyc, s), "lambda sum");

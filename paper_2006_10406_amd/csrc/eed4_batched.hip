@@ -7,7 +7,7 @@
 // The queue holds one entry per work item (a tile of a workgroup, or a strip
 // segment of a wave) of every image still iterating.  A launch has one wave or
 // workgroup per item of the full queue and walks the queue with a static
-// stride (a no-op loop unless the grid is smaller than the queue); every XCD
+// stride (a no-op loop unless the queue passes the largest grid); every XCD
 // takes contiguous runs of items, so neighbouring items share its L2.  (A
 // global atomic work counter was tried first: with one device-scope counter
 // for all XCDs the pulls serialise and the step took twice as long.  A grid
@@ -456,7 +456,7 @@ static int prepare(BatchRun &r, const eed4_image *im, int B, const eed4_params *
     // hardware dispatcher balances them.  Later cycles may have fewer items:
     // the waves past the queue length exit at once.
     const int ql = (int)r.queue.size();
-    r.grid = std::max(1, is_strip(shape) ? (ql + 3) / 4 : ql);
+    r.grid = (int)std::min(std::max<long long>(1, is_strip(shape) ? (ql + 3LL) / 4 : ql), max_blocks(256));
     return upload_queue(r, s);
 }
 

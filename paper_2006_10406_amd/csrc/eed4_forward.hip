@@ -241,10 +241,15 @@ __global__ __launch_bounds__(1024) void reduce_kernel(const double *partials, in
 hipError_t launch_hold(float *u, const uint8_t *mask, const float *known, size_t n,
                        hipStream_t s)
 {
-    if (n == 0) return hipSuccess;
-    const size_t blocks = (n + 1023) / 1024;      // <= 2^26 for the largest batch
-    hipLaunchKernelGGL(hold_kernel, dim3((unsigned)blocks), dim3(256), 0, s, u, mask, known, n);
-    return hipGetLastError();
+    constexpr size_t kPart = (size_t)1 << 33;     // elements to a launch: 2^23 workgroups
+    for (size_t i = 0; i < n; i += kPart) {
+        const size_t m = n - i < kPart ? n - i : kPart;
+        hipLaunchKernelGGL(hold_kernel, dim3((unsigned)((m + 1023) / 1024)), dim3(256), 0, s, u + i,
+                           mask + i, known + i, m);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 // Segment height of the default 124-column strips in a launch of `waves(rows)`
@@ -333,29 +338,27 @@ static hipError_t launch_strip_t(const float *ucur, const float *uprev, float *u
     using G = StripGeo<R, ROWS>;
     const int nstrip = (W + G::SW - 1) / G::SW;
     const int per_img = nstrip * ((H + G::OH - 1) / G::OH);
-    const long long nitems = (long long)per_img * B;
-    const long long nblk = (nitems + 3) / 4;
-    if (nitems <= 0 || nblk > 0x7fffffffLL) return hipErrorInvalidValue;
     static_assert(!GEN || ROWS == 28, "tensor variants run 28-row strips");
-    if constexpr (GEN) {
-        if (ref)
-            hipLaunchKernelGGL((strip_model_kernel<R, true>), dim3((unsigned)nblk), dim3(256), 0, s,
-                               ucur, uprev, uout, ref, mask, H, W, nstrip, per_img, (int)nitems, a,
-                               partials);
-        else
-            hipLaunchKernelGGL((strip_model_kernel<R, false>), dim3((unsigned)nblk), dim3(256), 0, s,
-                               ucur, uprev, uout, ref, mask, H, W, nstrip, per_img, (int)nitems, a,
-                               partials);
-    } else if (ref) {
-        hipLaunchKernelGGL((strip_kernel<R, true, ROWS>), dim3((unsigned)nblk), dim3(256), 0, s,
-                           ucur, uprev, uout, ref, mask, H, W, nstrip, per_img, (int)nitems, a,
-                           partials);
-    } else {
-        hipLaunchKernelGGL((strip_kernel<R, false, ROWS>), dim3((unsigned)nblk), dim3(256), 0, s,
-                           ucur, uprev, uout, ref, mask, H, W, nstrip, per_img, (int)nitems, a,
-                           partials);
-    }
-    return hipGetLastError();
+    return launch_batches(B, per_img, 4, 256, [&](int b0, int n, unsigned blocks) {
+        const size_t o = (size_t)b0 * H * W;
+        const float *r = ref ? ref + o : nullptr;
+        double *const pt = ref ? partials + 2 * (size_t)b0 * per_img : nullptr;
+        const dim3 g(blocks), b(256);
+        if constexpr (GEN) {
+            if (ref)
+                hipLaunchKernelGGL((strip_model_kernel<R, true>), g, b, 0, s, ucur + o, uprev + o,
+                                   uout + o, r, mask + o, H, W, nstrip, per_img, per_img * n, a, pt);
+            else
+                hipLaunchKernelGGL((strip_model_kernel<R, false>), g, b, 0, s, ucur + o, uprev + o,
+                                   uout + o, r, mask + o, H, W, nstrip, per_img, per_img * n, a, pt);
+        } else if (ref) {
+            hipLaunchKernelGGL((strip_kernel<R, true, ROWS>), g, b, 0, s, ucur + o, uprev + o,
+                               uout + o, r, mask + o, H, W, nstrip, per_img, per_img * n, a, pt);
+        } else {
+            hipLaunchKernelGGL((strip_kernel<R, false, ROWS>), g, b, 0, s, ucur + o, uprev + o,
+                               uout + o, r, mask + o, H, W, nstrip, per_img, per_img * n, a, pt);
+        }
+    });
 }
 
 // A pair shape; with vout the recompute step that keeps K_sigma * u^k.
@@ -367,20 +370,22 @@ static hipError_t launch_pair_r(int shape, const float *ucur, const float *uprev
     const int rows = strip_rows(R, shape, 1, &H, &W, B);
     const int nstrip = (W + PairGeo<R>::SW - 1) / PairGeo<R>::SW;
     const int per_img = nstrip * ((H + rows - 1) / rows);
-    const long long nitems = (long long)per_img * B;
-    const long long nblk = (nitems + 3) / 4;
-    if (nitems <= 0 || nblk > 0x7fffffffLL) return hipErrorInvalidValue;
-    const dim3 g((unsigned)nblk), b(256);
-    if (vout)
-        hipLaunchKernelGGL((pair_kernel<R, false, true>), g, b, 0, s, ucur, uprev, uout, nullptr,
-                           vout, mask, H, W, nstrip, per_img, (int)nitems, rows, a, nullptr);
-    else if (ref)
-        hipLaunchKernelGGL((pair_kernel<R, true, false>), g, b, 0, s, ucur, uprev, uout, ref,
-                           nullptr, mask, H, W, nstrip, per_img, (int)nitems, rows, a, partials);
-    else
-        hipLaunchKernelGGL((pair_kernel<R, false, false>), g, b, 0, s, ucur, uprev, uout, nullptr,
-                           nullptr, mask, H, W, nstrip, per_img, (int)nitems, rows, a, nullptr);
-    return hipGetLastError();
+    return launch_batches(B, per_img, 4, 256, [&](int b0, int n, unsigned blocks) {
+        const size_t o = (size_t)b0 * H * W;
+        const dim3 g(blocks), b(256);
+        if (vout)
+            hipLaunchKernelGGL((pair_kernel<R, false, true>), g, b, 0, s, ucur + o, uprev + o,
+                               uout + o, nullptr, vout + o, mask + o, H, W, nstrip, per_img,
+                               per_img * n, rows, a, nullptr);
+        else if (ref)
+            hipLaunchKernelGGL((pair_kernel<R, true, false>), g, b, 0, s, ucur + o, uprev + o,
+                               uout + o, ref + o, nullptr, mask + o, H, W, nstrip, per_img,
+                               per_img * n, rows, a, partials + 2 * (size_t)b0 * per_img);
+        else
+            hipLaunchKernelGGL((pair_kernel<R, false, false>), g, b, 0, s, ucur + o, uprev + o,
+                               uout + o, nullptr, nullptr, mask + o, H, W, nstrip, per_img,
+                               per_img * n, rows, a, nullptr);
+    });
 }
 
 template <int R, bool GEN>
@@ -391,12 +396,12 @@ static hipError_t launch_keepv_t(const float *ucur, const float *uprev, float *u
     using G = StripGeo<R, 28>;
     const int nstrip = (W + G::SW - 1) / G::SW;
     const int per_img = nstrip * ((H + G::OH - 1) / G::OH);
-    const long long nitems = (long long)per_img * B;
-    const long long nblk = (nitems + 3) / 4;
-    if (nitems <= 0 || nblk > 0x7fffffffLL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((strip_keepv_kernel<R, GEN>), dim3((unsigned)nblk), dim3(256), 0, s,
-                       ucur, uprev, uout, vout, mask, H, W, nstrip, per_img, (int)nitems, a);
-    return hipGetLastError();
+    return launch_batches(B, per_img, 4, 256, [&](int b0, int n, unsigned blocks) {
+        const size_t o = (size_t)b0 * H * W;
+        hipLaunchKernelGGL((strip_keepv_kernel<R, GEN>), dim3(blocks), dim3(256), 0, s, ucur + o,
+                           uprev + o, uout + o, vout + o, mask + o, H, W, nstrip, per_img,
+                           per_img * n, a);
+    });
 }
 
 template <int R>
@@ -405,11 +410,11 @@ static hipError_t launch_blur_r(const float *u, float *v, int B, int H, int W, c
 {
     const int nbx = (W + tile_cols(kBlurTW) - 1) / tile_cols(kBlurTW);
     const int nby = (H + kBlurTH - 1) / kBlurTH;
-    const long long ntiles = (long long)nbx * nby * B;
-    if (ntiles <= 0 || ntiles > 0x7fffffffLL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((blur_kernel<R>), dim3((unsigned)ntiles), dim3(256), 0, s, u, v, H, W, nbx,
-                       nbx * nby, a);
-    return hipGetLastError();
+    return launch_batches(B, (long long)nbx * nby, 1, 256, [&](int b0, int, unsigned blocks) {
+        const size_t o = (size_t)b0 * H * W;
+        hipLaunchKernelGGL((blur_kernel<R>), dim3(blocks), dim3(256), 0, s, u + o, v + o, H, W, nbx,
+                           nbx * nby, a);
+    });
 }
 
 template <int R, int TW, int TH, bool GEN = false>
@@ -419,16 +424,18 @@ static hipError_t launch_step_t(const float *ucur, const float *uprev, float *uo
 {
     const int nbx = (W + tile_cols(TW) - 1) / tile_cols(TW), nby = (H + TH - 1) / TH;
     const int tpi = nbx * nby;
-    const long long ntiles = (long long)tpi * B;
-    if (ntiles <= 0 || ntiles > 0x7fffffffLL) return hipErrorInvalidValue;
-    const dim3 g((unsigned)ntiles), b(256);
-    if (ref)
-        hipLaunchKernelGGL((step_kernel<R, TW, TH, true, GEN, false>), g, b, 0, s, ucur, uprev, uout,
-                           ref, mask, H, W, nbx, tpi, a, partials, nullptr);
-    else
-        hipLaunchKernelGGL((step_kernel<R, TW, TH, false, GEN, false>), g, b, 0, s, ucur, uprev,
-                           uout, nullptr, mask, H, W, nbx, tpi, a, nullptr, nullptr);
-    return hipGetLastError();
+    return launch_batches(B, tpi, 1, 256, [&](int b0, int, unsigned blocks) {
+        const size_t o = (size_t)b0 * H * W;
+        const dim3 g(blocks), b(256);
+        if (ref)
+            hipLaunchKernelGGL((step_kernel<R, TW, TH, true, GEN, false>), g, b, 0, s, ucur + o,
+                               uprev + o, uout + o, ref + o, mask + o, H, W, nbx, tpi, a,
+                               partials + 2 * (size_t)b0 * tpi, nullptr);
+        else
+            hipLaunchKernelGGL((step_kernel<R, TW, TH, false, GEN, false>), g, b, 0, s, ucur + o,
+                               uprev + o, uout + o, nullptr, mask + o, H, W, nbx, tpi, a, nullptr,
+                               nullptr);
+    });
 }
 
 template <int R, int TW, int TH, bool GEN>
@@ -437,12 +444,12 @@ static hipError_t launch_keepv_tile(const float *ucur, const float *uprev, float
                                     hipStream_t s)
 {
     const int nbx = (W + tile_cols(TW) - 1) / tile_cols(TW), nby = (H + TH - 1) / TH;
-    const long long ntiles = (long long)nbx * nby * B;
-    if (ntiles <= 0 || ntiles > 0x7fffffffLL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((step_kernel<R, TW, TH, false, GEN, true>), dim3((unsigned)ntiles), dim3(256),
-                       0, s, ucur, uprev, uout, nullptr, mask, H, W, nbx, nbx * nby, a, nullptr,
-                       vout);
-    return hipGetLastError();
+    return launch_batches(B, (long long)nbx * nby, 1, 256, [&](int b0, int, unsigned blocks) {
+        const size_t o = (size_t)b0 * H * W;
+        hipLaunchKernelGGL((step_kernel<R, TW, TH, false, GEN, true>), dim3(blocks), dim3(256), 0, s,
+                           ucur + o, uprev + o, uout + o, nullptr, mask + o, H, W, nbx, nbx * nby, a,
+                           nullptr, vout + o);
+    });
 }
 
 template <int R>
@@ -545,8 +552,10 @@ hipError_t launch_blur(int R, const float *u, float *v, int B, int H, int W, con
 hipError_t launch_reduce(const double *partials, int tiles_per_img, int B, double *sums,
                          hipStream_t s)
 {
-    hipLaunchKernelGGL(reduce_kernel, dim3(B), dim3(1024), 0, s, partials, tiles_per_img, sums);
-    return hipGetLastError();
+    return launch_batches(B, 1, 1, 1024, [&](int b0, int, unsigned blocks) {
+        hipLaunchKernelGGL(reduce_kernel, dim3(blocks), dim3(1024), 0, s,
+                           partials + 2 * (size_t)b0 * tiles_per_img, tiles_per_img, sums + 2 * (size_t)b0);
+    });
 }
 
 }  // namespace eed4

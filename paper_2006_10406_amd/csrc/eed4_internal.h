@@ -86,6 +86,29 @@ constexpr bool is_pair(int shape)
 }
 constexpr int strip_width(int shape) { return is_pair(shape) ? 124 : 60; }
 
+// Workgroups of `threads` threads one launch can have.  The runtime multiplies grid
+// and block in 32 bits: it refuses 2^32 threads and silently runs the remainder
+// beyond (2^24 + 1 workgroups of 256 run as one).
+constexpr long long max_blocks(int threads) { return 0xffffffffLL / threads; }
+
+// Launches over B images of `items` work items each, `per_block` items to a
+// workgroup, in as few launches as max_blocks allows (one, short of millions of
+// images): launch(b0, n, blocks) enqueues images b0 .. b0 + n - 1.
+template <typename Launch>
+hipError_t launch_batches(int B, long long items, int per_block, int threads, Launch &&launch)
+{
+    if (items <= 0 || B <= 0) return hipErrorInvalidValue;
+    const long long most = max_blocks(threads) * per_block / items;    // images to a launch
+    if (most < 1) return hipErrorInvalidValue;
+    for (long long b0 = 0; b0 < B; b0 += most) {
+        const int n = (int)(B - b0 < most ? B - b0 : most);
+        launch((int)b0, n, (unsigned)((n * items + per_block - 1) / per_block));
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 // ---- launchers (eed4_forward.hip) ----
 hipError_t launch_hold(float *u, const uint8_t *mask, const float *known, size_t n,
                        hipStream_t s);
