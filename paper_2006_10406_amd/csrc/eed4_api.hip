@@ -377,10 +377,9 @@ int default_step_shape(int R, int B, int H, int W)
 
 // Times the inner steps of every candidate shape (tune_candidates) and remembers
 // the fastest for this problem size.  A step reads u^k = S (not modified) and
-// u^{k-1} = X and writes X, three planes as in a run; the first of every
-// kTuneLaunches is step 0, S -> X.  (Timed on step 0 alone, which reads one
-// plane less, the 28-row strips were chosen at 2900^2, R = 6, though the default
-// is 5 % faster there in a run.)
+// u^{k-1} = X and writes X, three planes as in a run; the first is step 0, S -> X.
+// (Timed on step 0 alone, which reads one plane less, the 28-row strips were
+// chosen at 2900^2, R = 6, though the default is 5 % faster there in a run.)
 int tune_single_step(const eed4_params *p, int B, int H, int W, float *S, float *X,
                      const uint8_t *mask, hipStream_t s, int *shape)
 {
@@ -388,7 +387,7 @@ int tune_single_step(const eed4_params *p, int B, int H, int W, float *S, float 
     const int R = eed4_radius(p->sigma);
     const StepArgs a0 = make_args(p->sigma, R, p->tau, p->lambda, 0);
     const StepArgs a1 = make_args(p->sigma, R, p->tau, p->lambda, 1);
-    unsigned launched = 0;
+    bool started = false;
     int order[kNumShapes];
     const int first = default_step_shape(R, B, H, W);
     const int nc = tune_candidates(first, order);
@@ -397,7 +396,8 @@ int tune_single_step(const eed4_params *p, int B, int H, int W, float *S, float 
     const int rc = tune_pick(
         order, nc, s, [](int) { return (int)EED4_OK; },
         [&](int sh, hipStream_t q) {
-            const bool head = launched++ % kTuneLaunches == 0;
+            const bool head = !started;
+            started = true;
             return launch_step(R, sh, S, head ? S : X, X, nullptr, mask, B, H, W, head ? a0 : a1,
                                nullptr, q);
         },

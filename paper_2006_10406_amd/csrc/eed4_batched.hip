@@ -514,7 +514,7 @@ static std::string batch_tune_key(const eed4_image *im, int B, int R)
 }
 
 // Times the inner steps of every shape on the batch (as tune_single_step: u^k = S,
-// unchanged, u^{k-1} = X, out X; the first of a graph S -> X).
+// unchanged, u^{k-1} = X, out X; the first S -> X).
 static int autotune(const eed4_image *im, int B, const eed4_params *p, char *base,
                     const BatchLayout &L, hipStream_t s, int *best_shape, float *best_ms)
 {
@@ -522,7 +522,7 @@ static int autotune(const eed4_image *im, int B, const eed4_params *p, char *bas
     tune_order(kShapeStrip, order);
     BatchRun r;
     StepArgs a0, a1;
-    unsigned launched = 0;
+    bool started = false;
     return tune_pick(
         order, kNumShapes, s,
         [&](int sh) {
@@ -533,7 +533,8 @@ static int autotune(const eed4_image *im, int B, const eed4_params *p, char *bas
             return rc;
         },
         [&](int sh, hipStream_t q) {
-            const bool head = launched++ % kTuneLaunches == 0;
+            const bool head = !started;
+            started = true;
             return launch_bstep(r.R, sh, r.grid, r.dimg, r.dqueue, r.dqlen, 0, head ? 0 : 1, 1,
                                 r.ih, false, head ? a0 : a1, r.dpartials, q);
         },

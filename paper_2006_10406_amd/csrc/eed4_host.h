@@ -6,6 +6,7 @@
 
 #include <rocprofiler-sdk-roctx/roctx.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <functional>
@@ -119,16 +120,20 @@ int capture_graph(const std::function<int(hipStream_t)> &enqueue, hipGraphExec_t
 
 // Chooses one of n candidate shapes (cands[0] the default) by timing on stream
 // s.  prepare(shape) sets up a candidate outside the timed region (EED4 code);
-// launch(shape, stream) enqueues one launch of it.  A candidate is timed as it
-// will run, as kTuneLaunches launches replayed from one graph: launched one by
-// one from the host, kernels of less than about 5 us all take as long as the
-// host needs to launch them, and the choice between them is noise (16 x 256^2
-// got a shape 20 % slower than the best that way).  Every candidate is sampled
-// in two round-robin passes of one warm-up and two timed samples and keeps its
-// fastest sample, so the clock ramp at the start of tuning does not favour the
-// candidates timed later.  A candidate replaces the current choice only
-// when it is faster by more than kTuneMargin (or its own entry of margins).
-constexpr int kTuneLaunches = 8;
+// launch(shape, stream) enqueues one launch of it.  A caller who solves a size
+// once pays for all of this, so it takes few launches:
+//  - A sample is some untimed work, which keeps the GPU busy while the host
+//    queues the rest, and then the timed launches: about 100 us of them, at most
+//    four, launched directly; or, where the default's launch takes less than
+//    kTuneGraphUs, about 40 us of them replayed from a graph, as they will run
+//    (launched one by one, kernels of less than about 5 us all take as long as the
+//    host needs to launch them: 16 x 256^2 got a shape 20 % slower than the best).
+//  - Every candidate gets one sample, those within 30 % of the fastest a second
+//    and those within 6 % a third, in round-robin passes, and keeps its fastest,
+//    so the clock ramp at the start does not favour the candidates timed later.
+// A candidate replaces the current choice only when it is faster by more than
+// kTuneMargin (or its own entry of margins).
+constexpr float kTuneGraphUs = 12.0f;
 template <typename Prepare, typename Launch>
 int tune_pick(const int *cands, int n, hipStream_t s, Prepare &&prepare, Launch &&launch,
               const char *where, int *best, float *best_ms, const float *margins = nullptr)
@@ -140,13 +145,38 @@ int tune_pick(const int *cands, int n, hipStream_t s, Prepare &&prepare, Launch 
     float tmin[kNumShapes];
     for (int i = 0; i < n; ++i) tmin[i] = 1e30f;
     int rc = EED4_OK;
-    for (int pass = 0; pass < 2 && e == hipSuccess && rc == EED4_OK; ++pass)
+    // ms of `count` launches of candidate i (of its graph where it has one)
+    auto sample = [&](int i, int count) -> float {
+        auto enqueue = [&](int c) {
+            if (exec[i]) return hipGraphLaunch(exec[i], s);
+            hipError_t le = hipSuccess;
+            for (int l = 0; l < c && le == hipSuccess; ++l) le = launch(cands[i], s);
+            return le;
+        };
+        float ms = 0.0f;
+        e = enqueue(1);
+        if (e == hipSuccess) e = hipEventRecord(e0, s);
+        if (e == hipSuccess) e = enqueue(count);
+        if (e == hipSuccess) e = hipEventRecord(e1, s);
+        if (e == hipSuccess) e = hipEventSynchronize(e1);
+        if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
+        return ms;
+    };
+    float us = 0.0f;                                     // a launch of the default
+    if (e == hipSuccess && (rc = prepare(cands[0])) == EED4_OK) us = std::fmax(500.0f * sample(0, 2), 1.0f);
+    const bool graph = us < kTuneGraphUs;
+    const int count = graph ? (int)std::fmin(8.0f, std::ceil(40.0f / us))
+                            : (int)std::fmin(4.0f, std::ceil(100.0f / us));
+    for (int pass = 0; pass < 3 && e == hipSuccess && rc == EED4_OK; ++pass) {
+        constexpr float kWithin[3] = {1e30f, 1.3f, 1.06f};
+        const float limit = kWithin[pass] * *std::min_element(tmin, tmin + n);
         for (int i = 0; i < n && e == hipSuccess && rc == EED4_OK; ++i) {
+            if (pass > 0 && i > 0 && tmin[i] > limit) continue;      // the default stays in
             if ((rc = prepare(cands[i])) != EED4_OK) break;
-            if (!exec[i]) {
+            if (graph && !exec[i]) {
                 rc = capture_graph(
                     [&](hipStream_t cs) {
-                        for (int l = 0; l < kTuneLaunches; ++l) {
+                        for (int l = 0; l < count; ++l) {
                             const hipError_t le = launch(cands[i], cs);
                             if (le != hipSuccess) return hip_fail(le, where);
                         }
@@ -155,19 +185,10 @@ int tune_pick(const int *cands, int n, hipStream_t s, Prepare &&prepare, Launch 
                     &exec[i]);
                 if (rc != EED4_OK) break;
             }
-            for (int rep = 0; rep < 3 && e == hipSuccess; ++rep) {
-                // the replay ahead of the first event keeps the GPU busy while
-                // the host queues the timed ones
-                e = hipGraphLaunch(exec[i], s);
-                if (e == hipSuccess) e = hipEventRecord(e0, s);
-                for (int l = 0; l < 2 && e == hipSuccess; ++l) e = hipGraphLaunch(exec[i], s);
-                if (e == hipSuccess) e = hipEventRecord(e1, s);
-                if (e == hipSuccess) e = hipEventSynchronize(e1);
-                float ms = 0.0f;
-                if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
-                if (e == hipSuccess && rep > 0) tmin[i] = std::fmin(tmin[i], ms);
-            }
+            const float ms = sample(i, count);
+            if (e == hipSuccess) tmin[i] = std::fmin(tmin[i], ms);
         }
+    }
     if (rc != EED4_OK || e != hipSuccess) (void)hipStreamSynchronize(s);
     for (int i = 0; i < n; ++i)
         if (exec[i]) (void)hipGraphExecDestroy(exec[i]);
@@ -179,7 +200,7 @@ int tune_pick(const int *cands, int n, hipStream_t s, Prepare &&prepare, Launch 
     for (int i = 1; i < n; ++i)
         if (tmin[i] < (margins ? margins[i] : kTuneMargin) * tmin[b]) b = i;
     *best = cands[b];
-    if (best_ms) *best_ms = tmin[b];
+    if (best_ms) *best_ms = tmin[b] / count;
     return EED4_OK;
 }
 

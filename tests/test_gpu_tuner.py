@@ -1,0 +1,50 @@
+"""What the first call at a size pays for the choice of its kernels."""
+import time
+
+import pytest
+
+from synth import make_problem
+from tests.helpers import announce, to_dev
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("needs a GPU", allow_module_level=True)
+import paper_2006_10406_amd as eed4  # noqa: E402
+
+
+def ms(f):
+    torch.cuda.synchronize()
+    t = time.perf_counter()
+    f()
+    torch.cuda.synchronize()
+    return 1e3 * (time.perf_counter() - t)
+
+
+def test_first_call_costs_few_steps():
+    # 7 forward and 7 reverse candidates, timed in at most 3 samples of 5 launches, the slower
+    # ones in one: under 7 * 5 * 2 = 70 launches if all were as fast as the best; 200 leave room
+    # for candidates several times slower, and 2 ms for the host's part
+    pr = make_problem(1500, 1900, 20, True, 0.01, 0.05, 900)
+    u0, mask, known = (to_dev(pr[k]) for k in ("u_init", "mask", "known"))
+    n, M = 10, 4
+    u, gu = u0.clone(), torch.ones_like(u0)
+    ck = torch.empty((M,) + u.shape, device="cuda")
+    g = [torch.empty_like(u), torch.empty_like(u), torch.empty(1, device="cuda")]
+
+    def forward(flags=0):
+        eed4.eed4_inpaint(u.copy_(u0), mask, known, eed4.params(0.03, 2.0, 0.05, n, M, flags=flags), ckpt=ck)
+
+    def backward(flags=0):
+        eed4.eed4_backward(ck, mask, known, eed4.params(0.03, 2.0, 0.05, n, M, flags=flags), M, gu, *g)
+
+    announce("first call at 1500x1900, R = 6")
+    for s in range(11):                 # load every kernel; a forced shape does not tune
+        forward(eed4.EED4_FORCE_SHAPE(s))
+        backward(eed4.EED4_FORCE_SHAPE(s))
+    for f in (forward, backward):
+        first, rest = ms(f), min(ms(f) for _ in range(5))
+        step = rest / (n * M)
+        print(f"{f.__name__}: first {first:.2f} ms, then {rest:.2f} ms, a step {1e3 * step:.1f} us")
+        assert first - rest < 200 * step + 2.0
