@@ -81,7 +81,8 @@ extern "C" {
  * 0: 64x32 workgroup tiles (64 lanes, of which 60 output columns, by 32 rows),
  * 1: 64x16 tiles, 2: 32x32 tiles (28 output columns), 3: wave strips of 124
  * columns (two per lane) x 28 to 136 rows, the height that fills the chip most
- * evenly for the problem size, 4: 124-column strips of 136 rows, 5: strips of
+ * evenly for the problem size, or of 60 columns x >= 64 rows where those cover the
+ * images' widths better, 4: 124-column strips of 136 rows, 5: strips of
  * 60 columns x >= 28 rows, 6: of 60 columns x >= 8 rows, 7: 124-column strips of
  * 64 rows, 8: of 28 rows, 9: 32x16 tiles, 10: 16x16 tiles.
  * Every shape forms each value with the same operations in the same order, so

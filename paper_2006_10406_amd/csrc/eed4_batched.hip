@@ -232,8 +232,9 @@ __global__ __launch_bounds__(256) void bhold_kernel(const BImage *imgs, int per)
 
 // ---------------------------------------------------------------- host side
 
-// item size of a shape in pixels, for a batch of these images
-static void item_dims(int shape, int R, int B, const eed4_image *im, int *iw, int *ih)
+// Item size of a shape in pixels, for a batch of these images.  Returns the shape
+// that runs (fit_strip_shape's).
+static int item_dims(int shape, int R, int B, const eed4_image *im, int *iw, int *ih)
 {
     if (is_strip(shape)) {
         std::vector<int> H(B), W(B);
@@ -241,12 +242,14 @@ static void item_dims(int shape, int R, int B, const eed4_image *im, int *iw, in
             H[i] = im[i].H;
             W[i] = im[i].W;
         }
+        shape = fit_strip_shape(shape, B, H.data(), W.data());
         *iw = strip_width(shape);
         *ih = strip_rows(R, shape, B, H.data(), W.data(), 1);
-        return;
+        return shape;
     }
     *iw = tile_cols(kTileShapes[tile_index(shape)].tw);
     *ih = kTileShapes[tile_index(shape)].th;
+    return shape;
 }
 
 static long long items_of(const eed4_image &im, int iw, int ih)
@@ -286,6 +289,7 @@ static hipError_t launch_bstep_r(int shape, int grid, const BImage *imgs, const 
     case 2: EED4_BTILE(32, 32); break;
     case kShapeStripShort: EED4_BSTRIP(28); break;
     case kShapeStripTiny: EED4_BSTRIP(8); break;
+    case kShapeStripNarrow: EED4_BSTRIP(64); break;
     case kShapeStrip: case kShapeStripTall: case kShapeStripWide: case kShapeStripWideShort:
         if (res)
             hipLaunchKernelGGL((bpair_kernel<R, true>), g, b, 0, s, imgs, queue, qlen, sc, sp, so,
@@ -411,11 +415,10 @@ static int prepare(BatchRun &r, const eed4_image *im, int B, const eed4_params *
                    char *base, const BatchLayout &L, hipStream_t s)
 {
     r.R = eed4_radius(p->sigma);
-    r.shape = shape;
     r.n = p->cycle_len;
     r.B = B;
     r.p = p;
-    item_dims(shape, r.R, B, im, &r.iw, &r.ih);
+    r.shape = item_dims(shape, r.R, B, im, &r.iw, &r.ih);
     r.himg.resize(B);
     r.slot0.resize(B);
     r.nslot.resize(B);
@@ -532,10 +535,10 @@ static int autotune(const eed4_image *im, int B, const eed4_params *p, char *bas
             a1 = make_args(p->sigma, r.R, p->tau, 1.0f, 1);
             return rc;
         },
-        [&](int sh, hipStream_t q) {
+        [&](int, hipStream_t q) {
             const bool head = !started;
             started = true;
-            return launch_bstep(r.R, sh, r.grid, r.dimg, r.dqueue, r.dqlen, 0, head ? 0 : 1, 1,
+            return launch_bstep(r.R, r.shape, r.grid, r.dimg, r.dqueue, r.dqlen, 0, head ? 0 : 1, 1,
                                 r.ih, false, head ? a0 : a1, r.dpartials, q);
         },
         "autotune timing", best_shape, best_ms);

@@ -153,14 +153,14 @@ __global__ __launch_bounds__(256) void strip_model_kernel(const float *ucur, con
 // The step of the adjoint's forward recompute: u^{k+1} as strip_kernel (or
 // strip_model_kernel when GEN) computes it, and K_sigma * u^k for the reverse
 // step.
-template <int R, bool GEN>
+template <int R, int ROWS, bool GEN>
 __global__ __launch_bounds__(256) void strip_keepv_kernel(const float *ucur, const float *uprev,
                                                           float *uout, float *vout,
                                                           const uint8_t *__restrict__ mask, int H,
                                                           int W, int nstrip, int per_img,
                                                           int nitems, StepArgs a)
 {
-    strip_kernel_body<R, false, 28, GEN, true>(ucur, uprev, uout, nullptr, mask, H, W, nstrip,
+    strip_kernel_body<R, false, ROWS, GEN, true>(ucur, uprev, uout, nullptr, mask, H, W, nstrip,
                                                per_img, nitems, a, nullptr, vout);
 }
 
@@ -297,7 +297,9 @@ int strip_rows(int R, int shape, int B, const int *H, const int *W, int copies)
     }
     switch (R) {
 #define EED4_CASE(r) \
-    case r: return shape == kShapeStripShort ? StripGeo<r, 28>::OH : StripGeo<r, 8>::OH;
+    case r: return shape == kShapeStripNarrow  ? StripGeo<r, 64>::OH \
+                   : shape == kShapeStripShort ? StripGeo<r, 28>::OH \
+                                               : StripGeo<r, 8>::OH;
         EED4_CASE(0) EED4_CASE(1) EED4_CASE(2) EED4_CASE(3) EED4_CASE(4)
         EED4_CASE(5) EED4_CASE(6) EED4_CASE(7) EED4_CASE(8)
 #undef EED4_CASE
@@ -305,8 +307,29 @@ int strip_rows(int R, int shape, int B, const int *H, const int *W, int copies)
     }
 }
 
+// Shape 3 runs strips of 124 columns unless those of 60, whose lanes each take one
+// column, cover the images' widths with a sixth fewer columns in all, or the images
+// are at most 64 wide (one wave of 124 columns would be half empty, and all of it at
+// the border).  R = 3 / R = 8, us a step, 124 columns against 60: 500 x 128^2 35.7
+// and 29.8 / 46.2 and 36.6, 131072x130 37.7 and 28.7 / 45.8 and 37.9, 40000x250 33.6
+// and 29.7 / 44.1 and 42.1, 4000 x 48^2 46.9 and 28.3 / 66.9 and 42.4, 2000 x 64^2 37.3
+// and 34.8 / 46.6 and 43.4.  Where the 60 columns save less they are mostly slower:
+// 16000x380 (15 % fewer) 23.1 and 23.5 / 29.6 and 29.7, 2300x2900 20.3 and 23.5 / 28.1
+// and 29.7, 4096^2 40.6 and 42.1 / 51.7 and 53.5.
+int fit_strip_shape(int shape, int B, const int *H, const int *W)
+{
+    if (shape != kShapeStrip) return shape;
+    double narrow = 0.0, wide = 0.0;                      // columns covered, times rows
+    for (int i = 0; i < B; ++i) {
+        narrow += (W[i] <= 64 ? 1.0 : 1.2) * H[i] * ((W[i] + 59) / 60 * 60);
+        wide += (double)H[i] * ((W[i] + 123) / 124 * 124);
+    }
+    return narrow <= wide ? kShapeStripNarrow : shape;
+}
+
 int tiles_per_image(int shape, int R, int B, int H, int W)
 {
+    shape = fit_strip_shape(shape, 1, &H, &W);
     if (is_strip(shape)) {
         const int oh = strip_rows(R, shape, 1, &H, &W, B), sw = strip_width(shape);
         if (oh <= 0) return 0;
@@ -388,17 +411,17 @@ static hipError_t launch_pair_r(int shape, const float *ucur, const float *uprev
     });
 }
 
-template <int R, bool GEN>
+template <int R, int ROWS, bool GEN>
 static hipError_t launch_keepv_t(const float *ucur, const float *uprev, float *uout, float *vout,
                                  const uint8_t *mask, int B, int H, int W, const StepArgs &a,
                                  hipStream_t s)
 {
-    using G = StripGeo<R, 28>;
+    using G = StripGeo<R, ROWS>;
     const int nstrip = (W + G::SW - 1) / G::SW;
     const int per_img = nstrip * ((H + G::OH - 1) / G::OH);
     return launch_batches(B, per_img, 4, 256, [&](int b0, int n, unsigned blocks) {
         const size_t o = (size_t)b0 * H * W;
-        hipLaunchKernelGGL((strip_keepv_kernel<R, GEN>), dim3(blocks), dim3(256), 0, s, ucur + o,
+        hipLaunchKernelGGL((strip_keepv_kernel<R, ROWS, GEN>), dim3(blocks), dim3(256), 0, s, ucur + o,
                            uprev + o, uout + o, vout + o, mask + o, H, W, nstrip, per_img,
                            per_img * n, a);
     });
@@ -471,6 +494,7 @@ static hipError_t launch_step_r(int shape, const float *ucur, const float *uprev
     case 2: return launch_step_t<R, 32, 32>(ucur, uprev, uout, ref, mask, B, H, W, a, partials, s);
     case kShapeStripShort: return launch_strip_t<R, 28>(ucur, uprev, uout, ref, mask, B, H, W, a, partials, s);
     case kShapeStripTiny: return launch_strip_t<R, 8>(ucur, uprev, uout, ref, mask, B, H, W, a, partials, s);
+    case kShapeStripNarrow: return launch_strip_t<R, 64>(ucur, uprev, uout, ref, mask, B, H, W, a, partials, s);
     case kShapeStrip: case kShapeStripTall: case kShapeStripWide: case kShapeStripWideShort:
         return launch_pair_r<R>(shape, ucur, uprev, uout, ref, nullptr, mask, B, H, W, a, partials, s);
     case kShapeTile32x16: return launch_step_t<R, 32, 16>(ucur, uprev, uout, ref, mask, B, H, W, a, partials, s);
@@ -493,7 +517,11 @@ static hipError_t launch_keepv_r(int shape, const float *ucur, const float *upre
     switch (shape) {
     case 0: return launch_keepv_tile<R, 64, 32, GEN>(ucur, uprev, uout, vout, mask, B, H, W, a, s);
     case kShapeStripShort:
-        return launch_keepv_t<R, GEN>(ucur, uprev, uout, vout, mask, B, H, W, a, s);
+        return launch_keepv_t<R, 28, GEN>(ucur, uprev, uout, vout, mask, B, H, W, a, s);
+    case kShapeStripNarrow:
+        if constexpr (!GEN)
+            return launch_keepv_t<R, 64, false>(ucur, uprev, uout, vout, mask, B, H, W, a, s);
+        return hipErrorInvalidValue;
     case kShapeStrip: case kShapeStripTall: case kShapeStripWide: case kShapeStripWideShort:
         if constexpr (!GEN)
             return launch_pair_r<R>(shape, ucur, uprev, uout, nullptr, vout, mask, B, H, W, a,
@@ -510,6 +538,7 @@ hipError_t launch_step(int R, int shape, const float *ucur, const float *uprev, 
                        const float *ref, const uint8_t *mask, int B, int H, int W,
                        const StepArgs &a, double *partials, hipStream_t s)
 {
+    shape = fit_strip_shape(shape, 1, &H, &W);
     switch (R) {
 #define EED4_CASE(r) \
     case r: return launch_step_r<r>(shape, ucur, uprev, uout, ref, mask, B, H, W, a, partials, s);
@@ -524,6 +553,7 @@ hipError_t launch_step_keepv(int R, int shape, const float *ucur, const float *u
                              float *uout, float *vout, const uint8_t *mask, int B, int H, int W,
                              const StepArgs &a, hipStream_t s)
 {
+    shape = fit_strip_shape(shape, 1, &H, &W);
     switch (R) {
 #define EED4_CASE(r) \
     case r:                                                                                   \

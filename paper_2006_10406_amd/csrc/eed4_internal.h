@@ -62,13 +62,13 @@ constexpr int tile_cols(int tw) { return tw - 4; }
 
 // Kernel shapes compiled into the library (index = config id): 0..2 and
 // 9..10 are workgroup tiles (tw - 4 columns x th rows per 256 threads);
-// 3..8 are wave strips: 3, 4, 7 and 8 of 124 columns (eed4_pair.h), 5 and 6 of
-// 60 (eed4_strip.h), by a segment of rows per wave.  The
+// 3..8 are wave strips: 3, 4, 7 and 8 of 124 columns (eed4_pair.h), 5 and 6 (and
+// 3 on narrow images) of 60 (eed4_strip.h), by a segment of rows per wave.  The
 // small tiles (9, 10) give images of a few hundred pixels a side more
 // workgroups than the chip has CUs.
 constexpr int kNumTileShapes = 5;
 constexpr TileShape kTileShapes[kNumTileShapes] = {{64, 32}, {64, 16}, {32, 32}, {32, 16}, {16, 16}};
-constexpr int kShapeStrip = 3;           // segment height by fit_strip_rows
+constexpr int kShapeStrip = 3;           // height by fit_strip_rows, or kShapeStripNarrow
 constexpr int kShapeStripTall = 4;       // 136 rows
 constexpr int kShapeStripShort = 5;      // >= 28 rows (more waves for small images)
 constexpr int kShapeStripTiny = 6;       // >= 8 rows (shortest row pipeline per wave)
@@ -77,12 +77,19 @@ constexpr int kShapeStripWideShort = 8;  // 28 rows
 constexpr int kShapeTile32x16 = 9;
 constexpr int kShapeTile16x16 = 10;
 constexpr int kNumShapes = 11;
-constexpr bool is_strip(int shape) { return shape >= kShapeStrip && shape <= kShapeStripWideShort; }
+// What shape 3 runs where 60 columns fill the images' widths better than 124
+// (fit_strip_shape): 60 columns x >= 64 rows.  Not a public id.
+constexpr int kShapeStripNarrow = kNumShapes;
+constexpr bool is_strip(int shape)
+{
+    return (shape >= kShapeStrip && shape <= kShapeStripWideShort) || shape == kShapeStripNarrow;
+}
 // index into kTileShapes of a tile shape
 constexpr int tile_index(int shape) { return shape < kShapeStrip ? shape : shape - 6; }
 constexpr bool is_pair(int shape)
 {
-    return is_strip(shape) && shape != kShapeStripShort && shape != kShapeStripTiny;
+    return is_strip(shape) && shape != kShapeStripShort && shape != kShapeStripTiny &&
+           shape != kShapeStripNarrow;
 }
 constexpr int strip_width(int shape) { return is_pair(shape) ? 124 : 60; }
 
@@ -128,6 +135,8 @@ hipError_t launch_reduce(const double *partials, int tiles_per_img, int B, doubl
 // residual partials per image of a launch over B images of H x W
 int tiles_per_image(int shape, int R, int B, int H, int W);
 int variant_shape(int R, int B, int H, int W);        // kernel shape of a tensor variant
+// shape, or kShapeStripNarrow in the place of kShapeStrip, for B images of H[i] x W[i]
+int fit_strip_shape(int shape, int B, const int *H, const int *W);
 // output rows per strip segment in a launch over B images of the sizes
 // (H[i], W[i]) with `copies` copies of each
 int strip_rows(int R, int shape, int B, const int *H, const int *W, int copies);

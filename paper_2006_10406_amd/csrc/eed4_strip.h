@@ -1,6 +1,7 @@
 // Device code of one fused FOEED/FSI inner step on a vertical strip, one
-// wavefront per strip, no workgroup barriers (the short segments and the tensor
-// variants; eed4_pair.h has the tall ones).
+// wavefront per strip, no workgroup barriers (the short segments, images whose
+// width 60 columns fill better than 124, and the tensor variants; eed4_pair.h has
+// the wide and tall ones).
 //
 // A wave owns 64 consecutive columns c = X0-2 .. X0+61, one per lane, and
 // streams down the rows of a segment.  For each input row y it
@@ -322,6 +323,17 @@ __device__ __forceinline__ void strip_step(float *ring, const StripArgs &s,
     prefetch(r0);
     prefetch(r1);
 
+    // The Hessian of u at row g needs u(x-1), u(x), u(x+1) at rows g-1, g, g+1.
+    // Segments of >= 64 rows (about 4 waves a SIMD, registers to spare) keep them
+    // per staged row, as u(x), u(x-1) + u(x+1) and u(x+1) - u(x-1), in registers
+    // indexed like the ring (slot i % D), from the x-pass taps R-1, R, R+1 of row i;
+    // the shorter strips, which need 8 waves a SIMD, read them back from the ring.
+    constexpr bool HREG = ROWS >= 64;
+    constexpr int HD = HREG ? D : 1;
+    float hc[HD], hs[HD], hd[HD];
+#pragma unroll
+    for (int j = 0; j < HD; ++j) hc[j] = hs[j] = hd[j] = 0.0f;
+
     // stage one row of u^k into ring row rr and take its x pass into window slot ws
     auto stage_xpass = [&](const StripRow &cur, int rr, int ws) {
         col[rr] = cur.a;
@@ -331,6 +343,12 @@ __device__ __forceinline__ void strip_step(float *ring, const StripArgs &s,
 #pragma unroll
         for (int j = 1; j <= 2 * R; ++j) acc = fmaf(w[j], col[j * CS + rr], acc);
         win[ws] = acc;
+        if constexpr (HREG) {
+            const float l = col[(R - 1) * CS + rr], c = col[R * CS + rr], r = col[(R + 1) * CS + rr];
+            hc[rr] = c;
+            hs[rr] = l + r;
+            hd[rr] = xdiff(l, r);
+        }
     };
 
     // ---- prologue: stage rows 0 .. 2R-1 and their x pass ----
@@ -342,6 +360,11 @@ __device__ __forceinline__ void strip_step(float *ring, const StripArgs &s,
         stage_xpass(cur, i % D, i % P);
     }
 
+    // iterations up to the image's last row (the tall segments end there; a constant
+    // bound with an early exit: with a variable bound the compiler took up to 275
+    // registers)
+    const int below = H - s.Y0;
+    const int M = HREG && below < G::OH ? (below + 4 + U - 1) / U : G::M;
 #pragma unroll 1
     for (int it = 0; it < G::M; ++it) {
         // Issue priority falls as the wave moves down its segment, so waves
@@ -353,7 +376,7 @@ __device__ __forceinline__ void strip_step(float *ring, const StripArgs &s,
         // The adjoint's recompute steps (VST) stay at the lowest priority: they
         // run beside the reverse steps, which are the critical path.
         if constexpr (!VST) {
-            const int left = G::M - it;
+            const int left = M - it;
             if (left >= 4) __builtin_amdgcn_s_setprio(3);
             else if (left == 3) __builtin_amdgcn_s_setprio(2);
             else if (left == 2) __builtin_amdgcn_s_setprio(1);
@@ -381,13 +404,21 @@ __device__ __forceinline__ void strip_step(float *ring, const StripArgs &s,
             // rows g-1, g, g+1 are in ring slots sm, sg, sp; this lane's column
             // is staged column l + R
             const int sm = (R - 2 + ph + D) % D, sg = (R - 1 + ph + D) % D, sp = (R + ph) % D;
-            const float *um = col + R * CS + sm;
-            const float *u0 = col + R * CS + sg;
-            const float *up = col + R * CS + sp;
-            const float uc = u0[0];
-            const float hxx = second_diff(u0[-CS], uc, u0[CS]);
-            const float hyy = second_diff(um[0], uc, up[0]);
-            const float hxy = mixed_diff(xdiff(up[-CS], up[CS]), xdiff(um[-CS], um[CS]));
+            float uc, hxx, hyy, hxy;
+            if constexpr (HREG) {
+                uc = hc[sg];
+                hxx = second_diff_sum(hs[sg], uc);
+                hyy = second_diff(hc[sm], uc, hc[sp]);
+                hxy = mixed_diff(hd[sp], hd[sm]);
+            } else {
+                const float *um = col + R * CS + sm;
+                const float *u0 = col + R * CS + sg;
+                const float *up = col + R * CS + sp;
+                uc = u0[0];
+                hxx = second_diff(u0[-CS], uc, u0[CS]);
+                hyy = second_diff(um[0], uc, up[0]);
+                hxy = mixed_diff(xdiff(up[-CS], up[CS]), xdiff(um[-CS], um[CS]));
+            }
 
             const float s2 = grad2_sq(gxs, gys);                              // 4 |grad|^2
             float mu1, mu3;
@@ -427,6 +458,8 @@ __device__ __forceinline__ void strip_step(float *ring, const StripArgs &s,
             z_p = z;
             uc_p = uc;
         }
+        if constexpr (HREG)
+            if (it + 1 == M) break;
     }
     if constexpr (RES) {
         for (int off = 32; off > 0; off >>= 1) {
