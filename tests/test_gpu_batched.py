@@ -159,3 +159,42 @@ def test_tensor_variant_batched_equals_single_images(d, r):
     oref, _, _ = oracle.inpaint(probs[i]["u_init"], probs[i]["mask"], probs[i]["known"], LAMS[i],
                                 sigma, tau, n, M, diff=d, mu3=r)
     assert_steady_parity(outs[i], oref, f"batched variant image {i}")
+
+
+def test_a_large_image_among_thumbnails_costs_its_own_time():
+    # the known set of every image is set in one launch that shares out pixels, not images: the
+    # mixed batch takes about what its parts take (0.9 of them; 1.9 with as many workgroups to a
+    # thumbnail as to the large image)
+    import time
+    announce("batched 4096x4096 + 200 x 64x64, one step")
+    big, small = torch.rand((4096, 4096), device="cuda"), torch.rand((200, 64, 64), device="cuda")
+    image = lambda u: (u.clone(), (u < 0.05).to(torch.uint8), u, 0.03)
+    large, thumbs = [image(big)], [image(u) for u in small]
+    p = eed4.params(0.03, 1.0, 0.05, 1, 1, flags=eed4.EED4_FORCE_SHAPE(3))
+    best = {}
+    for _ in range(12):
+        for name, ims in (("large", large), ("thumbs", thumbs), ("both", large + thumbs)):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            eed4.eed4_inpaint_batched(ims, p)
+            torch.cuda.synchronize()
+            best[name] = min(best.get(name, 1e9), time.perf_counter() - t)
+    print({k: f"{1e6 * v:.0f} us" for k, v in best.items()})
+    assert best["both"] < 1.35 * (best["large"] + best["thumbs"])
+
+
+@pytest.mark.parametrize("shape", [0, 3, 5, 10])
+def test_known_pixels_of_uneven_images_are_set(shape):
+    # u starts at 7 everywhere: after one step every known pixel holds its value
+    announce(f"batched hold, shape {shape}")
+    rng = np.random.default_rng(12)
+    ims = []
+    for h, w in [(1, 1), (5, 300), (300, 5), (137, 249), (64, 64), (17, 125)]:
+        mask = to_dev((rng.random((h, w)) < 0.3).astype(np.uint8))
+        known = to_dev(rng.random((h, w)).astype(np.float32))
+        ims.append((torch.full((h, w), 7.0, device="cuda"), mask, known, 0.03))
+    eed4.eed4_inpaint_batched(ims, eed4.params(0.03, 1.0, 0.05, 1, 1, flags=eed4.EED4_FORCE_SHAPE(shape)))
+    torch.cuda.synchronize()
+    for u, mask, known, _ in ims:
+        m = mask != 0
+        assert torch.equal(u[m], known[m]) and torch.isfinite(u).all()
