@@ -261,7 +261,8 @@ int eed4_inpaint_batched(const eed4_image *imgs, int B, const eed4_params *p,
  * for batches of this kind (radius, image count, size classes) and returns
  * its id (>= 0), or a negative EED4_E* code.  eed4_inpaint_batched runs it by
  * itself on the first call for a kind of batch; with the environment variable
- * EED4_AUTOTUNE_CACHE naming a file, choices persist across processes. */
+ * EED4_AUTOTUNE_CACHE naming a file, choices persist across processes (until the
+ * kernels behind the shape ids change: lines of such a build are kept, not used). */
 int eed4_autotune_batched(const eed4_image *imgs, int B, const eed4_params *p,
                           void *ws, size_t ws_bytes, void *stream);
 

@@ -293,6 +293,10 @@ InpaintLayout inpaint_layout(int op, int B, int H, int W, int R, int M)
 }
 
 // ---- autotuner choice cache ----
+// Keys start with the generation of the kernels, raised when the kernels behind the
+// shape ids change enough for old choices to be wrong: a file from before then
+// keeps its lines, but no problem takes its choice from them.
+constexpr char kTuneGeneration[] = "g2.";
 static std::mutex g_tune_mu;
 static std::map<std::string, int> g_tune;
 static bool g_tune_loaded = false;
@@ -316,7 +320,7 @@ bool tune_lookup(const std::string &key, int *shape)
 {
     std::lock_guard<std::mutex> lk(g_tune_mu);
     tune_load_locked();
-    auto it = g_tune.find(key);
+    auto it = g_tune.find(kTuneGeneration + key);
     if (it == g_tune.end()) return false;
     *shape = it->second;
     return true;
@@ -326,7 +330,7 @@ void tune_remember(const std::string &key, int shape)
 {
     std::lock_guard<std::mutex> lk(g_tune_mu);
     tune_load_locked();
-    g_tune[key] = shape;
+    g_tune[kTuneGeneration + key] = shape;
     const char *path = std::getenv("EED4_AUTOTUNE_CACHE");
     if (!path) return;
     FILE *f = std::fopen(path, "w");

@@ -190,3 +190,21 @@ def test_static_cycle_keeps_its_largest_images(lib):
             # two planes and 181 x 181 partials of 16 bytes, each rounded up to 256, and the sums
             up = lambda x: (x + 255) // 256 * 256
             assert size(2884) == 2 * up(4 * 2884 ** 2) + up(16 * 181 ** 2) + 256
+
+
+def test_saved_choices_of_other_kernels_are_not_used(lib, tmp_path):
+    # a line without the generation of the kernels (the form of the first files) is not a choice
+    # for them, one with it is; eed4_step_shape reads the file without device work
+    import os
+    import subprocess
+    import sys
+    import paper_2006_10406_amd as e
+    f = tmp_path / "choices"
+    f.write_text("single_R3_B1_H40_W30 6\ng2.single_R3_B1_H41_W30 6\n")
+    code = ("import ctypes, paper_2006_10406_amd as e; p = e.params(0.05, 1.0, 0.05, 10, 2); "
+            "print(*(e._lib.lib().eed4_step_shape(1, h, 30, ctypes.byref(p)) for h in (40, 41, 42)))")
+    root = os.path.dirname(os.path.dirname(os.path.abspath(e.__file__)))
+    out = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=300,
+                         cwd=root, env=dict(os.environ, EED4_AUTOTUNE_CACHE=str(f)), check=True)
+    old, new, none = map(int, out.stdout.split()[-3:])
+    assert (old, new) == (none, 6) and none != 6
