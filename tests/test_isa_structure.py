@@ -114,3 +114,26 @@ def test_no_scalar_stores_or_atomics(tmp_path):
     hits = re.findall(r"^\s*(s_store\w*|s_buffer_store\w*|s_atomic\w*|s_buffer_atomic\w*|"
                       r"s_dcache_wb\w*|s_scratch_store\w*)", asm, re.M)
     assert not hits, hits[:5]
+
+
+def test_every_family_of_queue_kernels_exits_uniformly(tmp_path):
+    # as above for all kernels that walk the queue with strips or tiles, every build of each
+    # family present: R = 0..8 by shapes, and with and without the residual for the strips
+    asm = _assembly(tmp_path)
+    want = {"bstrip_kernel": 9 * 3 * 2, "bpair_kernel": 9 * 2, "bstrip_model_kernel": 9 * 2,
+            "btile_kernel": 9 * 5}
+    for family, count in want.items():
+        kernels = re.findall(r"^(_ZN4eed4%d%sI\w+):" % (len(family), family), asm, re.M)
+        assert len(kernels) == count, (family, len(kernels))
+        for k in kernels:
+            i = asm.index(k + ":")
+            raw = asm[i:asm.index(".Lfunc_end", i)].splitlines()
+            ends = {m.group(1) for n, line in enumerate(raw) for m in [re.match(r"^(\.LBB\w+):", line)]
+                    if m and any("s_endpgm" in x for x in raw[n + 1:n + 3])}
+            assert ends, k
+            bad = [x for x in raw if re.search(r"s_cbranch_execz\s+(\.LBB\w+)", x)
+                   and re.search(r"s_cbranch_execz\s+(\.LBB\w+)", x).group(1) in ends]
+            assert not bad, (k, bad)
+            loops, atom_blocks = _loops(asm, k)
+            assert sum(L["depth"] == 1 for L in loops.values()) == 1, (k, dict(loops))
+            assert not atom_blocks, (k, atom_blocks)
