@@ -168,11 +168,19 @@ __device__ __forceinline__ void adjoint_point(float gx, float gy, float inv_lam2
 // Relative L2 error of dL/du_init against FP64, geometric mean of 15 runs of 128^2 to
 // 256^2: 4.01e-7 with the sums, 3.98e-7 so (the output's own rounding is most of it).
 //
-// Second difference along x of a value held by consecutive lanes.
-__device__ __forceinline__ float lane_diff2(float v)
+// First difference along x of a value held by consecutive lanes, and the second
+// difference from it.  Strips, which have one row in hand, carry the first to the
+// next row: a lane shift right after it would wait for the result (28-row strips, five
+// radii: 1.018x the time of the sums so, 1.012x carried; tiles, whose rows interleave,
+// 0.99x without).
+__device__ __forceinline__ float lane_diff(float v)
 {
 #pragma clang fp contract(off)
-    const float f = from_next_lane(v) - v;
+    return from_next_lane(v) - v;
+}
+__device__ __forceinline__ float lane_diff2(float f)
+{
+#pragma clang fp contract(off)
     return f - from_prev_lane(f);
 }
 // P(u) r at a pixel from the second differences xx of T_xx and yy of T_yy (T = D:A)
@@ -326,10 +334,10 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(4))) void a
     for (int t = 0; t < OQ; ++t) {
         const float gxs = from_next_lane(v[t + 1]) - from_prev_lane(v[t + 1]);   // 2 gx
         const float gys = v[t + 2] - v[t];                                       // 2 gy
-        const float hxx = lane_diff2(u[t + 1]);
+        const float hxx = lane_diff2(lane_diff(u[t + 1]));
         const float hyy = (u[t + 2] - u[t + 1]) - (u[t + 1] - u[t]);
         const float hxy = 0.25f * (du[t + 2] - du[t]);
-        const float axx = lane_diff2(r[t + 1]);
+        const float axx = lane_diff2(lane_diff(r[t + 1]));
         const float ayy = (r[t + 2] - r[t + 1]) - (r[t + 1] - r[t]);
         const float axy = 0.25f * (dr[t + 2] - dr[t]);
         float txy, qx, sds;
@@ -379,7 +387,8 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(4))) void a
                 const float tp = t > 0 ? tyy[t > 0 ? t - 1 : 0] : tyu;
                 const float zn = t + 1 < OQ ? z[t + 1 < OQ ? t + 1 : 0] : zd;
                 const float zp = t > 0 ? z[t > 0 ? t - 1 : 0] : zu;
-                sP[o * 64 + lane] = adj_outer(lane_diff2(txx[t]), (tn - tyy[t]) - (tyy[t] - tp), zn, zp);
+                sP[o * 64 + lane] = adj_outer(lane_diff2(lane_diff(txx[t])),
+                                              (tn - tyy[t]) - (tyy[t] - tp), zn, zp);
             }
         }
     }
@@ -538,12 +547,12 @@ __device__ __forceinline__ void adjoint_strip_step(float *lds, const AdjStripArg
 #pragma unroll
     for (int j = 0; j < P; ++j) dwin[j] = 0.0f;
     float v_m1 = 0.0f, v_m2 = 0.0f;                          // v at rows g, g-1
-    // u and r at row g, their differences to row g-1, and along x their second
-    // (row g) and central (rows g, g-1) differences, taken when a row arrives
-    float u_m1 = 0.0f, eu_m1 = 0.0f, hx_m1 = 0.0f, du_m1 = 0.0f, du_m2 = 0.0f;
-    float r_m1 = 0.0f, er_m1 = 0.0f, ax_m1 = 0.0f, dr_m1 = 0.0f, dr_m2 = 0.0f;
-    // (D:A)xx: second x difference at row g-1; (D:A)yy at row g-1, less row g-2
-    float txx_p = 0.0f, tyy_p = 0.0f, ety_p = 0.0f;
+    // u and r at row g, their differences to row g-1, and along x their first (row g)
+    // and central (rows g, g-1) differences, taken when a row arrives
+    float u_m1 = 0.0f, eu_m1 = 0.0f, fu_m1 = 0.0f, du_m1 = 0.0f, du_m2 = 0.0f;
+    float r_m1 = 0.0f, er_m1 = 0.0f, fr_m1 = 0.0f, dr_m1 = 0.0f, dr_m2 = 0.0f;
+    // (D:A)xx: x difference at row g-1; (D:A)yy at row g-1, and less row g-2
+    float ftx_p = 0.0f, tyy_p = 0.0f, ety_p = 0.0f;
     float z_p = 0.0f, z_pp = 0.0f;                           // (D:A)xy(l+1)-(D:A)xy(l-1)
     float qx_p = 0.0f, qy_p = 0.0f, qy_pp = 0.0f;            // q at rows g-1 (g-2 for y)
     float dsum = 0.0f;                                       // de/dlambda over the lane's rows
@@ -624,7 +633,7 @@ __device__ __forceinline__ void adjoint_strip_step(float *lds, const AdjStripArg
             const float du_p1 = from_next_lane(u_p1) - from_prev_lane(u_p1);  // row g+1
             const float dr_p1 = from_next_lane(r_p1) - from_prev_lane(r_p1);
             const float eu_p1 = u_p1 - u_m1, er_p1 = r_p1 - r_m1;
-            const float hxx = hx_m1, axx = ax_m1;
+            const float hxx = lane_diff2(fu_m1), axx = lane_diff2(fr_m1);
             const float hyy = eu_p1 - eu_m1, ayy = er_p1 - er_m1;
             const float hxy = 0.25f * (du_p1 - du_m2);
             const float axy = 0.25f * (dr_p1 - dr_m2);
@@ -632,10 +641,10 @@ __device__ __forceinline__ void adjoint_strip_step(float *lds, const AdjStripArg
             v_m1 = v_p1;
             u_m1 = u_p1;
             eu_m1 = eu_p1;
-            hx_m1 = lane_diff2(u_p1);
+            fu_m1 = lane_diff(u_p1);
             r_m1 = r_p1;
             er_m1 = er_p1;
-            ax_m1 = lane_diff2(r_p1);
+            fr_m1 = lane_diff(r_p1);
             du_m2 = du_m1;
             du_m1 = du_p1;
             dr_m2 = dr_m1;
@@ -649,7 +658,7 @@ __device__ __forceinline__ void adjoint_strip_step(float *lds, const AdjStripArg
 
             // ---- S4 at row g - 1: P(u) r and d = -div q ----
             const float ety = ty_ - tyy_p;
-            const float pr = adj_outer(txx_p, ety - ety_p, z, z_pp);
+            const float pr = adj_outer(lane_diff2(ftx_p), ety - ety_p, z, z_pp);
             const float d = adj_div(from_next_lane(qx_p) - from_prev_lane(qx_p), qy - qy_pp);
             dw[R] = d;
             wave_lds_sync();
@@ -661,7 +670,7 @@ __device__ __forceinline__ void adjoint_strip_step(float *lds, const AdjStripArg
             prr[jd * 64] = pr;
             ety_p = ety;
             tyy_p = ty_;
-            txx_p = lane_diff2(tx);
+            ftx_p = lane_diff(tx);
             z_pp = z_p;
             z_p = z;
             qy_pp = qy_p;
