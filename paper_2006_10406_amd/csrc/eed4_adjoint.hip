@@ -1176,7 +1176,13 @@ static int adjoint_shape(const eed4_params *p, RevStep t, hipStream_t s, int *sh
     const std::string key = adjoint_tune_key(t.R, t.B, t.H, t.W);
     if (tune_lookup(key, shape)) return EED4_OK;
     // the wide forward shapes map onto the same reverse strips as their heights
-    const int cands[] = {kShapeStrip, 0, 1, 2, kShapeStripTall, kShapeStripShort, kShapeStripTiny};
+    const int cands[] = {kShapeStrip, kShapeStripTall, kShapeStripShort, kShapeStripTiny, 0, 1, 2};
+    // The step is timed alone but runs beside the recompute, where instructions count:
+    // short segments and tiles, which issue more of them, have to be clearly faster.
+    // 2048^2 at R = 6: the tile 39 us alone against the 28-row strips' 38, the whole
+    // backward 1830 us against 1700; 2700x2900 at R = 8, 80 rows 2110 us, 28 rows 2340.
+    float margins[sizeof(cands) / sizeof(cands[0])];
+    for (float &m : margins) m = kTuneMarginRefetch;
     const size_t N = (size_t)t.B * t.H * t.W;
     // the strip candidates read the presmoothed state t.v
     const StepArgs a0 = make_args(p->sigma, t.R, p->tau, p->lambda, 0, model_of_flags(p->flags));
@@ -1193,8 +1199,7 @@ static int adjoint_shape(const eed4_params *p, RevStep t, hipStream_t s, int *sh
             return (int)EED4_OK;
         },
         [&](int, hipStream_t q) { return launch_reverse_step(t, p, p->cycle_len - 1, q); },
-        "adjoint autotune",
-        &best, nullptr);
+        "adjoint autotune", &best, nullptr, margins);
     if (rc != EED4_OK) return rc;
     tune_remember(key, best);
     *shape = best;

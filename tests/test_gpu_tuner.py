@@ -48,3 +48,25 @@ def test_first_call_costs_few_steps():
         step = rest / (n * M)
         print(f"{f.__name__}: first {first:.2f} ms, then {rest:.2f} ms, a step {1e3 * step:.1f} us")
         assert first - rest < 200 * step + 2.0
+
+
+def test_reverse_shape_of_2048_runs_well_beside_the_recompute():
+    # the reverse tiles (39 us a step alone) and the 28-row strips (38) differ by 8 % once the
+    # recompute runs beside them.  Measured against forced 28-row strips (recompute and reverse):
+    # 1.06 with the reverse strips chosen, 1.15 with the tiles; the bound lies between
+    announce("tuned backward at 2048x2048, R = 6")
+    u = torch.rand((2048, 2048), device="cuda")
+    mask, gu = (u < 0.05).to(torch.uint8), torch.ones_like(u)
+    ck = torch.stack([u, u])
+    g = [torch.empty_like(u), torch.empty_like(u), torch.empty(1, device="cuda")]
+
+    def run(shape):
+        flags = 0 if shape is None else eed4.EED4_FORCE_SHAPE(shape)
+        eed4.eed4_backward(ck, mask, u, eed4.params(0.02, 2.0, 0.05, 12, 2, flags=flags), 2, gu, *g)
+
+    eed4.eed4_inpaint(u.clone(), mask, u, eed4.params(0.02, 2.0, 0.05, 12, 1))   # the forward shape
+    for shape in (None, 0, 5):
+        run(shape)
+    best = {s: min(ms(lambda: run(s)) for _ in range(8)) for s in (None, 0, 5)}
+    print({str(s): f"{v:.3f} ms" for s, v in best.items()})
+    assert best[None] < 1.10 * min(best[0], best[5])
