@@ -43,12 +43,6 @@
 
 namespace eed4 {
 
-// Per-point pieces of the adjoint.  (gx, gy) = G = grad u_sigma; A = Hessian
-// of r, H = Hessian of u.  Outputs: D(G) : A, q = de/dG and s de/ds with
-// e = A : D(G) : H, s = |G|; mu depends on s/lambda only, so de/dlambda =
-// -(s/lambda) de/ds, and the 1/lambda goes into the per-step scale.  In the gradient frame n = G/|G|, t = n rotated by +90
-// degrees, e = A:H + (mu1 - 1) a1 h1 + 2 (mu3 - 1) a3 h3 with a1 = n.A.n,
-// a3 = t.A.n; d/ds and d/dtheta of it give q = (de/ds) n + (1/s)(de/dtheta) t.
 // Eigenvalue data of a tensor variant (diffusivities of Table 7, mu3 choices
 // of Sec. 3.1) at x = (s/lambda)^2: mu1 = g(x), mu3, their derivatives G1, G3
 // with respect to x, and Q1 = (mu1 - 1)/x, Q3 = (mu3 - 1)/x, written so that
@@ -96,6 +90,13 @@ __device__ __forceinline__ MuData model_mu_data(float x, int model)
     return m;
 }
 
+// Per-point pieces of the adjoint.  (gx, gy) = G = grad u_sigma; A = Hessian
+// of r, H = Hessian of u.  Outputs: D(G) : A, q = de/dG and s de/ds with
+// e = A : D(G) : H, s = |G|; mu depends on s/lambda only, so de/dlambda =
+// -(s/lambda) de/ds, and the 1/lambda goes into the per-step scale.  In the
+// gradient frame n = G/|G|, t = n rotated by +90 degrees, e = A:H +
+// (mu1 - 1) a1 h1 + 2 (mu3 - 1) a3 h3 with a1 = n.A.n, a3 = t.A.n; d/ds and
+// d/dtheta of it give q = (de/ds) n + (1/s)(de/dtheta) t.
 template <bool GEN = false>
 __device__ __forceinline__ void adjoint_point(float gx, float gy, float inv_lam2, float axx,
                                               float ayy, float axy, float hxx, float hyy,
@@ -242,7 +243,7 @@ struct AdjTileGeo {
     static constexpr int DS = DSn > PL + 64 ? DSn : PL + 64;  // row stride of d (a multiple of 4)
     static constexpr int NE = 6 * NG * 64, ND = DH * DS, NX = DH * 64, NP = TH * 64;
     static constexpr int LDS = NE + ND + NX + NP;
-    static_assert(TH > 0, "tile height");
+    static_assert(TH > 0 && rows_addressable(QH + 2), "tile height");
 };
 
 // Wave-tree sum of v, then the groups' sums in order; thread 0 writes scale * sum.
@@ -471,6 +472,7 @@ struct AdjStripGeo {
     static constexpr int NROW = M * U;                        // rows streamed per wave
     static constexpr int OH = NROW - 2 * h;                   // output rows per wave
     static constexpr int LDS = ND + P * 64;                   // floats of LDS per wave
+    static_assert(rows_addressable(NROW), "row offsets");
 };
 
 struct AdjStripArgs {
@@ -1130,7 +1132,7 @@ static BackwardLayout backward_layout(int B, int H, int W, int n, int R)
     size_t o = 0;
     // two sets of recompute buffers: cycle m-1 is recomputed while cycle m is reversed
     L.U = o; o = align_up(o + sizeof(float) * N * 2 * (size_t)(n > 1 ? n - 1 : 1));
-    // ... and K_sigma * u^{m,k}, k = 0 .. n-1, for the strip reverse step
+    // ... and K_sigma * u^{m,k}, k = 0 .. n-1, for the reverse step
     L.V = o; o = align_up(o + sizeof(float) * N * 2 * (size_t)(n > 0 ? n : 1));
     L.an = o; o = align_up(o + sizeof(float) * N);
     L.ac = o; o = align_up(o + sizeof(float) * N);
@@ -1162,9 +1164,8 @@ static std::string adjoint_tune_key(int R, int B, int H, int W)
 }
 
 // Reverse-step implementation: a forced shape (tile shapes select the tile
-// passes, strip shapes the strip kernel of that height; the reverse strip
-// has one column per lane), else the tuned
-// choice for this problem size, else the timing of one reverse step of each
+// kernel, strip shapes the strip kernel of that height; the reverse strip
+// has one column per lane), else the tuned choice for this problem size, else the timing of one reverse step of each
 // on the caller's data (t holds real buffers; what it writes is scratch).
 static int adjoint_shape(const eed4_params *p, RevStep t, hipStream_t s, int *shape)
 {
@@ -1184,7 +1185,7 @@ static int adjoint_shape(const eed4_params *p, RevStep t, hipStream_t s, int *sh
     float margins[sizeof(cands) / sizeof(cands[0])];
     for (float &m : margins) m = kTuneMarginRefetch;
     const size_t N = (size_t)t.B * t.H * t.W;
-    // the strip candidates read the presmoothed state t.v
+    // every candidate reads the presmoothed state t.v
     const StepArgs a0 = make_args(p->sigma, t.R, p->tau, p->lambda, 0, model_of_flags(p->flags));
     hipError_t e = launch_blur(t.R, t.u, const_cast<float *>(t.v), t.B, t.H, t.W, a0, s);
     if (e == hipSuccess) e = launch_fill(t.ac, N, 0.0f, s);
@@ -1281,7 +1282,7 @@ extern "C" int eed4_backward(const float *ckpt, const uint8_t *mask, const float
     float *Uset[2] = {Ubuf, Ubuf + nU * N};
     float *Vset[2] = {Vbuf, Vbuf + (size_t)n * N};
     std::vector<const float *> Ur[2] = {std::vector<const float *>(n), std::vector<const float *>(n)};
-    // u^{m,1..n-1} from the checkpoint, on s1, and (strip reverse step) v^{m,k} =
+    // u^{m,1..n-1} from the checkpoint, on s1, and v^{m,k} =
     // K_sigma * u^{m,k} for k = 0 .. n-1: the steps keep the v they compute, and
     // the last one, which no recomputed step forms, comes from the blur kernel
     auto recompute = [&](int m) -> hipError_t {

@@ -63,7 +63,7 @@ int run_shape(const eed4_params *p, int B, int H, int W);
 
 // Without a tuned choice, the single-image path uses workgroup tiles when the
 // problem has fewer 60 x 64 blocks than this, and strips otherwise.  Measured,
-// 60 x 32 tiles against the strips: 2048^2 (1155 blocks) 17.6 against 21.5 us at
+// 60 x 32 tiles against the strips: 2048^2 (1120 blocks) 17.6 against 21.5 us at
 // R = 3, 23.0 against 28.4 at R = 8; 2560^2 (1720) 24.5 against 21.9 and 31.1
 // against 30.4; 4096^2 55.5 against 43.6 and 68.8 against 55.2.
 constexpr long long kMinStripBlocks = 1700;
@@ -108,7 +108,8 @@ int default_step_shape(int R, int B, int H, int W);
 // strips, which fetch more of the halo rows their neighbours share again, have
 // to be clearly faster: in sustained runs they are at best level with the
 // default (8 x 1037x771 at R = 3: 25.9 against 25.8 us; 2560^2 24.9 and 22.9),
-// while a short tuning burst has at times put them a few percent ahead.
+// while a short tuning burst has at times put them a few percent ahead.  The tuner
+// of the reverse step takes this margin for every shape but its default.
 constexpr float kTuneMarginRefetch = 0.95f;
 inline float tune_margin(int first, int shape)
 {

@@ -37,6 +37,13 @@ __device__ __forceinline__ void sentinel_fill_wave(float *p, int n)
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
 }
 
+// A kernel addresses the rows of a plane that one wave or workgroup touches with
+// 32-bit byte offsets, which must stay below 2^31 (the offset of lanes without an
+// output pixel): fewer than 256 rows at the largest width.  The most are the 170
+// rows of a reverse strip of 136 output rows at R = 8; each geometry asserts it.
+constexpr int kMaxWidth = 1 << 21;
+constexpr bool rows_addressable(int rows) { return 4LL * kMaxWidth * rows < (1LL << 31); }
+
 // Per-launch constants of one inner FSI step.
 struct StepArgs {
     float w[2 * kRMax + 1];  // sampled Gaussian, w[j + R], j = -R..R, sums to 1

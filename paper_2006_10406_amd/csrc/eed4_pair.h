@@ -37,6 +37,7 @@ struct PairGeo {
     static constexpr int DS = D | 1;                                 // ring stride of a pair
     static constexpr int LDS = 2 * (64 + 2 * NP) * DS;               // floats of LDS per wave
     static_assert(D >= R + 2 && U % D == 0 && D % 4 == 0 && 2 * R <= 16, "ring geometry");
+    static_assert(rows_addressable(136 + 4 + PR), "row offsets");    // 136: the most rows
 };
 
 // Global loads of one stream row: the lane's two columns of u^k, and u^{k-1},

@@ -85,6 +85,7 @@ struct StripGeo {
     static constexpr int NROW = 2 * R + M * U;                // rows streamed per wave
     static constexpr int OH = NROW - 2 * h;                   // output rows per wave
     static constexpr int LDS = (NU + 2) * CS;                 // floats of LDS per wave
+    static_assert(rows_addressable(NROW), "row offsets");
 };
 
 // Per-wave constants of a strip step.
@@ -247,8 +248,8 @@ struct StripRow {
 // Addressing: every plane is seen through a buffer resource based at image
 // row b0 = max(Y0 - h, 0) (the lowest row a needed value comes from) and
 // covering nb = min(H - b0, NROW) rows, so a row offset is one 32-bit scalar
-// (the library keeps NROW * W * 4 below 2^31) and the per-lane column offsets
-// stay fixed for the whole strip.
+// (rows_addressable(NROW)) and the per-lane column offsets stay fixed for the
+// whole strip.
 
 template <int R, bool RES, int ROWS, bool GEN = false, bool VST = false>
 __device__ __forceinline__ void strip_step(float *ring, const StripArgs &s,

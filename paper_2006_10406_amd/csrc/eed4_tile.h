@@ -24,9 +24,11 @@
 // What bounds it: a tile is a chain of a global load, two barriers and about
 // OH + 4 rows of dependent arithmetic, and below about a million pixels that
 // chain and the launch are the whole time.  Stage C keeps OH + 4 independent
-// rows in flight, which the streaming strips cannot, so two waves a SIMD
-// already fill the vector unit; it reads the x pass from LDS instead of taking
-// it again for the 2R + 4 halo rows of every group.
+// rows in flight, which the streaming strips cannot, and reads the x pass from
+// LDS instead of taking it again for the 2R + 4 halo rows of every group.  On
+// larger images a wave still waits for 0.45 (64 x 32) to 0.56 (32 x 32) of its
+// cycles (4096^2, R = 6): a tile's loads and x pass overlap only with the stage C
+// of other workgroups on the CU.
 #pragma once
 
 #include "eed4_internal.h"
@@ -72,6 +74,7 @@ struct TileGeo {
     static constexpr int SMEM = NU + NX;                  // floats of LDS
     static constexpr int NV = OH + 4, NT = OH + 2;        // rows of v and of T per group
     static constexpr int IA = (NA + NTH - 1) / NTH;       // stage A items per thread
+    static_assert(rows_addressable(UH), "row offsets");
 };
 
 // Stage A: 16 bytes of u per item, from row y0 / column xs of the mirrored
@@ -200,7 +203,7 @@ __device__ __forceinline__ void step_tile(float *smem, const float *ucur, const 
     if constexpr (kLdsSentinel) sentinel_fill_block(smem, G::SMEM);
 
     // Every plane through a buffer resource based at the lowest row a needed
-    // value comes from (the library keeps UH * W * 4 below 2^31); lanes without
+    // value comes from (rows_addressable(UH)); lanes without
     // an output pixel use an offset beyond it, so they read 0 and store nothing.
     const unsigned W4 = 4u * (unsigned)W;
     const int y0 = Y0 - G::h, b0 = y0 > 0 ? y0 : 0;
