@@ -25,10 +25,10 @@
 // OH + 4 rows of dependent arithmetic, and below about a million pixels that
 // chain and the launch are the whole time.  Stage C keeps OH + 4 independent
 // rows in flight, which the streaming strips cannot, and reads the x pass from
-// LDS instead of taking it again for the 2R + 4 halo rows of every group.  On
-// larger images a wave still waits for 0.45 (64 x 32) to 0.56 (32 x 32) of its
-// cycles (4096^2, R = 6): a tile's loads and x pass overlap only with the stage C
-// of other workgroups on the CU.
+// LDS instead of taking it again for the 2R + 4 halo rows of every group.  Of its
+// cycles a wave waits for a load, LDS or a barrier 0.46 on 512^2 (R = 5, 32 x 16),
+// 0.32 on 1037x771 (R = 8, 32 x 32) and 0.40 on 1024^2 (64 x 32), and is ready while
+// another wave issues 0.17, 0.31 and 0.18; on 4096^2 (R = 6) 0.19 and 0.45.
 #pragma once
 
 #include "eed4_internal.h"
