@@ -174,12 +174,15 @@ int capture_graph(const std::function<int(hipStream_t)> &enqueue, hipGraphExec_t
     return EED4_OK;
 }
 
+// A graph of nc cycles of job j, of which only the last forms the residual.
 int capture_cycle(const CycleJob &j, hipGraphExec_t *exec, int nc)
 {
     return capture_graph(
         [&](hipStream_t cs) {
-            for (int c = 0; c < nc; ++c) {
-                const int rc = enqueue_cycle(j, cs);
+            CycleJob c = j;
+            for (int i = 0; i < nc; ++i) {
+                c.residual = j.residual && i == nc - 1;
+                const int rc = enqueue_cycle(c, cs);
                 if (rc != EED4_OK) return rc;
             }
             return (int)EED4_OK;
@@ -194,14 +197,13 @@ int capture_cycle(const CycleJob &j, hipGraphExec_t *exec, int nc)
 // kMaxCachedGraphs jobs a call captures its own graph and destroys it at the
 // end, as without the cache.  Entries are never evicted (a launch of an
 // evicted graph might still be in flight on another stream).  A run of a fixed
-// number of cycles holds up to three (four cycles, one, and the last one with
-// its residual), two where it has no group of four.  (With the last cycle
-// launched step by step instead, small64 took 667 us against 656.)
+// number of cycles holds up to two: four cycles, and the one to four that end it,
+// or, with checkpoints, one cycle without and one with its residual.
 constexpr size_t kMaxCachedGraphs = 128;
 constexpr int kGraphCycles = 4;    // cycles per graph when no host work sits between cycles
 
 struct CycleKey {
-    int dev, nc, residual;         // device, cycles per graph, residual formed
+    int dev, nc, residual;         // device, cycles per graph, residual formed (in the last)
     const void *S, *X, *Y, *Out, *mask, *partials, *sums;
     int B, H, W, R, shape, n, model;
     float sigma, tau, lambda;      // finite (checked), so < is a strict order
@@ -571,10 +573,11 @@ constexpr int kDirectCkptCycles = 4;
 // or a single cycle).  Without a history only the last cycle's residual is
 // ever read, so the others are not formed (a residual step and its reduction
 // cost 3 us on 64^2, where a cycle of 10 takes 32, and 25 us on 4096^2).
-// Without checkpoints or history nothing sits between the cycles: whole groups
-// of kGraphCycles cycles run as one graph each (one launch, and one gap between
-// launches, per group), the rest one by one.  The group size is fixed, so calls
-// of any length share one cached graph.
+// Without checkpoints or history nothing sits between the cycles: groups of
+// kGraphCycles cycles run as one graph each (one launch, and one gap between
+// launches, per group), and so do the one to kGraphCycles cycles that end the run,
+// the last of them with its residual.  The group size is fixed, so calls of any
+// length share one cached graph.
 static int run_fixed(const CycleJob &j, int M, const eed4_params *p, float *ckpt,
                      double *hist_dev, hipStream_t s, RunResult *out)
 {
@@ -582,7 +585,7 @@ static int run_fixed(const CycleJob &j, int M, const eed4_params *p, float *ckpt
     const size_t N = (size_t)B * j.H * j.W;
     CycleJob plain = j;                    // a cycle whose residual nobody reads
     plain.residual = hist_dev != nullptr;
-    hipGraphExec_t exec = nullptr, last = nullptr, multi = nullptr;
+    hipGraphExec_t exec = nullptr, last = nullptr, multi = nullptr;   // last: the last `tail` cycles
     bool own_exec = false, own_last = false, own_multi = false;
     int rc = EED4_OK;
     hipError_t e = hipSuccess;
@@ -591,22 +594,24 @@ static int run_fixed(const CycleJob &j, int M, const eed4_params *p, float *ckpt
     // needs its steps launched one by one (a graph holds its buffers).
     const bool direct = ckpt && N >= kDirectCkptPixels && M >= kDirectCkptCycles;
     const bool graphs = !(p->flags & EED4_NO_GRAPH) && !direct;
+    const int tail = graphs && !ckpt && !hist_dev ? (M - 1) % kGraphCycles + 1 : 1;
     int m = 0;
     if (direct) {
         e = hipMemcpyAsync(ckpt, j.S, sizeof(float) * N, hipMemcpyDeviceToDevice, s);
         if (e != hipSuccess) rc = hip_fail(e, "checkpoint copy");
     }
-    if (graphs && !ckpt && !hist_dev && M > kGraphCycles) {
+    if (graphs && !ckpt && !hist_dev && M > tail) {
         rc = cycle_graph(plain, kGraphCycles, &multi, &own_multi);
-        for (; rc == EED4_OK && m + kGraphCycles < M; m += kGraphCycles) {
+        for (; rc == EED4_OK && m < M - tail; m += kGraphCycles) {
             trace_mark("eed4 cycles %d-%d queued", m, m + kGraphCycles - 1);
             e = hipGraphLaunch(multi, s);
             if (e != hipSuccess) rc = hip_fail(e, "graph launch");
         }
     }
-    if (rc == EED4_OK && graphs && m < M - 1) rc = cycle_graph(plain, 1, &exec, &own_exec);
-    if (rc == EED4_OK && graphs) rc = cycle_graph(j, 1, &last, &own_last);
+    if (rc == EED4_OK && graphs && m < M - tail) rc = cycle_graph(plain, 1, &exec, &own_exec);
+    if (rc == EED4_OK && graphs) rc = cycle_graph(j, tail, &last, &own_last);
     for (; rc == EED4_OK && m < M; ++m) {
+        if (m == M - tail) m = M - 1;              // the last `tail` cycles are one graph
         trace_mark("eed4 cycle %d queued", m);
         if (ckpt && !direct) {
             e = hipMemcpyAsync(ckpt + (size_t)m * N, j.S, sizeof(float) * N,

@@ -7,6 +7,8 @@ for multi-cycle runs at equal cycle counts (grey values in [0, 1]).  The
 FP32-vs-FP64 error of every case is printed.  Inputs come from the seeded
 generator.
 """
+import time
+
 import numpy as np
 import pytest
 
@@ -444,3 +446,47 @@ def test_run_to_tolerance_equals_fixed_cycle_run():
         assert st.residual == st2.residual and st.rel_residual == st2.rel_residual
         seen.add(c % 2)
     assert seen == {0, 1}, "both buffer parities should be covered"
+
+
+@pytest.mark.parametrize("M", [1, 2, 3, 4, 5, 6, 7, 8, 9, 13])
+@pytest.mark.parametrize("n", [1, 2, 5])
+def test_every_length_of_a_fixed_run_equals_direct_launches(M, n):
+    # groups of four cycles and the one to four that end the run are graphs: each call, replays of
+    # the cached graphs among them, equals the run launched step by step
+    announce(f"fixed run of {M} cycles of {n}: graphs against direct launches")
+    pr = make_problem(70, 53, 6, True, 0.01, 0.06, 800 + M)
+    mask, known = to_dev(pr["mask"]), to_dev(pr["known"])
+
+    def run(u, flags):
+        st, _ = eed4.eed4_inpaint(u, mask, known, eed4.params(0.03, 1.0, 0.05, n, M, flags=flags))
+        torch.cuda.synchronize()
+        return st.cycles, st.residual, st.rel_residual
+
+    ref = to_dev(pr["u_init"])
+    rst = run(ref, eed4.EED4_NO_GRAPH)
+    u = to_dev(pr["u_init"])
+    for _ in range(3):
+        u.copy_(to_dev(pr["u_init"]))
+        assert run(u, 0) == rst and torch.equal(u, ref)
+        (ref + 1).sum().item()             # the program's own work between the replays
+
+
+def test_a_run_of_four_cycles_is_one_graph_launch():
+    # 4 cycles of 2 steps on 8 x 74x26 have the steps and the one residual of a cycle of 8; each
+    # graph launch beyond the first costs 9 us of some 75, three of them 36 %: half of that is allowed
+    announce("4 cycles of 2 steps on 8 x 74x26 against a cycle of 8")
+    pr = make_problem(74, 26, 4, True, 0.01, 0.06, 900)
+    u0 = to_dev(np.stack([pr["u_init"]] * 8))
+    mask, known = (to_dev(np.stack([pr[k]] * 8)) for k in ("mask", "known"))
+    times = {4: [], 1: []}
+    for _ in range(80):
+        for M in times:
+            u = u0.clone()
+            p = eed4.params(0.03, 1.0, 0.05, 8 // M, M, flags=eed4.EED4_FORCE_SHAPE(10))
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            eed4.eed4_inpaint(u, mask, known, p)
+            times[M].append(time.perf_counter() - t)
+    t4, t1 = (1e6 * sorted(times[M])[20] for M in (4, 1))
+    print(f"4 cycles of 2: {t4:.1f} us, a cycle of 8: {t1:.1f} us")
+    assert t4 < 1.18 * t1
