@@ -165,21 +165,43 @@ __global__ __launch_bounds__(256) void strip_keepv_kernel(const float *ucur, con
 }
 
 // v = K_sigma * u on the mirror-extended image (the presmoothing of Sec. 2.2)
-// over the 64 x 16 tiles of the fused step: its stages A and B and its y pass,
-// so v is bitwise the one a step from u computes.  (One LDS read per tap and
-// pixel, as before, took 29.8 us on 2048^2 at R = 6, three times a copy.)
+// over 64 x 16 tiles with the fused step's stages A and B and its y pass, so v is
+// bitwise the one a step from u computes.  (One LDS read per tap and pixel took
+// 17.4 us on 2048^2 at R = 6, now 10.6.)  All 64 columns are outputs: no stencil
+// follows that would take two of them on each side (64 x 2374x61 at R = 4 / 8:
+// 30.5 / 40.5 us; with 60 output columns, two tiles across, 76.5 / 80).
 constexpr int kBlurTW = 64, kBlurTH = 16;
+
+// Geometry of a blur tile; the names are those of the step's tiles.
+template <int R>
+struct BlurGeo {
+    static constexpr int OH = kBlurTH * kBlurTW / kThreads;   // output rows per wave
+    static constexpr int h = R;                               // input halo
+    static constexpr int SC = h;                              // staged columns left of the outputs
+    static constexpr int OFF = SC - h;                        // first tap of lane 0's column
+    static constexpr int UH = kBlurTH + 2 * h;                // staged rows
+    static constexpr int UQ = (SC + kBlurTW + h + 3) / 4;     // 16-byte loads per staged row
+    static constexpr int NF4 = (OFF + 4 + 2 * R + 3) / 4;     // 16-byte LDS reads per x-pass item
+    static constexpr int NQ = kBlurTW / 4;                    // x-pass items per row
+    static constexpr int UW = 4 * (UQ > NF4 + NQ - 1 ? UQ : NF4 + NQ - 1);   // row stride of u
+    static constexpr int NA = UH * UQ, NB = UH * NQ;          // items of stages A and B
+    static constexpr int NU = UH * UW, NX = UH * kBlurTW;
+    static constexpr int SMEM = NU + NX;                      // floats of LDS
+    static constexpr int IA = (NA + kThreads - 1) / kThreads; // stage A items per thread
+    static_assert(rows_addressable(UH), "row offsets");
+};
+
 template <int R>
 __global__ __launch_bounds__(256) void blur_kernel(const float *u_all, float *v_all, int H, int W,
                                                    int nbx, int tiles_per_img, StepArgs a)
 {
-    using G = TileGeo<R, kBlurTW, kBlurTH>;
+    using G = BlurGeo<R>;
     __shared__ __attribute__((aligned(16))) float smem[G::SMEM];
     float *sU = smem, *sX = smem + G::NU;
     const int tile = __builtin_amdgcn_readfirstlane(xcd_tile(blockIdx.x, gridDim.x));
     const int b = tile / tiles_per_img;
     const int t = tile - b * tiles_per_img;
-    const int Y0 = (t / nbx) * kBlurTH, X0 = (t - (t / nbx) * nbx) * G::SW;
+    const int Y0 = (t / nbx) * kBlurTH, X0 = (t - (t / nbx) * nbx) * kBlurTW;
     const int lane = threadIdx.x & 63;
     const int grp = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), Yg = Y0 + grp * G::OH;
     if constexpr (kLdsSentinel) sentinel_fill_block(smem, G::SMEM);
@@ -197,9 +219,9 @@ __global__ __launch_bounds__(256) void blur_kernel(const float *u_all, float *v_
     __syncthreads();
     tile_xpass<R, kBlurTW, G, kThreads>(sU, sX, wv);
     __syncthreads();
-    const int c = X0 - 2 + lane;
-    const unsigned vo = lane >= 2 && lane < 62 && c < W ? 4u * (unsigned)c : kOffNone;
-    const float *px = sX + 64 * (grp * G::OH + 2) + lane;            // row Yg - R
+    const int c = X0 + lane;
+    const unsigned vo = c < W ? 4u * (unsigned)c : kOffNone;
+    const float *px = sX + 64 * (grp * G::OH) + lane;                // row Yg - R
 #pragma unroll
     for (int j = 0; j < G::OH; ++j) {
         const float x = ypass_sym<R>(wv, [&](int t) { return px[64 * (j + R + t)]; });
@@ -431,8 +453,7 @@ template <int R>
 static hipError_t launch_blur_r(const float *u, float *v, int B, int H, int W, const StepArgs &a,
                                 hipStream_t s)
 {
-    const int nbx = (W + tile_cols(kBlurTW) - 1) / tile_cols(kBlurTW);
-    const int nby = (H + kBlurTH - 1) / kBlurTH;
+    const int nbx = (W + kBlurTW - 1) / kBlurTW, nby = (H + kBlurTH - 1) / kBlurTH;
     return launch_batches(B, (long long)nbx * nby, 1, 256, [&](int b0, int, unsigned blocks) {
         const size_t o = (size_t)b0 * H * W;
         hipLaunchKernelGGL((blur_kernel<R>), dim3(blocks), dim3(256), 0, s, u + o, v + o, H, W, nbx,

@@ -203,3 +203,48 @@ def test_reverse_step_takes_exact_differences_of_neighbours(H, W, flags, sigma):
     torch.cuda.synchronize()
     assert np.array_equal(g[1].cpu().numpy(), want)
     assert not g[0].any() and not g[2].any()
+
+
+@pytest.mark.parametrize("sigma", [0.0, 0.3, 0.6, 1.0, 1.3, 1.6, 2.0, 2.3, 2.6])   # R = 0 .. 8
+@pytest.mark.parametrize("H,W", [(15, 63), (16, 64), (17, 65), (33, 129), (48, 192), (50, 84), (5, 3)])
+def test_presmoothing_at_the_edges_of_its_tiles(H, W, sigma):
+    # with one step a cycle every presmoothed state comes from the 64 x 16 tiles of the blur
+    announce(f"blur tiles {H}x{W} sigma={sigma}")
+    b = {k: np.stack([make_problem(H, W, 4, True, 0.01, 0.06, 300 + i + H)[k] for i in range(2)])
+         for k in ("image", "mask", "known", "u_init")}
+    gu = np.random.default_rng(H * W).normal(size=b["u_init"].shape) * 1e-2
+    _, ck, gk, gi, _ = gpu_forward_backward(b, 0.04, sigma, 0.05, 1, 2, gu,
+                                            flags=eed4.EED4_FORCE_SHAPE(5))
+    # dL/dlambda, one number an image, says nothing of a tile's edge, and for a random dL/du its
+    # terms cancel: at 33x129, sigma 2.3, it is 1.2e-4 off whichever kernel presmooths
+    ogk, ogi, _ = oracle.backward(ck.astype(np.float64), b["mask"], b["known"], 0.04, sigma, 0.05, 1,
+                                  gu)
+    m = b["mask"] != 0
+    assert np.all(gk[~m] == 0) and np.all(gi[m] == 0)
+    assert_grad_parity(gk[m], ogk[m], f"{H}x{W} s{sigma} dL/df")
+    assert_grad_parity(gi[~m], ogi[~m], f"{H}x{W} s{sigma} dL/du_init")
+
+
+def test_presmoothing_of_64_columns_is_one_tile_wide():
+    # 64 x 2374x61 and x60 at sigma 1.3: the reverse strips are two wide in both, and the rest of the
+    # backward differs by the pixels, 1.017.  Two blur tiles across add 40 us of some 200 at 61
+    announce("backward of one step, 64 x 2374x61 against 64 x 2374x60")
+    p = eed4.params(0.02, 1.3, 0.05, 1, 1, flags=eed4.EED4_FORCE_SHAPE(5))
+    calls, best = {}, {}
+    for W in (61, 60):
+        u = torch.rand((64, 2374, W), device="cuda")
+        mask, gu = (u < 0.05).to(torch.uint8), torch.randn_like(u)
+        g = (torch.empty_like(u), torch.empty_like(u), torch.empty(64, device="cuda"))
+        calls[W] = (u[None].contiguous(), mask, u.clone(), p, 1, gu, *g)
+        best[W] = 1e9
+    for _ in range(40):
+        for W, args in calls.items():
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            torch.cuda.synchronize()
+            a.record()
+            eed4.eed4_backward(*args)
+            b.record()
+            b.synchronize()
+            best[W] = min(best[W], 1e3 * a.elapsed_time(b))
+    print(f"61 columns {best[61]:.1f} us, 60 columns {best[60]:.1f} us")
+    assert best[61] < 1.1 * best[60]
