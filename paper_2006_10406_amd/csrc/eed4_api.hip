@@ -376,7 +376,9 @@ int run_shape(const eed4_params *p, int B, int H, int W)
 int default_step_shape(int R, int B, int H, int W)
 {
     const long long blocks = (long long)((W + 59) / 60) * ((H + 63) / 64) * B;
-    return blocks < kMinStripBlocks ? 2 : kShapeStrip;
+    if (blocks >= kMinStripBlocks) return kShapeStrip;
+    const bool two_tiles = W > tile_cols(32) && W <= 32;
+    return two_tiles && blocks >= kMinNarrowBlocks ? kShapeStripTiny : 2;
 }
 
 // Times the inner steps of every candidate shape (tune_candidates) and remembers

@@ -67,6 +67,12 @@ int run_shape(const eed4_params *p, int B, int H, int W);
 // R = 3, 23.0 against 28.4 at R = 8; 2560^2 (1720) 24.5 against 21.9 and 31.1
 // against 30.4; 4096^2 55.5 against 43.6 and 68.8 against 55.2.
 constexpr long long kMinStripBlocks = 1700;
+// Images 29 to 32 wide need two 32 x 32 tiles across (28 output columns each), the
+// second nearly empty, and one strip: from this many blocks on they run 8-row
+// strips.  Tiles against strips, us a step at R = 2 / R = 8: 43 x 1024x29 (688
+// blocks) 18.0 and 13.4 / 23.1 and 20.6, 84 x 1024x29 (1344) 28.8 and 20.4 / 37.5 and
+// 29.3; 21 x 1024x29 (336) 9.8 and 8.3 / 12.9 and 12.1, but at R = 5 10.7 and 11.6.
+constexpr long long kMinNarrowBlocks = 512;
 
 // The autotuners keep the default shape unless another is faster by more than
 // this factor, so shapes within timing noise of each other do not swap between

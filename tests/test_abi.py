@@ -208,3 +208,16 @@ def test_saved_choices_of_other_kernels_are_not_used(lib, tmp_path):
                          cwd=root, env=dict(os.environ, EED4_AUTOTUNE_CACHE=str(f)), check=True)
     old, new, none = map(int, out.stdout.split()[-3:])
     assert (old, new) == (none, 6) and none != 6
+
+
+def test_untuned_shape_of_images_of_up_to_32_columns(lib):
+    # 29 to 32 columns need two 32 x 32 tiles across (28 output columns each): 8-row strips from 512
+    # blocks of 60 x 64 on, the strips' own rule above
+    import ctypes
+    import paper_2006_10406_amd as e
+    p = e.params(0.03, 1.0, 0.05, 10, 2)
+    q = lambda B, H, W: lib.eed4_step_shape(B, H, W, ctypes.byref(p))
+    for W in (29, 30, 31, 32):
+        assert [q(*s) for s in ((511, 64, W), (512, 64, W), (1699, 64, W), (1700, 64, W))] == [2, 6, 6, 3]
+    for W in (28, 33, 61):
+        assert q(700, 64, W) == 2

@@ -81,3 +81,29 @@ def test_narrow_images_do_not_run_half_empty_strips():
             best[s] = min(best[s], a.elapsed_time(b) / 20)
     print(f"shape 3 {1e3 * best[3]:.1f} us, shape 7 {1e3 * best[7]:.1f} us")
     assert best[3] < 0.93 * best[7]
+
+
+@pytest.mark.parametrize("sigma", [0.6, 2.6])
+def test_untuned_images_of_32_columns_do_not_run_half_empty_tiles(sigma):
+    # 64 x 1200x32 before any tuning: two 32 x 32 tiles across, the second with 4 columns of 28, took
+    # 1.35 to 1.4 of the time of 8-row strips
+    announce(f"64 x 1200x32 untuned against its strips and tiles, sigma={sigma}")
+    u = torch.rand((64, 1200, 32), device="cuda")
+    mask = (u < 0.05).to(torch.uint8)
+    out = {}
+    best = {}
+    for _ in range(12):
+        for s in (None, 6, 2):
+            p = eed4.params(0.03, sigma, 0.05, 15, 1, flags=0 if s is None else eed4.EED4_FORCE_SHAPE(s))
+            out[s] = torch.empty_like(u)
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            eed4.eed4_fsi_step(u, u, out[s], mask, p, 1)
+            a.record()
+            for _ in range(20):
+                eed4.eed4_fsi_step(u, u, out[s], mask, p, 1)
+            b.record()
+            b.synchronize()
+            best[s] = min(best.get(s, 1e9), a.elapsed_time(b) / 20)
+    print(" ".join(f"{s}: {1e3 * t:.1f} us" for s, t in best.items()))
+    assert torch.equal(out[None], out[6]) and torch.equal(out[None], out[2])
+    assert best[None] < 1.1 * min(best[6], best[2])
